@@ -220,7 +220,7 @@ kx_status kx_production_rates(const kx_mech *mech, int64_t n, const double *T,
  * relative); and the Troe / SRI blending factor F (eq:blend).  Everything else
  * stays FP64: the species Gibbs energies and K_c factors, the third-body sums,
  * the products of concentrations, the bracket of forward minus reverse terms,
- * and the wdot sum (Neumaier-compensated across groups of eight terms).  The
+ * and the wdot sum (Neumaier-compensated across groups of four or eight terms).  The
  * result is within 1e-5 of the FP64 value relative to s_k = sum_i |nu_ki|
  * |R_i| (the magnitude of the terms that cancel into wdot_k); where s_k >>
  * |wdot_k| the plain relative error can exceed 1e-5.  Inputs and outputs are

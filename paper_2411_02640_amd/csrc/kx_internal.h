@@ -21,6 +21,7 @@ constexpr int kMaxSpecies = 256;     // species per mechanism (4 per lane)
 constexpr int kMaxFitOrder = 8;
 constexpr int kWave = 64;
 constexpr int kMaxQss = 64;          // QSS species per mechanism (one wave of rows)
+constexpr int kWideMaxSpecies = 128; // one-lane-per-point kernels (species rows in LDS)
 constexpr int kChunkMax = 192;       // reactions per chunk of the gather lists, at most
 
 // Reaction flags.
@@ -68,7 +69,8 @@ struct alignas(16) DevAux {
     double dalpha[kInlineEff];
     uint16_t eoff[kInlineEff];
     int32_t has_T2, ext_off, ext_cnt;
-    int32_t plog_off, plog_cnt, pad;
+    int32_t plog_off, plog_cnt;
+    int32_t eff_cnt;         // inline efficiencies in use
     // explicit forward orders: LDS byte offset of the species pair and the
     // order (unused entries have order 0)
     double oval[kMaxOrd];
@@ -81,6 +83,30 @@ static_assert(sizeof(DevAux) == 224, "DevAux layout");
 // last).  48 bytes.
 struct alignas(16) DevPlog {
     double lnp, lnA, beta, ER, inv_dlnp, pad;
+};
+
+// One reaction of the one-lane-per-point kernels (kx_wide.h), in kernel order:
+// k_f = 2^(lA + beta log2 T - ER / T) in the FP64 table (lA = log2 A, ER =
+// E_a log2(e) / R), e^(lA + beta ln T - ER / T) in the mixed path's; where
+// kWideConst is set, beta holds k_f = A itself and ER is 0.  r01 / p01 are the
+// species of the first two molecules of either side (16 bits each), rp2 those
+// of the third ones; meta holds kWide* bits and the DevAux index in its upper
+// half.  40 bytes: the scalar cache holds 16 KB, so the table's size counts.
+struct DevWide {
+    double lA, beta, ER;
+    uint32_t r01, p01, rp2, meta;
+};
+static_assert(sizeof(DevWide) == 40, "DevWide layout");
+enum : uint32_t {
+    kWideConst = 1,       // k_f = A without an exponential
+    kWidePlog = 2,        // k_f from the pressure table
+    kWideThird = 4,       // a side has a third molecule
+    kWideOrders = 8,      // explicit forward orders
+    kWideThirdBody = 16,  // [X]_i enters (three-body and falloff)
+    kWideFalloff = 32,
+    kWideTroe = 64,
+    kWideSri = 128,
+    kWideChemAct = 256,
 };
 
 struct alignas(16) DevEff {
@@ -106,6 +132,19 @@ static_assert(sizeof(DevSpecies) == 256, "DevSpecies layout");
 // one (k-block, j) step are contiguous for scalar loads.
 constexpr int kKB = 8;
 
+// Shape of a one-lane-per-point workgroup and how its waves divide the species.
+struct WideMap {
+    int32_t chunk, nchunks;  // reactions per chunk (rate rows in LDS), chunks
+    const int32_t *species;  // [waves][8] species of a wave (-1: none), split so that the
+                             // waves' gather lists are about equally long
+    const uint32_t *start;   // [waves] first 16-byte word of a wave's gather stream
+    const uint4 *gather;     // streams: per wave and chunk a header (groups of the wave's
+                             // species, 8 bits each, in the first two words), then the groups
+                             // of four entries: the rate row of the reaction (listed |nu|
+                             // times), the sign of nu in bit 31; padding entries name the row
+                             // of zeros
+};
+
 struct MechDev {
     int32_t ns, nr, nchunks;   // species, reactions, reaction chunks for the gather
     int32_t chunk;             // reactions per chunk (multiple of 64)
@@ -128,11 +167,21 @@ struct MechDev {
                                // 16 * slot_in_chunk per lane and group (a species with
                                // |nu''-nu'| = 2 or 3 lists the slot that many times);
                                // padding entries read the zero slot after the chunk
-    const int32_t *gmgrp;      // [nchunks] the rates kernel's lists: groups per chunk
-    const int32_t *gmoff;      // [nchunks] first group of each chunk
-    const uint4 *gment;        // [group][64 * gpass][2]: as gent, one list per species
-                               // with the +q and -q entries together, the sign of an
-                               // entry in bit 31 (set: -q) above its LDS byte offset
+    // One-lane-per-point kernels (kx_wide.h); wnw = 0 above kWideMaxSpecies.
+    int32_t wnw;               // waves per workgroup (4, 8, 12 or 16)
+    int32_t nplog;             // PLOG reactions
+    const DevWide *wrx;        // [nr] FP64 (base 2); wrx32: the mixed path's
+    const DevWide *wrx32;
+    const DevAux *waux;        // [naux] FP64: exponents in base 2 (k_0's lnA0 is log2 A0;
+                               // ER0, 1/T***, 1/T*, T**, b, 1/c carry log2 e; ln d is log2 d)
+    const DevPlog *wplog;      // [nplog points] exponents in base 2
+    const double *wsp;         // [ns][16] -G/(RT ln 2) = c0 log2 T + c1 T + ... + c4 T^4 +
+                               // c5 / T + c6 of both ranges (fields 0..6, 7..13), T_mid, 1/W
+                               // (0 for a QSS species)
+    // 0: wnw waves, the LDS shared by several workgroups of a CU; 1: 16 waves with
+    // the same chunks (so that the mixed path's compensated groups stay the same);
+    // 2: 16 waves, as many rate rows as the LDS holds
+    WideMap wmaps[3];
     // transport (FP64)
     const double *W;           // [ns]
     const double *visc;        // [ns][order]

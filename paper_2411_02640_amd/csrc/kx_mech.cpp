@@ -48,6 +48,45 @@ template <class T> size_t add_vec(Blob &b, const std::vector<T> &v)
     return b.add(v.data(), v.size() * sizeof(T));
 }
 
+// Shape of the one-lane-per-point kernels: waves per workgroup and reactions per
+// chunk.  The rate rows fill what the species rows leave of a workgroup's share
+// of the 160 KB of LDS: as many workgroups per CU as 24 waves allow with at
+// least 24 rows each (above 56 species the species rows take more than half of
+// the LDS, so one workgroup of 16 waves).  Measured on 2^20 points, 53 species:
+// two workgroups of 12 waves 1.00 ms, two of 8 waves 1.28, one of 16 waves with
+// 192 rows 1.36.
+struct WideShape {
+    int nw = 0, chunk = 0, nchunks = 0;
+};
+WideShape wide_shape(int ns, int nr)
+{
+    WideShape s;
+    if (ns > kWideMaxSpecies || nr == 0) return s;
+    s.nw = ns <= 16 ? 4 : (ns <= 32 ? 8 : (ns <= 56 ? 12 : 16));
+    const int need = std::min(24, nr);
+    int groups = (s.nw == 16 ? 16 : 24) / s.nw, rows = 0;
+    for (; groups >= 1; --groups) {
+        rows = (160 * 1024 / groups - 256) / 512 - (2 * (ns + 2) + 1);
+        if (rows >= need) break;
+    }
+    s.chunk = std::max(s.nw, std::min({rows, kChunkMax, nr + s.nw - 1}) / s.nw * s.nw);
+    s.nchunks = (nr + s.chunk - 1) / s.chunk;
+    return s;
+}
+
+// The shape for calls of few tiles: every tile has a CU to itself, so 16 waves
+// and all of the LDS (53 species, 2000 points: 2 chunks instead of 7, 23 against
+// 26 us a call).
+WideShape wide_shape_alone(int ns, int nr)
+{
+    WideShape s;
+    s.nw = 16;
+    const int rows = (160 * 1024 - 256) / 512 - (2 * (ns + 2) + 1);
+    s.chunk = std::min({rows, kChunkMax, nr + s.nw - 1}) / s.nw * s.nw;
+    s.nchunks = (nr + s.chunk - 1) / s.chunk;
+    return s;
+}
+
 // Net stoichiometric coefficient nu''_ki - nu'_ki of species k in reaction i.
 int net_nu(const kx_mech_desc *d, int i, int k)
 {
@@ -57,6 +96,69 @@ int net_nu(const kx_mech_desc *d, int i, int k)
     for (int e = d->prod_ptr[i]; e < d->prod_ptr[i + 1]; ++e)
         if (d->prod_sp[e] == k) nu += d->prod_nu[e];
     return nu;
+}
+
+// The species of each wave of a shape and the waves' gather streams (WideMap).
+void wide_gather(const kx_mech_desc *d, const std::vector<int> &perm, const WideShape &ws,
+                 std::vector<int32_t> &species, std::vector<uint32_t> &start,
+                 std::vector<uint32_t> &gather)
+{
+    const int ns = d->n_species, nr = d->n_reactions, nw = ws.nw;
+    // (reaction in kernel order, net nu) of every species
+    std::vector<std::vector<std::pair<int, int>>> rows(ns);
+    for (int s = 0; s < nr; ++s) {
+        const int i = perm[s];
+        for (int side = 0; side < 2; ++side) {
+            const int32_t *ptr = side ? d->prod_ptr : d->reac_ptr;
+            const int32_t *sp = side ? d->prod_sp : d->reac_sp;
+            const int32_t *nu = side ? d->prod_nu : d->reac_nu;
+            for (int e = ptr[i]; e < ptr[i + 1]; ++e) {
+                auto &r = rows[sp[e]];
+                const int v = side ? nu[e] : -nu[e];
+                if (!r.empty() && r.back().first == s)
+                    r.back().second += v;
+                else
+                    r.push_back({s, v});
+            }
+        }
+    }
+    // longest list first, to the wave with the shortest total so far that has a
+    // slot free (a list costs about four entries more than it holds)
+    std::vector<int> len(ns, 0), order(ns), load(nw, 0), used(nw, 0);
+    for (int k = 0; k < ns; ++k)
+        for (auto &e : rows[k]) len[k] += std::abs(e.second);
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return len[a] > len[b]; });
+    species.assign((size_t)nw * 8, -1);
+    const int cap = (ns + nw - 1) / nw;
+    for (int k : order) {
+        int best = -1;
+        for (int w = 0; w < nw; ++w)
+            if (used[w] < cap && (best < 0 || load[w] < load[best])) best = w;
+        species[best * 8 + used[best]++] = k;
+        load[best] += len[k] + 4;
+    }
+    for (int w = 0; w < nw; ++w) {
+        start.push_back((uint32_t)(gather.size() / 4));
+        std::vector<size_t> at(8, 0);  // next entry of each species' list
+        for (int c = 0; c < ws.nchunks; ++c) {
+            const size_t head = gather.size();
+            gather.resize(head + 4, 0);
+            for (int q = 0; q < 8; ++q) {
+                const int k = species[w * 8 + q];
+                if (k < 0) continue;
+                const size_t first = gather.size();
+                for (; at[q] < rows[k].size() && rows[k][at[q]].first < (c + 1) * ws.chunk; ++at[q]) {
+                    const auto &e = rows[k][at[q]];
+                    for (int u = 0; u < std::abs(e.second); ++u)
+                        gather.push_back((uint32_t)(e.first - c * ws.chunk) |
+                                         (e.second < 0 ? 0x80000000u : 0u));
+                }
+                while (gather.size() % 4) gather.push_back((uint32_t)ws.chunk);
+                gather[head + q / 4] |= (uint32_t)((gather.size() - first) / 4) << (8 * (q % 4));
+            }
+        }
+    }
 }
 
 // QSS species of one side of reaction i (the first one) and their molecule count.
@@ -372,6 +474,7 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
                     eff.push_back(f);
                 }
             }
+            a.eff_cnt = q;
             a.ext_cnt = (int32_t)eff.size() - a.ext_off;
             if (r.type == KX_RXN_LINDEMANN || r.type == KX_RXN_TROE || r.type == KX_RXN_SRI) {
                 a.lnA0 = std::log(d->A0[i]);
@@ -441,9 +544,6 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
     std::vector<int32_t> gpos(nchunks), gneg(nchunks), goff(nchunks);
     std::vector<uint32_t> gent;  // 8 per (group, lane)
     size_t ngroups = 0;
-    std::vector<int32_t> mgrp(nchunks), moff(nchunks);
-    std::vector<uint32_t> ment;  // signed lists of the rates kernel, 8 per (group, lane)
-    size_t nmgroups = 0;
     for (int c = 0; c < nchunks; ++c) {
         std::vector<std::vector<uint32_t>> pos(gw), neg(gw);
         for (int s = c * chunk; s < std::min(nr, (c + 1) * chunk); ++s) {
@@ -471,28 +571,6 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
         gpos[c] = (int32_t)((lp + 7) / 8);
         gneg[c] = (int32_t)((ln + 7) / 8);
         goff[c] = (int32_t)ngroups;
-        // the rates kernel's lists: one list per species with the sign of each
-        // entry in bit 31 (+q entries first), padded to whole groups of eight
-        {
-            size_t lm = 0;
-            for (int k = 0; k < gw; ++k) lm = std::max(lm, pos[k].size() + neg[k].size());
-            mgrp[c] = (int32_t)((lm + 7) / 8);
-            moff[c] = (int32_t)nmgroups;
-            const uint32_t zpad = (uint32_t)(16 * chunk);
-            for (int g = 0; g < mgrp[c]; ++g)
-                for (int k = 0; k < gw; ++k)
-                    for (int u = 0; u < 8; ++u) {
-                        const size_t e = (size_t)g * 8 + u;
-                        const size_t np_ = pos[k].size();
-                        uint32_t v = zpad;
-                        if (e < np_)
-                            v = pos[k][e];
-                        else if (e < np_ + neg[k].size())
-                            v = neg[k][e - np_] | 0x80000000u;
-                        ment.push_back(v);
-                    }
-            nmgroups += mgrp[c];
-        }
         const uint32_t pad = (uint32_t)(16 * chunk);  // the zero slot
         for (int side = 0; side < 2; ++side) {
             const auto &lists = side ? neg : pos;
@@ -507,7 +585,6 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
         }
     }
     if (gent.empty()) gent.resize(8, 0);
-    if (ment.empty()) ment.resize(8, 0);
 
     // ---- QSS species: index per species, per reaction (kernel order) the QSS
     // species of either side, and per QSS species the reactions of its balance
@@ -569,6 +646,95 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
         g[14 * kWave] = spv[k].t_mid;
         g[15 * kWave] = spv[k].inv_W;
     }
+
+    // ---- tables of the one-lane-per-point kernels (kx_wide.h)
+    const WideShape ws = wide_shape(ns, nr);
+    const long double kLog2e = 1.44269504088896340735992468100189214L;
+    std::vector<DevWide> wrx, wrx32;
+    std::vector<DevAux> waux;
+    std::vector<DevPlog> wplog;
+    std::vector<double> wsp;
+    WideShape wsh[3];
+    std::vector<int32_t> wmap[3];
+    std::vector<uint32_t> wstart[3], wgat[3];
+    int nplog = 0;
+    if (ws.nw > 0) {
+        for (int s = 0; s < nr; ++s) {
+            const DevRxn &r = rx[s];
+            const int i = perm[s];
+            DevWide v;
+            const uint32_t dummy = (uint32_t)ns;
+            uint32_t o[2 * kMaxSide];
+            for (int q = 0; q < kMaxSide; ++q) {
+                o[q] = r.roff[q] / 16u;
+                o[kMaxSide + q] = r.poff[q] / 16u;
+            }
+            // an irreversible reaction's products: the species with b = 0
+            if (!(r.flags & kFlagReversible)) o[kMaxSide] = (uint32_t)ns + 1;
+            v.r01 = o[0] | o[1] << 16;
+            v.p01 = o[3] | o[4] << 16;
+            v.rp2 = o[2] | o[5] << 16;
+            const bool kconst = r.flags & kFlagKfConst;
+            v.lA = r.lnA;
+            v.beta = kconst ? r.A : r.beta;
+            v.ER = r.ER;
+            const bool fall = r.type == KX_RXN_LINDEMANN || r.type == KX_RXN_TROE ||
+                              r.type == KX_RXN_SRI;
+            v.meta = (r.flags & kFlagKfConst ? kWideConst : 0u) |
+                     (r.type == KX_RXN_PLOG ? kWidePlog : 0u) |
+                     (o[2] != dummy || o[5] != dummy ? kWideThird : 0u) |
+                     (r.flags & kFlagOrders ? kWideOrders : 0u) |
+                     (fall || r.type == KX_RXN_THREEBODY ? kWideThirdBody : 0u) |
+                     (fall ? kWideFalloff : 0u) | (r.type == KX_RXN_TROE ? kWideTroe : 0u) |
+                     (r.type == KX_RXN_SRI ? kWideSri : 0u) |
+                     (r.flags & kFlagChemAct ? kWideChemAct : 0u) |
+                     ((r.aux == 0xFFFF ? 0u : (uint32_t)r.aux) << 16);
+            nplog += r.type == KX_RXN_PLOG;
+            wrx32.push_back(v);
+            if (r.type != KX_RXN_PLOG) {
+                v.lA = (double)std::log2((long double)d->A[i]);
+                v.ER = (double)((long double)d->Ea[i] / kRcal * kLog2e);
+            }
+            wrx.push_back(v);
+        }
+        auto l2 = [&](double x) { return (double)((long double)x * kLog2e); };
+        waux = aux;
+        for (int s = 0; s < nr; ++s) {
+            if (rx[s].aux == 0xFFFF) continue;
+            DevAux &a = waux[rx[s].aux];
+            const int i = perm[s], t = rx[s].type;
+            if (t == KX_RXN_LINDEMANN || t == KX_RXN_TROE || t == KX_RXN_SRI) {
+                a.lnA0 = (double)std::log2((long double)d->A0[i]);
+                a.ER0 = (double)((long double)d->Ea0[i] / kRcal * kLog2e);
+                for (int q = 1; q < 4; ++q) a.fp[q] = l2(a.fp[q]);
+            }
+        }
+        wplog = plog;
+        for (DevPlog &e : wplog) {
+            e.lnA = l2(e.lnA);
+            e.ER = l2(e.ER);
+        }
+        wsp.assign((size_t)16 * ns, 0.0);
+        for (int k = 0; k < ns; ++k) {
+            for (int r = 0; r < 2; ++r) {
+                const double *g = r ? spv[k].g_hi : spv[k].g_lo;
+                double *o = &wsp[(size_t)16 * k + 7 * r];
+                o[0] = g[0];  // c0 (1 - ln T) = c0 - c0 ln 2 log2 T
+                for (int e = 1; e < 6; ++e) o[e] = -l2(g[e]);
+                o[6] = -(double)(((long double)g[0] + g[6]) * kLog2e);
+            }
+            wsp[(size_t)16 * k + 14] = spv[k].t_mid;
+            wsp[(size_t)16 * k + 15] = d->qss && d->qss[k] ? 0.0 : spv[k].inv_W;
+        }
+        wsh[0] = wsh[1] = ws;
+        wsh[1].nw = 16;
+        wsh[2] = wide_shape_alone(ns, nr);
+        for (int v = 0; v < 3; ++v) wide_gather(d, perm, wsh[v], wmap[v], wstart[v], wgat[v]);
+    }
+    if (wrx.empty()) wrx.resize(1), wrx32.resize(1);
+    if (waux.empty()) waux.resize(1);
+    if (wplog.empty()) wplog.resize(1);
+    if (wsp.empty()) wsp.resize(16);
 
     // ---- transport tables
     const int nkb = (ns + kKB - 1) / kKB;
@@ -633,7 +799,14 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
     const size_t o_gsoa = add_vec(b, gsoa);
     const size_t o_goff = add_vec(b, goff);
     const size_t o_gent = add_vec(b, gent);
-    const size_t o_mgrp = add_vec(b, mgrp), o_moff = add_vec(b, moff), o_ment = add_vec(b, ment);
+    const size_t o_wrx = add_vec(b, wrx), o_wrx32 = add_vec(b, wrx32), o_waux = add_vec(b, waux);
+    const size_t o_wplog = add_vec(b, wplog), o_wsp = add_vec(b, wsp);
+    size_t o_wmap[3], o_wstart[3], o_wgat[3];
+    for (int v = 0; v < 3; ++v) {
+        o_wmap[v] = add_vec(b, wmap[v]);
+        o_wstart[v] = add_vec(b, wstart[v]);
+        o_wgat[v] = add_vec(b, wgat[v]);
+    }
     const size_t o_W = add_vec(b, W), o_visc = add_vec(b, visc), o_cond = add_vec(b, cond);
     const size_t o_wil = add_vec(b, wilke), o_df = add_vec(b, dfit), o_dd = add_vec(b, ddiag);
     const size_t o_wq = add_vec(b, wq), o_wq32 = add_vec(b, to32(wq));
@@ -698,9 +871,20 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
     v.gneg = (const int32_t *)at(o_gneg);
     v.goff = (const int32_t *)at(o_goff);
     v.gent = (const uint4 *)at(o_gent);
-    v.gmgrp = (const int32_t *)at(o_mgrp);
-    v.gmoff = (const int32_t *)at(o_moff);
-    v.gment = (const uint4 *)at(o_ment);
+    v.wnw = ws.nw;
+    v.nplog = nplog;
+    v.wrx = (const DevWide *)at(o_wrx);
+    v.wrx32 = (const DevWide *)at(o_wrx32);
+    v.waux = (const DevAux *)at(o_waux);
+    v.wplog = (const DevPlog *)at(o_wplog);
+    v.wsp = (const double *)at(o_wsp);
+    for (int q = 0; q < 3; ++q) {
+        v.wmaps[q].chunk = wsh[q].chunk;
+        v.wmaps[q].nchunks = wsh[q].nchunks;
+        v.wmaps[q].species = (const int32_t *)at(o_wmap[q]);
+        v.wmaps[q].start = (const uint32_t *)at(o_wstart[q]);
+        v.wmaps[q].gather = (const uint4 *)at(o_wgat[q]);
+    }
     v.W = (const double *)at(o_W);
     v.visc = (const double *)at(o_visc);
     v.cond = (const double *)at(o_cond);
@@ -741,7 +925,10 @@ bool rebase_tables(const kx_mech *m, const void *base, MechDev *out)
     KX_REBASE(rxn); KX_REBASE(aux); KX_REBASE(eff); KX_REBASE(plog); KX_REBASE(sp);
     KX_REBASE(gsoa);
     KX_REBASE(gpos); KX_REBASE(gneg); KX_REBASE(goff); KX_REBASE(gent);
-    KX_REBASE(gmgrp); KX_REBASE(gmoff); KX_REBASE(gment);
+    KX_REBASE(wrx); KX_REBASE(wrx32); KX_REBASE(waux); KX_REBASE(wplog); KX_REBASE(wsp);
+    for (int q = 0; q < 3; ++q) {
+        KX_REBASE(wmaps[q].species); KX_REBASE(wmaps[q].start); KX_REBASE(wmaps[q].gather);
+    }
     KX_REBASE(W); KX_REBASE(visc); KX_REBASE(cond); KX_REBASE(wq); KX_REBASE(wilke);
     KX_REBASE(dfit); KX_REBASE(ddiag);
     KX_REBASE(visc32); KX_REBASE(cond32); KX_REBASE(wq32); KX_REBASE(wilke32);

@@ -1,46 +1,44 @@
 // kx_rates.hip -- species net production rates on gfx950.
 //
-// Work decomposition.  A workgroup is one wave that owns a tile of `tp`
-// consecutive points (8; 2 above 128 species): the tile's T and p are read
-// first, the tile of Y is staged through LDS with coalesced row loads, and the
-// same LDS tile later receives wdot and is written back with coalesced row
-// stores.  The wave takes the tile's points four at a time (two above 128
-// species) and runs three phases per step, with lanes spread over species,
-// then (reaction, point) pairs, then species again:
+// Two kernels.  Mechanisms of up to kWideMaxSpecies species: one lane per point,
+// every species and reaction wave-uniform (kx_wide.h, rates_wide_tile below).
+// Larger ones, whose species rows for 64 points exceed the LDS: lanes over
+// species and (reaction, point) pairs (rates_tile).
 //
-//  1. species (lane = k, every point of the step): C_k, the Gibbs energy
-//     g_k = G_k/RT of eq:Ck (range by T_mid; both ranges' coefficients read
-//     once per step from a by-field table), a_k = (p_atm/RT) exp(-g_k) and
-//     b_k = C_k / a_k into LDS as one 16-byte pair per species and point.
-//     With these, prod_k C_k^nu' = A' B' and prod_k C_k^nu'' / K_c = A' B''
+// Both evaluate, per point,
+//  1. species: C_k, the Gibbs energy g_k = G_k/RT of eq:Ck (range by T_mid),
+//     a_k = (p_atm/RT) exp(-g_k) and b_k = C_k / a_k into LDS.  With these,
+//     prod_k C_k^nu' = A' B' and prod_k C_k^nu'' / K_c = A' B''
 //     (A' = prod_reac a^nu', B' = prod_reac b^nu', B'' = prod_prod b^nu''), since
 //     K_c = prod_k a_k^(nu''-nu') by eq:K_p and K_c = K_p (p_atm/RT)^(sum nu).
 //     So K_c needs one exponential per species instead of one per reaction and
 //     the rate of progress needs no division:
 //         R_i = c_i k_f A' (B' - B'')                   (eq:r_i, eq:c_i)
-//     and B' - B'' is the near-equilibrium difference, formed in FP64.
-//  2. reactions (lanes 2r, 2r+1 = reaction r, each at half of the step's
-//     points): k_f (eq:arrhenius, with the beta = E_R = 0 shortcut of eq:k_f),
-//     [X]_i, the Lindemann / Troe factor (eq:blend) and R_i into LDS, one
-//     chunk of reactions at a time; the 48-byte record is read and decoded
-//     once per two rates of progress, a third-body reaction's efficiency data
-//     loaded with it.  Reactions are sorted heaviest type first, so the
-//     falloff code runs for 32 reactions per 64-lane iteration.  Each reaction
-//     side is three molecule slots (unused ones hit a dummy species with
-//     a = b = 1), so the products A', B', B'' are branch-free.
-//  3. species (lane = k, every point of the step): wdot_k = sum_i nu_ki R_i
-//     gathered from species-major lists of R slots (a net |nu| of 2 or 3 is
-//     listed that many times); one 16-byte LDS read returns R_i at two points.
-//     With four points per step a species has one list, each entry's sign in
-//     its bit 31; with two, separate +R and -R lists.  The summation order is
-//     fixed, so results are deterministic; the mixed path adds each two list
-//     groups' sum with one Neumaier-compensated step.
+//     and B' - B'' is the near-equilibrium difference, formed in FP64;
+//  2. reactions: k_f (eq:arrhenius, with the beta = E_R = 0 shortcut of eq:k_f),
+//     [X]_i, the Lindemann / Troe factor (eq:blend) and R_i into LDS, one chunk
+//     of reactions at a time, heaviest type first;
+//  3. species: wdot_k = sum_i nu_ki R_i gathered from species-major lists of R
+//     slots (a net |nu| of 2 or 3 is listed that many times).  The summation
+//     order is fixed, so results are deterministic; the mixed path adds its
+//     groups' sums with Neumaier-compensated steps.
+//
+// What bounds the one-lane-per-point kernel (53 species, FP64, 2^20 points;
+// measured 1.02 ms, 1.57 ms by the lanes-over-reactions form it replaced; 9
+// species 0.083 against 0.64 ms, 100 species at 2^18 points 0.77 against 0.94):
+// it issues about 400 vector and as many scalar instructions per point (657
+// vector ones before: the record decoding, the padded gather lists and the idle
+// lanes are gone), 65 % of the time the vector units could take at best; the rest
+// is the latency of the scalar loads that miss the 16 KB scalar cache (the
+// tables stream through it once per tile: their size and the number of waves
+// decide, see DevWide and wide_shape) and the chunk barriers.
 #include <float.h>
 
 #include <type_traits>
 
 #include "kx_internal.h"
 #include "kx_math.h"
+#include "kx_wide.h"
 
 namespace kx {
 namespace {
@@ -51,16 +49,6 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// exp(x) for the mixed path: the argument stays in FP64, is reduced by n ln 2
-// in FP64 and only exp(r), |r| <= ln2/2, is evaluated in FP32.
-__device__ __forceinline__ double exp_mixed(double x)
-{
-    const double nd = rint(x * 1.4426950408889634);
-    const double r = fma(-nd, 6.93147180559945286e-01, x);
-    const float er = __expf((float)r);
-    return ldexp((double)er, (int)nd);
 }
 
 // The falloff data of a reaction: k_0's Arrhenius parameters and the blend
@@ -139,14 +127,6 @@ __device__ __forceinline__ double plog_exponent(const DevPlog *pl, int cnt, doub
     const DevPlog &b = pl[j + 1];
     const double x2 = fma(b.beta, lnT, fma(-b.ER, invT, b.lnA));
     return fma(x2 - x1, (lnp - a.lnp) * a.inv_dlnp, x1);
-}
-
-// log10 of a positive double over its whole range, in FP32 arithmetic.
-__device__ __forceinline__ float log10_wide(double v)
-{
-    int ex;
-    const double mant = frexp(fmax(v, DBL_MIN), &ex);
-    return (__log2f((float)mant) + (float)ex) * 0.30102999566398120f;
 }
 
 // Per-point factors of one species in LDS: {a_k, b_k}, 16 bytes, aligned so
@@ -425,22 +405,9 @@ __device__ __forceinline__ void second_of_pair(double (&acc)[PS], double (&cmp)[
     }
 }
 
-// Points per workgroup tile: 8 (64-byte row segments of Y and wdot; tiles that
-// share a 128-byte line run on the same XCD, see xcd_tile); 2 for mechanisms
-// of more than 128 species, whose Y tile would otherwise crowd the LDS.
-__host__ __device__ constexpr int rates_tile_points_for(int spl) { return spl == 4 ? 2 : 8; }
-
-// Points per step: four for mechanisms of up to 128 species (each lane of the
-// reaction phase evaluates its reaction at two points, so a reaction record is
-// read and decoded once per two rates of progress), two above (the per-point
-// LDS arrays of a 4-point step would crowd the LDS).
-__host__ __device__ constexpr int rates_step_points_for(int spl) { return spl == 4 ? 2 : 4; }
-
-// Byte distance between the two halves of the rate-of-progress array of a
-// 4-point step: slot s of the chunk holds R at points 0 and 1 at 16 s and at
-// points 2 and 3 at kSqHalf + 16 s, so one gather offset addresses both halves
-// (the second through the LDS instruction's immediate offset).
-constexpr int kSqHalf = 16 * (kChunkMax + 1);
+// Points per tile and per step of the lanes-over-reactions kernel.
+__host__ __device__ constexpr int rates_tile_points_for(int) { return 2; }
+__host__ __device__ constexpr int rates_step_points_for(int) { return 2; }
 
 // Per-point constants of a tile, computed once per point (lane = point).
 struct PointConst {
@@ -490,74 +457,6 @@ __device__ __forceinline__ unsigned lds_base()
 // for each read in turn), and two groups are handled per trip with
 // alternating offset registers (the next group's offsets in flight).
 //
-// gather_signed: one list per species with the sign of each entry in bit 31,
-// turned into the factor +-1 of an exact FMA (used with four points per step,
-// where the +q and -q lists padded separately cost a third more reads).
-template <bool MIXED, int SPL, bool DIRECT, int PS>
-__device__ __forceinline__ void gather_signed(const MechDev &m, int c, int gw, int lane,
-                                              const char *qb, double (&acc)[SPL][PS],
-                                              double (&cmp)[SPL][PS])
-{
-    const int ngrp = m.gmgrp[c];
-    const uint4 *ge = m.gment + ((size_t)m.gmoff[c] * gw + lane) * 2;
-#pragma unroll
-    for (int s = 0; s < SPL; ++s) {
-        const uint4 *g = ge + 2 * kWave * s;
-        auto group = [&](const uint4 &v0, const uint4 &v1, double (&gs)[PS]) {
-            const unsigned raw[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
-#pragma unroll
-            for (int h = 0; h < PS / 2; ++h) {
-                double2 q2[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const unsigned off = raw[u] & 0x7fffffffu;
-                    q2[u] = DIRECT ? lds_read16(off + h * kSqHalf)
-                                   : *reinterpret_cast<const double2 *>(qb + off + h * kSqHalf);
-                }
-                __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);  // DS reads
-                __builtin_amdgcn_sched_group_barrier(0x002, 24, 0);  // VALU
-                auto sgn = [&](int u) {
-                    return __hiloint2double((int)((raw[u] & 0x80000000u) | 0x3ff00000u), 0);
-                };
-                double g0 = q2[0].x * sgn(0), g1 = q2[0].y * sgn(0);
-#pragma unroll
-                for (int u = 1; u < 8; ++u) {
-                    const double sg = sgn(u);
-                    g0 = fma(q2[u].x, sg, g0);
-                    g1 = fma(q2[u].y, sg, g1);
-                }
-                gs[2 * h] = g0;
-                gs[2 * h + 1] = g1;
-            }
-        };
-        uint4 a0 = make_uint4(0, 0, 0, 0), a1 = a0, b0 = a0, b1 = a0;
-        if (ngrp > 0) {
-            a0 = g[0];
-            a1 = g[1];
-        }
-        int it = 0;
-        for (; it + 1 < ngrp; it += 2) {
-            b0 = g[(size_t)(it + 1) * 2 * gw];
-            b1 = g[(size_t)(it + 1) * 2 * gw + 1];
-            double ga[PS], gb[PS];
-            group(a0, a1, ga);
-            first_of_pair<MIXED, PS>(acc[s], ga);
-            if (it + 2 < ngrp) {
-                a0 = g[(size_t)(it + 2) * 2 * gw];
-                a1 = g[(size_t)(it + 2) * 2 * gw + 1];
-            }
-            group(b0, b1, gb);
-            second_of_pair<MIXED, PS>(acc[s], cmp[s], ga, gb);
-        }
-        if (it < ngrp) {
-            double ga[PS];
-            group(a0, a1, ga);
-#pragma unroll
-            for (int j = 0; j < PS; ++j) accumulate<MIXED>(acc[s][j], cmp[s][j], ga[j]);
-        }
-    }
-}
-
 // gather_split: a +q list and a -q list per species, each padded to whole
 // groups (the group's sum is negated for the -q groups); two points per step.
 template <bool MIXED, int SPL, bool DIRECT, int PS>
@@ -639,7 +538,7 @@ __device__ __forceinline__ void rates_tile(int lane, const MechDev &m, int64_t l
     const int ns = m.ns;
     const int ys = TP + 1;
     double *sq = lds;
-    double *pairs = sq + (PS == 4 ? 2 * kSqHalf / 8 : 2 * (m.chunk + 1));
+    double *pairs = sq + (2 * (m.chunk + 1));
     PointConst *pc = reinterpret_cast<PointConst *>(pairs + 2 * PS * (ns + 1));
     double *Yt = reinterpret_cast<double *>(pc + TP);
     const char *qb = reinterpret_cast<const char *>(sq);
@@ -716,7 +615,6 @@ __device__ __forceinline__ void rates_tile(int lane, const MechDev &m, int64_t l
     }
     if (lane < 2) {
         sq[2 * m.chunk + lane] = 0.0;
-        if (PS == 4) sq[kSqHalf / 8 + 2 * m.chunk + lane] = 0.0;
     }
 
     const int jl = lane & 1;   // point of this lane in phase 2 (and jl + 2)
@@ -804,13 +702,9 @@ __device__ __forceinline__ void rates_tile(int lane, const MechDev &m, int64_t l
                 double R[NPT];
                 rates_of_progress<MIXED, NPT>(m, cur, pbl, qv, R);
                 sq[2 * r + jl] = R[0];
-                if (PS == 4) sq[kSqHalf / 8 + 2 * r + jl] = R[NPT - 1];
             }
             wave_sync();
-            if (PS == 4)
-                gather_signed<MIXED, SPL, DIRECT, PS>(m, c, gw, lane, qb, acc, cmp);
-            else
-                gather_split<MIXED, SPL, DIRECT, PS>(m, c, gw, lane, qb, acc, cmp);
+            gather_split<MIXED, SPL, DIRECT, PS>(m, c, gw, lane, qb, acc, cmp);
             wave_sync();
         }
         // the rates of progress were stored as points (0, 1) and (2, 3); the
@@ -927,17 +821,186 @@ __global__ __launch_bounds__(kWave, SPL == 1 ? 3 : 2) void rates_items_kernel(
     rates_tile<MIXED, SPL, DIRECT>(threadIdx.x, m, it.n, i0, np, tp, it.T, it.p, it.Y, it.wdot);
 }
 
+// ---------------------------------------------------------------------------
+// One lane per point (mechanisms of up to kWideMaxSpecies species, see
+// kx_wide.h): one tile of 64 points by NW waves.  i0: first point; points past
+// npts repeat the last one and are not stored.
+template <bool MIXED, int NW, bool CQ>
+__device__ __forceinline__ void rates_wide_tile(const MechDev &m, int64_t ld, int64_t i0, int npts,
+                                                const double *__restrict__ T,
+                                                const double *__restrict__ P,
+                                                const double *__restrict__ Y,
+                                                const double *__restrict__ cq,
+                                                double *__restrict__ wdot)
+{
+#pragma clang fp contract(off)
+    extern __shared__ double lds[];
+    constexpr int NS = wide_species(NW);
+    const int lane = threadIdx.x & (kWave - 1);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const WideMap &wm = m.wmaps[NW == 16 ? (MIXED ? 1 : 2) : 0];
+    const int nr = m.nr, chunk = wm.chunk;
+    const int64_t i = i0 + min(lane, npts - 1);
+    double *sq = lds + 2 * (m.ns + 2) * kRow;  // rate rows
+    const Exp2 ex;
+    int ks[NS];  // species of this wave
+#pragma unroll
+    for (int s = 0; s < NS; ++s) ks[s] = const_table(wm.species)[8 * w + s];
+    const WidePoint q =
+        species_rows<MIXED, NW, CQ>(ex, m, ks, w, lane, ld, i, T, P, Y, cq, lds, sq);
+    if (w == 0) sq[chunk * kRow + lane] = 0.0;
+
+    KX_CONST DevWide *rx = const_table(MIXED ? m.wrx32 : m.wrx);
+    KX_CONST uint32_t *g =
+        (KX_CONST uint32_t *)(const_table(wm.gather) + const_table(wm.start)[w]);
+    const unsigned lane8 = 8u * (unsigned)lane;
+    double acc[NS], cmp[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) acc[s] = cmp[s] = 0.0;
+    for (int c = 0; c < wm.nchunks; ++c) {
+        const int base = c * chunk, cnt = min(chunk, nr - base);
+        const uint32_t h0 = g[0], h1 = g[1];  // groups of each species
+        for (int r = w; r < cnt; r += NW) {
+            const WideTerms t = reaction_wide<MIXED>(ex, m, rx + base + r, lds, lane8, q);
+            sq[r * kRow + lane] = t.ckf * t.A * (t.Bf - t.Br);
+        }
+        __syncthreads();
+        g += 4;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+#pragma clang loop unroll(disable)
+            for (int n = ((s < 4 ? h0 : h1) >> 8 * (s & 3)) & 255u; n > 0; --n, g += 4) {
+                double v[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = row_val(sq, g[e], lane8);
+                auto nu = [&](int e) { return (int)g[e] < 0 ? -1.0 : 1.0; };
+                if (MIXED) {
+                    double t = v[0] * nu(0);
+#pragma unroll
+                    for (int e = 1; e < 4; ++e) t = fma(v[e], nu(e), t);
+                    accumulate<true>(acc[s], cmp[s], t);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[s] = fma(v[e], nu(e), acc[s]);
+                }
+            }
+        }
+        if (c + 1 < wm.nchunks) __syncthreads();
+    }
+    if (lane < npts) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+            if (ks[s] >= 0) wdot[(int64_t)ks[s] * ld + i] = MIXED ? acc[s] + cmp[s] : acc[s];
+    }
+}
+
+template <bool MIXED, int NW>
+__global__ __launch_bounds__(NW *kWave, wide_waves(NW)) void rates_wide_kernel(
+    MechDev m, int64_t n, const double *__restrict__ T, const double *__restrict__ P,
+    const double *__restrict__ Y, double *__restrict__ wdot)
+{
+    const int64_t i0 = (int64_t)blockIdx.x * kRow;
+    rates_wide_tile<MIXED, NW, false>(m, n, i0, (int)min((int64_t)kRow, n - i0), T, P, Y, nullptr,
+                                      wdot);
+}
+
+// Batched requests, one tile per workgroup.
+template <bool MIXED, int NW>
+__global__ __launch_bounds__(NW *kWave, wide_waves(NW)) void rates_wide_items_kernel(
+    MechDev m, const WorkList *__restrict__ wl)
+{
+    const int t = (int)blockIdx.x;
+    if (t >= wl->ntiles[0]) return;
+    const int r = work_item_ballot(wl, 0, t);
+    const WorkItem it = wl->items[r];
+    const int64_t i0 = (int64_t)(t - wl->start[0][r]) * kRow;
+    rates_wide_tile<MIXED, NW, false>(m, it.n, i0, (int)min((int64_t)kRow, it.n - i0), it.T, it.p,
+                                      it.Y, nullptr, it.wdot);
+}
+
+// Batched requests, persistent workgroups taking one tile at a time from one
+// counter (a tile is 64 points by NW waves, so its ticket costs little).
+template <bool MIXED, int NW>
+__global__ __launch_bounds__(NW *kWave, wide_waves(NW)) void rates_wide_batch_kernel(
+    MechDev m, const WorkList *__restrict__ wl, int *__restrict__ counter)
+{
+    __shared__ int tile;
+    const int ntiles = wl->ntiles[0];
+    int r = 0;  // item of the previous tile
+    for (;;) {
+        __syncthreads();  // the previous tile's LDS reads are done
+        if (threadIdx.x == 0) tile = atomicAdd(counter, 1);
+        __syncthreads();
+        const int t = __builtin_amdgcn_readfirstlane(tile);
+        if (t >= ntiles) break;
+        r = work_item_of(wl, 0, t, r);
+        const WorkItem it = wl->items[r];
+        const int64_t i0 = (int64_t)(t - wl->start[0][r]) * kRow;
+        rates_wide_tile<MIXED, NW, false>(m, it.n, i0, (int)min((int64_t)kRow, it.n - i0), it.T,
+                                          it.p, it.Y, nullptr, it.wdot);
+    }
+}
+
+size_t wide_lds_bytes(const MechDev &m, int precision, int nw)
+{
+    const WideMap &wm = m.wmaps[nw == 16 ? (precision == KX_MIXED ? 1 : 2) : 0];
+    return sizeof(double) * kRow * (2 * (size_t)(m.ns + 2) + (size_t)wm.chunk + 1);
+}
+
+// Waves per workgroup for a launch of `tiles` tiles: all 16 a workgroup can have
+// when every tile gets a CU of its own (the tile's latency is then all that
+// counts), else the number the mechanism's LDS share was laid out for.  A point's
+// results do not depend on it.
+int wide_launch_waves(const MechDev &m, int64_t tiles) { return tiles <= 256 ? 16 : m.wnw; }
+
+// The instance of a wide kernel for a precision and number of waves.  FORM 0:
+// direct launch, 1: work-stealing batch, 2: one tile per workgroup.
+template <int FORM, bool MIXED, int NW> const void *wide_instance()
+{
+    if (FORM == 1) return (const void *)rates_wide_batch_kernel<MIXED, NW>;
+    if (FORM == 2) return (const void *)rates_wide_items_kernel<MIXED, NW>;
+    return (const void *)rates_wide_kernel<MIXED, NW>;
+}
+
+template <int FORM> const void *wide_kernel(int precision, int nw)
+{
+    auto pick = [&](auto mixed) {
+        constexpr bool M = decltype(mixed)::value;
+        return nw == 4    ? wide_instance<FORM, M, 4>()
+               : nw == 8  ? wide_instance<FORM, M, 8>()
+               : nw == 12 ? wide_instance<FORM, M, 12>()
+                          : wide_instance<FORM, M, 16>();
+    };
+    return precision == KX_MIXED ? pick(std::true_type{}) : pick(std::false_type{});
+}
+
+template <int FORM>
+kx_status launch_wide(const MechDev &m, int precision, int nw, int64_t grid, void **args,
+                      hipStream_t s, const char *what)
+{
+    const void *kern = wide_kernel<FORM>(precision, nw);
+    const size_t lds = wide_lds_bytes(m, precision, nw);
+    hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute (rates)");
+    e = hipLaunchKernel(kern, dim3((unsigned)grid), dim3(nw * kWave), args, lds, s);
+    if (e != hipSuccess) return hip_fail(e, what);
+    return ok();
+}
+
 size_t rates_lds_bytes(const MechDev &m, int tp)
 {
     const int ps = rates_step_points_for(m.gpass);
-    const size_t sq = ps == 4 ? 2 * (size_t)kSqHalf / 8 : 2 * (size_t)(m.chunk + 1);
+    const size_t sq = 2 * (size_t)(m.chunk + 1);
     return sizeof(double) * (sq + 2 * (size_t)ps * (m.ns + 1) + 8 * (size_t)tp +
                              (size_t)m.ns * (tp + 1));
 }
 
 }  // namespace
 
-int rates_tile_points(const MechDev &m) { return rates_tile_points_for(m.gpass); }
+int rates_tile_points(const MechDev &m)
+{
+    return m.wnw ? kRow : rates_tile_points_for(m.gpass);
+}
 
 namespace {
 template <class K>
@@ -948,9 +1011,6 @@ kx_status set_lds(K kern, size_t lds)
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute (rates)");
     return KX_OK;
 }
-
-// species per lane of the species and gather phases
-int rates_spl(const MechDev &m) { return m.gpass <= 1 ? 1 : (m.gpass <= 2 ? 2 : 4); }
 
 // The instance to launch: the DIRECT one when it has no static LDS.
 template <class K>
@@ -969,17 +1029,21 @@ kx_status launch_rates(const kx_mech *mech, int64_t n, const double *T, const do
 {
     const MechDev &m = mech->dev;
     const int tp = rates_tile_points(m);
+    if (m.wnw) {
+        const int64_t nblk = (n + kRow - 1) / kRow;
+        if (nblk > 0x7fffffff) return fail(KX_EINVAL, "production rates: n too large");
+        void *args[] = {(void *)&m, (void *)&n, (void *)&T, (void *)&p, (void *)&Y, (void *)&wdot};
+        return launch_wide<0>(m, precision, wide_launch_waves(m, nblk), nblk, args, s,
+                              "rates kernel launch");
+    }
     const size_t lds = rates_lds_bytes(m, tp);
     if (lds > 160 * 1024)
         return fail(KX_EUNSUPPORTED, "production rates: mechanism too large for LDS");
     const int64_t nblk = (n + tp - 1) / tp;
     if (nblk > 0x7fffffff) return fail(KX_EINVAL, "production rates: n too large");
-    const int spl = rates_spl(m);
     auto pick = [&](auto mixed) {
         constexpr bool M = decltype(mixed)::value;
-        return spl == 1 ? pick_direct(rates_kernel<M, 1, true>, rates_kernel<M, 1, false>)
-                        : (spl == 2 ? pick_direct(rates_kernel<M, 2, true>, rates_kernel<M, 2, false>)
-                                    : pick_direct(rates_kernel<M, 4, true>, rates_kernel<M, 4, false>));
+        return pick_direct(rates_kernel<M, 4, true>, rates_kernel<M, 4, false>);
     };
     auto kern = precision == KX_MIXED ? pick(std::true_type{}) : pick(std::false_type{});
     kx_status st = set_lds(kern, lds);
@@ -994,15 +1058,9 @@ kx_status launch_rates(const kx_mech *mech, int64_t n, const double *T, const do
 namespace {
 auto pick_batch(const MechDev &m, int precision)
 {
-    const int spl = rates_spl(m);
     auto pick = [&](auto mixed) {
         constexpr bool M = decltype(mixed)::value;
-        return spl == 1
-                   ? pick_direct(rates_batch_kernel<M, 1, true>, rates_batch_kernel<M, 1, false>)
-                   : (spl == 2 ? pick_direct(rates_batch_kernel<M, 2, true>,
-                                             rates_batch_kernel<M, 2, false>)
-                               : pick_direct(rates_batch_kernel<M, 4, true>,
-                                             rates_batch_kernel<M, 4, false>));
+        return pick_direct(rates_batch_kernel<M, 4, true>, rates_batch_kernel<M, 4, false>);
     };
     return precision == KX_MIXED ? pick(std::true_type{}) : pick(std::false_type{});
 }
@@ -1011,15 +1069,9 @@ auto pick_batch(const MechDev &m, int precision)
 namespace {
 auto pick_items(const MechDev &m, int precision)
 {
-    const int spl = rates_spl(m);
     auto pick = [&](auto mixed) {
         constexpr bool M = decltype(mixed)::value;
-        return spl == 1
-                   ? pick_direct(rates_items_kernel<M, 1, true>, rates_items_kernel<M, 1, false>)
-                   : (spl == 2 ? pick_direct(rates_items_kernel<M, 2, true>,
-                                             rates_items_kernel<M, 2, false>)
-                               : pick_direct(rates_items_kernel<M, 4, true>,
-                                             rates_items_kernel<M, 4, false>));
+        return pick_direct(rates_items_kernel<M, 4, true>, rates_items_kernel<M, 4, false>);
     };
     return precision == KX_MIXED ? pick(std::true_type{}) : pick(std::false_type{});
 }
@@ -1030,6 +1082,11 @@ kx_status launch_rates_items(const MechDev &m, const WorkList *wl, int64_t ntile
 {
     if (ntiles <= 0) return ok();
     if (ntiles > 0x7fffffff) return fail(KX_EINVAL, "production rates: too many tiles");
+    if (m.wnw) {
+        void *args[] = {(void *)&m, (void *)&wl};
+        return launch_wide<2>(m, precision, wide_launch_waves(m, ntiles), ntiles, args, s,
+                              "rates items kernel launch");
+    }
     const int tp = rates_tile_points(m);
     const size_t lds = rates_lds_bytes(m, tp);
     if (lds > 160 * 1024)
@@ -1045,6 +1102,13 @@ kx_status launch_rates_items(const MechDev &m, const WorkList *wl, int64_t ntile
 
 kx_status prepare_rates_batch(const MechDev &m, int precision)
 {
+    if (m.wnw) {
+        hipError_t e = hipFuncSetAttribute(wide_kernel<1>(precision, m.wnw),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)wide_lds_bytes(m, precision, m.wnw));
+        if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute (rates)");
+        return KX_OK;
+    }
     const size_t lds = rates_lds_bytes(m, rates_tile_points(m));
     if (lds > 160 * 1024)
         return fail(KX_EUNSUPPORTED, "production rates: mechanism too large for LDS");
@@ -1054,6 +1118,13 @@ kx_status prepare_rates_batch(const MechDev &m, int precision)
 kx_status launch_rates_batch(const MechDev &m, const WorkList *wl, int *counter, int precision,
                              int grid, hipStream_t s)
 {
+    if (m.wnw) {
+        void *args[] = {(void *)&m, (void *)&wl, (void *)&counter};
+        hipError_t e = hipLaunchKernel(wide_kernel<1>(precision, m.wnw), dim3(grid / m.wnw),
+                                       dim3(m.wnw * kWave), args, wide_lds_bytes(m, precision, m.wnw), s);
+        if (e != hipSuccess) return hip_fail(e, "rates batch kernel launch");
+        return ok();
+    }
     const int tp = rates_tile_points(m);
     const size_t lds = rates_lds_bytes(m, tp);
     hipLaunchKernelGGL(pick_batch(m, precision), dim3(grid), dim3(kWave), lds, s, m, wl,
