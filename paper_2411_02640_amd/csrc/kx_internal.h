@@ -22,6 +22,7 @@ constexpr int kMaxFitOrder = 8;
 constexpr int kWave = 64;
 constexpr int kMaxQss = 64;          // QSS species per mechanism (one wave of rows)
 constexpr int kWideMaxSpecies = 128; // one-lane-per-point kernels (species rows in LDS)
+constexpr int kJacBlockSpecies = 128;   // Jacobian in row blocks
 constexpr int kChunkMax = 192;       // reactions per chunk of the gather lists, at most
 
 // Reaction flags.
@@ -182,6 +183,18 @@ struct MechDev {
     // the same chunks (so that the mixed path's compensated groups stay the same);
     // 2: 16 waves, as many rate rows as the LDS holds
     WideMap wmaps[3];
+    // Jacobian in row blocks (kx_jacobian.hip); jrows = 0: not laid out (more than
+    // 128 species, QSS species, or more slot derivatives than the LDS holds)
+    int32_t jnv;               // slot derivatives of all reactions (a zero follows them)
+    int32_t jrows, jnblk;      // rows of a row block, row blocks
+    int32_t jpts;              // points per workgroup (2, 4 or 8)
+    const uint32_t *jval;      // [nr] first slot derivative of a reaction (kernel order)
+    const int32_t *jptr;       // [jnblk + 1] lane blocks of a row block
+    const uint2 *jlist;        // [lane block] {first entry word, entries per lane}
+    const uint2 *jent;         // [word][64] four entries of 16 bits per lane: the slot
+                               // derivative, bit 15 set: subtracted
+    const uint16_t *jtgt;      // [lane block][64] element of the row block (row * ns + column,
+                               // then jrows row constants); 0xFFFF: none
     // transport (FP64)
     const double *W;           // [ns]
     const double *visc;        // [ns][order]

@@ -367,6 +367,128 @@ kx_status validate(const kx_mech_desc *d, std::vector<double> &W)
     return KX_OK;
 }
 
+// Tables of the Jacobian in row blocks: which slot derivatives of which reactions
+// add up to each element.  A reaction's slot derivatives, in this order: its
+// reactant molecules (or the species of explicit orders), its product molecules
+// if reversible, its listed colliders, and the part that is the same for every
+// column.
+struct JacTables {
+    int nv = 0, rows = 0, nblk = 0, pts = 2;
+    std::vector<uint32_t> val;
+    std::vector<int32_t> ptr;
+    std::vector<uint2> list, ent;
+    std::vector<uint16_t> tgt;
+};
+
+void jac_tables(const kx_mech_desc *d, const std::vector<int> &perm, const std::vector<DevRxn> &rx,
+                const std::vector<DevAux> &aux, const std::vector<DevEff> &eff, JacTables &t)
+{
+    const int ns = d->n_species, nr = d->n_reactions;
+    if (ns > kJacBlockSpecies || nr == 0 || d->qss) return;
+    const int dense = ns;  // pseudo column
+    // contributions to (row, column): slot derivative and sign, |nu| times
+    std::vector<std::vector<uint16_t>> el((size_t)ns * (ns + 1));
+    std::vector<std::pair<int, int>> net;
+    for (int s = 0; s < nr; ++s) {
+        const DevRxn &r = rx[s];
+        const int i = perm[s];
+        net.clear();
+        for (int side = 0; side < 2; ++side) {
+            const int32_t *ptr = side ? d->prod_ptr : d->reac_ptr;
+            for (int e = ptr[i]; e < ptr[i + 1]; ++e) {
+                const int k = (side ? d->prod_sp : d->reac_sp)[e];
+                const int v = side ? d->prod_nu[e] : -d->reac_nu[e];
+                bool found = false;
+                for (auto &q : net)
+                    if (q.first == k) q.second += v, found = true;
+                if (!found) net.push_back({k, v});
+            }
+        }
+        t.val.push_back((uint32_t)t.nv);
+        auto add = [&](int column) {
+            if (t.nv >= 0x7FFF) {
+                t.nv = 0x8000;
+                return;
+            }
+            for (auto &q : net)
+                for (int u = 0; u < std::abs(q.second); ++u)
+                    el[(size_t)q.first * (ns + 1) + column].push_back(
+                        (uint16_t)(t.nv | (q.second < 0 ? 0x8000 : 0)));
+            ++t.nv;
+        };
+        const DevAux *ax = r.aux == 0xFFFF ? nullptr : &aux[r.aux];
+        if (r.flags & kFlagOrders) {
+            for (int e = 0; e < kMaxOrd; ++e)
+                if (ax->oval[e] != 0.0) add(ax->ooff[e] / 16);
+        } else {
+            for (int q = 0; q < kMaxSide; ++q)
+                if (r.roff[q] != 16 * ns) add(r.roff[q] / 16);
+        }
+        if (r.flags & kFlagReversible)
+            for (int q = 0; q < kMaxSide; ++q)
+                if (r.poff[q] != 16 * ns) add(r.poff[q] / 16);
+        if (r.type != KX_RXN_ELEMENTARY && r.type != KX_RXN_PLOG) {
+            for (int e = 0; e < ax->eff_cnt; ++e) add(ax->eoff[e] / 16);
+            for (int e = 0; e < ax->ext_cnt; ++e) add(eff[ax->ext_off + e].sp);
+        }
+        if (r.type != KX_RXN_ELEMENTARY) add(dense);
+        if (t.nv > 0x7FFF) break;
+    }
+    // points per workgroup and rows per block: the most points with which four
+    // workgroups share a CU's LDS, each with at least eight rows; two points and
+    // fewer workgroups if there is no such number
+    int rows = 0;
+    const int need = std::min(8, ns);
+    auto fit = [&](int pts, int groups) {
+        const size_t share = 160 * 1024 / groups;
+        const size_t fixed = 8 * (size_t)pts * ((size_t)t.nv + 1 + 2 * (ns + 1) + 4) + 16;
+        return share > fixed ? (int)std::min<size_t>((share - fixed) / (8 * pts * (ns + 1)), ns) : 0;
+    };
+    for (t.pts = 8; t.pts > 2 && (rows = fit(t.pts, 4)) < need;) t.pts /= 2;
+    if (t.pts == 2)
+        for (int groups = 4; groups >= 1 && (rows = fit(2, groups)) < need;) --groups;
+    if (t.nv > 0x7FFF || rows == 0) {
+        t = JacTables();
+        return;
+    }
+    t.nblk = (ns + rows - 1) / rows;
+    t.rows = (ns + t.nblk - 1) / t.nblk;
+    t.ptr.push_back(0);
+    std::vector<int> order;
+    for (int b = 0; b < t.nblk; ++b) {
+        // the elements of the block, longest list first, 64 to a lane block
+        const int r0 = b * t.rows, r1 = std::min(ns, r0 + t.rows);
+        order.clear();
+        for (int k = r0; k < r1; ++k)
+            for (int j = 0; j <= ns; ++j) order.push_back(k * (ns + 1) + j);
+        std::stable_sort(order.begin(), order.end(),
+                         [&](int a, int c) { return el[a].size() > el[c].size(); });
+        for (size_t o = 0; o < order.size(); o += 64) {
+            const size_t len = el[order[o]].size(), words = (len + 3) / 4, first = t.ent.size();
+            t.list.push_back(uint2{(uint32_t)(first / 64), (uint32_t)len});
+            t.ent.resize(first + 64 * words);
+            for (size_t l = 0; l < 64; ++l) {
+                const bool in = o + l < order.size();
+                const int k = in ? order[o + l] / (ns + 1) : 0, j = in ? order[o + l] % (ns + 1) : 0;
+                t.tgt.push_back(!in ? 0xFFFF
+                                    : (uint16_t)(j < ns ? (k - r0) * ns + j : t.rows * ns + k - r0));
+                for (size_t w = 0; w < words; ++w) {
+                    uint16_t e4[4];
+                    for (int u = 0; u < 4; ++u) {
+                        const size_t e = 4 * w + u;
+                        e4[u] = in && e < el[order[o + l]].size() ? el[order[o + l]][e]
+                                                                  : (uint16_t)t.nv;
+                    }
+                    t.ent[first + 64 * w + l] = uint2{(uint32_t)e4[0] | (uint32_t)e4[1] << 16,
+                                                      (uint32_t)e4[2] | (uint32_t)e4[3] << 16};
+                }
+            }
+        }
+        t.ptr.push_back((int32_t)t.list.size());
+    }
+    t.ent.resize(t.ent.size() + 64);  // an empty list's first word is read, not used
+}
+
 }  // namespace
 
 namespace {
@@ -736,6 +858,9 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
     if (wplog.empty()) wplog.resize(1);
     if (wsp.empty()) wsp.resize(16);
 
+    JacTables jt;
+    jac_tables(d, perm, rx, aux, eff, jt);
+
     // ---- transport tables
     const int nkb = (ns + kKB - 1) / kKB;
     std::vector<double> visc((size_t)ns * order), cond((size_t)ns * order);
@@ -801,6 +926,9 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
     const size_t o_gent = add_vec(b, gent);
     const size_t o_wrx = add_vec(b, wrx), o_wrx32 = add_vec(b, wrx32), o_waux = add_vec(b, waux);
     const size_t o_wplog = add_vec(b, wplog), o_wsp = add_vec(b, wsp);
+    const size_t o_jval = add_vec(b, jt.val), o_jptr = add_vec(b, jt.ptr);
+    const size_t o_jlist = add_vec(b, jt.list), o_jent = add_vec(b, jt.ent);
+    const size_t o_jtgt = add_vec(b, jt.tgt);
     size_t o_wmap[3], o_wstart[3], o_wgat[3];
     for (int v = 0; v < 3; ++v) {
         o_wmap[v] = add_vec(b, wmap[v]);
@@ -871,6 +999,15 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
     v.gneg = (const int32_t *)at(o_gneg);
     v.goff = (const int32_t *)at(o_goff);
     v.gent = (const uint4 *)at(o_gent);
+    v.jnv = jt.nv;
+    v.jrows = jt.rows;
+    v.jnblk = jt.nblk;
+    v.jpts = jt.pts;
+    v.jval = (const uint32_t *)at(o_jval);
+    v.jptr = (const int32_t *)at(o_jptr);
+    v.jlist = (const uint2 *)at(o_jlist);
+    v.jent = (const uint2 *)at(o_jent);
+    v.jtgt = (const uint16_t *)at(o_jtgt);
     v.wnw = ws.nw;
     v.nplog = nplog;
     v.wrx = (const DevWide *)at(o_wrx);
@@ -926,6 +1063,7 @@ bool rebase_tables(const kx_mech *m, const void *base, MechDev *out)
     KX_REBASE(gsoa);
     KX_REBASE(gpos); KX_REBASE(gneg); KX_REBASE(goff); KX_REBASE(gent);
     KX_REBASE(wrx); KX_REBASE(wrx32); KX_REBASE(waux); KX_REBASE(wplog); KX_REBASE(wsp);
+    KX_REBASE(jval); KX_REBASE(jptr); KX_REBASE(jlist); KX_REBASE(jent); KX_REBASE(jtgt);
     for (int q = 0; q < 3; ++q) {
         KX_REBASE(wmaps[q].species); KX_REBASE(wmaps[q].start); KX_REBASE(wmaps[q].gather);
     }
