@@ -22,6 +22,7 @@ constexpr int kMaxFitOrder = 8;
 constexpr int kWave = 64;
 constexpr int kMaxQss = 64;          // QSS species per mechanism (one wave of rows)
 constexpr int kWideMaxSpecies = 128; // one-lane-per-point kernels (species rows in LDS)
+constexpr int kWideQss = 7;           // QSS species of the one-lane-per-point kernel
 constexpr int kJacBlockSpecies = 128;   // Jacobian in row blocks
 constexpr int kChunkMax = 192;       // reactions per chunk of the gather lists, at most
 
@@ -227,6 +228,14 @@ struct MechDev {
                                //  reactants, among its products}
     const int2 *qrx;           // [nr] kernel order: QSS index among the reactants,
                                // among the products (-1: none)
+    // One lane per point (kx_qss.hip), up to kWideQss QSS species and no more than
+    // waves: wnqr reactions with a QSS species of non-zero net nu (0: not laid out),
+    // qchunk of them at a time (two rate rows each)
+    int32_t wnqr, qchunk;
+    const int32_t *qsp;        // [nq] species of a QSS index
+    const int32_t *qlist;      // [wnqr] kernel order
+    const uint32_t *qstart;    // [nq], qgather: the streams of a balance row (WideMap), its
+    const uint4 *qgather;      // accumulators the columns of [A | b]
 };
 
 // Work list of one batch of served requests (device memory, written by the

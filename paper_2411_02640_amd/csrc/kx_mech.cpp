@@ -736,6 +736,51 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
         }
     }
     if (qrow_ent.empty()) qrow_ent.push_back(int4{0, 0, -1, -1});
+    // the balances of the one-lane-per-point kernel: the reactions that enter
+    // them, and per balance row the streams of its columns (rate rows 2 r and
+    // 2 r + 1 hold the forward and reverse terms of reaction r of a chunk)
+    std::vector<int32_t> qsp, qlist;
+    std::vector<uint32_t> qstart, qgather;
+    int qchunk = 0;
+    {
+        const WideShape q = wide_shape(ns, nr);
+        if (nq > 0 && nq <= std::min(kWideQss, q.nw)) {
+            std::vector<int> seen(nr, -1);
+            for (int k = 0; k < ns; ++k)
+                if (qidx[k] >= 0) qsp.push_back(k);
+            for (int s = 0; s < nr; ++s)
+                for (int k : qsp)
+                    if (seen[s] < 0 && net_nu(d, perm[s], k) != 0) {
+                        seen[s] = (int)qlist.size();
+                        qlist.push_back(s);
+                    }
+            qchunk = std::max(1, q.chunk / 2);
+            const int nqr = (int)qlist.size();
+            for (int j = 0; j < nq; ++j) {
+                qstart.push_back((uint32_t)(qgather.size() / 4));
+                for (int c0 = 0; c0 < nqr; c0 += qchunk) {
+                    const size_t head = qgather.size();
+                    qgather.resize(head + 4, 0);
+                    for (int col = 0; col <= nq; ++col) {
+                        const size_t first = qgather.size();
+                        for (int r = c0; r < std::min(nqr, c0 + qchunk); ++r) {
+                            const int s = qlist[r], nu = net_nu(d, perm[s], qsp[j]);
+                            for (int side = 0; side < 2; ++side) {
+                                const int at = side ? qrx[s].y : qrx[s].x;
+                                if ((at >= 0 ? at : nq) != col) continue;
+                                for (int u = 0; u < std::abs(nu); ++u)
+                                    qgather.push_back((uint32_t)(2 * (r - c0) + side) |
+                                                      ((nu < 0) != (side == 1) ? 0x80000000u : 0u));
+                            }
+                        }
+                        while (qgather.size() % 4) qgather.push_back((uint32_t)(2 * qchunk));
+                        qgather[head + col / 4] |= (uint32_t)((qgather.size() - first) / 4)
+                                                   << (8 * (col % 4));
+                    }
+                }
+            }
+        }
+    }
 
     // ---- species thermo
     std::vector<DevSpecies> spv(ns);
@@ -926,6 +971,8 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
     const size_t o_gent = add_vec(b, gent);
     const size_t o_wrx = add_vec(b, wrx), o_wrx32 = add_vec(b, wrx32), o_waux = add_vec(b, waux);
     const size_t o_wplog = add_vec(b, wplog), o_wsp = add_vec(b, wsp);
+    const size_t o_qsp = add_vec(b, qsp), o_qlist = add_vec(b, qlist);
+    const size_t o_qstart = add_vec(b, qstart), o_qgather = add_vec(b, qgather);
     const size_t o_jval = add_vec(b, jt.val), o_jptr = add_vec(b, jt.ptr);
     const size_t o_jlist = add_vec(b, jt.list), o_jent = add_vec(b, jt.ent);
     const size_t o_jtgt = add_vec(b, jt.tgt);
@@ -1044,6 +1091,12 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
     v.nq = nq;
     v.nqent = nq > 0 ? qrow_ptr[nq] : 0;
     v.qidx = (const int32_t *)at(o_qidx);
+    v.wnqr = (int32_t)qlist.size();
+    v.qchunk = qchunk;
+    v.qsp = (const int32_t *)at(o_qsp);
+    v.qlist = (const int32_t *)at(o_qlist);
+    v.qstart = (const uint32_t *)at(o_qstart);
+    v.qgather = (const uint4 *)at(o_qgather);
     v.qrx = (const int2 *)at(o_qrx);
     v.qrow_ptr = (const int32_t *)at(o_qptr);
     v.qrow_ent = (const int4 *)at(o_qent);
@@ -1072,6 +1125,7 @@ bool rebase_tables(const kx_mech *m, const void *base, MechDev *out)
     KX_REBASE(visc32); KX_REBASE(cond32); KX_REBASE(wq32); KX_REBASE(wilke32);
     KX_REBASE(dfit32); KX_REBASE(ddiag32);
     KX_REBASE(gfrag); KX_REBASE(c1frag); KX_REBASE(gfrag32); KX_REBASE(c1frag32);
+    KX_REBASE(qsp); KX_REBASE(qlist); KX_REBASE(qstart); KX_REBASE(qgather);
     KX_REBASE(qidx); KX_REBASE(qrow_ptr); KX_REBASE(qrow_ent); KX_REBASE(qrx);
 #undef KX_REBASE
     // every table pointer must have moved: no 8-byte word of the result may

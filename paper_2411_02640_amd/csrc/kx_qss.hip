@@ -10,6 +10,9 @@
 // sums run over transported species (a QSS species may not carry an
 // efficiency; [M] = p/(R_u T) is their total concentration).
 //
+// Two kernels: one lane per point (below), for up to kWideQss QSS species and
+// calls of more than a few thousand points, and one wave per point:
+//
 // Work decomposition: one workgroup of one wave per point.
 //  1. species (thread = k): a_k = (p_atm/RT) e^{-g_k} (eq:K_p, eq:Ck) and C_k;
 //     a QSS slot holds C = 1, so the products of phase 2 leave its factor out;
@@ -42,6 +45,7 @@
 
 #include "kx_internal.h"
 #include "kx_math.h"
+#include "kx_wide.h"
 
 namespace kx {
 namespace {
@@ -369,6 +373,113 @@ __global__ __launch_bounds__(kWave) void qss_kernel(MechDev m, int64_t n,
     }
 }
 
+// ---------------------------------------------------------------------------
+// One lane per point (kx_wide.h): one tile of 64 points by NW waves.  A pass over
+// the reactions that enter the balances writes their forward and reverse terms
+// with the QSS factor left out (C = 1 in the QSS rows) as two rate rows each, and
+// wave j sums the entries of row j of [A | b] in registers; the waves then take
+// Gauss-Jordan steps on the diagonal together, the pivot row passing through the
+// LDS, and the solved C_Q replace C = 1 in the species rows, from which the rates
+// of every reaction follow as in the rates kernel.
+//
+// Against one wave per point (the kernel above): 53 species with 6 QSS species,
+// 2^18 points, 1.48 -> 0.37 ms (20000 points 117 -> 52 us): lanes no longer idle in
+// the species, row and gather phases.  The reactions that enter the balances (a
+// third) are evaluated twice, which costs less than keeping their terms per point.
+// It is bound as the rates kernel is, by vector issue and scalar-load latency.
+constexpr int kPivotRows = 16;  // two buffers of [A | b] rows
+
+// LDS rows of a workgroup: the rate rows serve the balances (two per reaction and
+// the zero row) and the pivots too.
+size_t qss_wide_lds_bytes(const MechDev &m, int nw)
+{
+    const size_t rows = std::max({m.wmaps[nw == 16 ? 2 : 0].chunk + 1, 2 * m.qchunk + 1, kPivotRows});
+    return sizeof(double) * kRow * (2 * (size_t)(m.ns + 2) + rows);
+}
+
+template <int NW, bool RATES>
+__global__ __launch_bounds__(NW *kWave, wide_waves(NW)) void qss_wide_kernel(
+    MechDev m, int64_t n, const double *__restrict__ T, const double *__restrict__ P,
+    const double *__restrict__ Y, double *__restrict__ wdot, double *__restrict__ Cq)
+{
+    extern __shared__ double lds[];
+    constexpr int NA = kWideQss + 1;  // columns of [A | b]
+    const int64_t i0 = (int64_t)blockIdx.x * kRow;
+    const WideTile<NW> t(m, m.wmaps[NW == 16 ? 2 : 0], i0, (int)min((int64_t)kRow, n - i0));
+    const Exp2 ex;
+    const WidePoint q = species_rows<false, NW, true>(ex, m, t, n, T, P, Y, lds);
+    double *sq = t.rates(m, lds);
+    const int nq = m.nq, w = t.w, lane = t.lane;
+    const unsigned lane8 = 8u * (unsigned)lane;
+
+    // ---- row w of [A | b]
+    if (w == 0) sq[2 * m.qchunk * kRow + lane] = 0.0;
+    double a[NA], unused[NA];
+#pragma unroll
+    for (int c = 0; c < NA; ++c) a[c] = unused[c] = 0.0;
+    KX_CONST uint32_t *g = (KX_CONST uint32_t *)(const_table(m.qgather) +
+                                                 (w < nq ? const_table(m.qstart)[w] : 0u));
+    for (int c0 = 0; c0 < m.wnqr; c0 += m.qchunk) {
+        const int cnt = min(m.qchunk, m.wnqr - c0);
+        const uint32_t h0 = g[0], h1 = g[1];
+        for (int r = w; r < cnt; r += NW) {
+            const WideTerms x = reaction_wide<false>(
+                ex, m, const_table(m.wrx) + const_table(m.qlist)[c0 + r], lds, lane8, q);
+            const double k = x.ckf * x.A;
+            sq[2 * r * kRow + lane] = k * x.Bf;
+            sq[(2 * r + 1) * kRow + lane] = k * x.Br;
+        }
+        __syncthreads();
+        if (w < nq) g = gather_stream<false>(g, h0, h1, sq, lane8, a, unused);
+        __syncthreads();
+    }
+    // ---- elimination on the diagonal (see the head of this file)
+#pragma unroll
+    for (int k = 0; k < kWideQss; ++k) {
+        if (k < nq) {
+            double *piv = sq + (k & 1) * (kPivotRows / 2) * kRow + lane;
+            if (w == k) {
+#pragma unroll
+                for (int c = k; c < NA; ++c)
+                    if (c <= nq) piv[c * kRow] = a[c];
+            }
+            __syncthreads();
+            if (w < nq && w != k) {
+                const double f = -(a[k] / piv[k * kRow]);
+#pragma unroll
+                for (int c = k + 1; c < NA; ++c)
+                    if (c <= nq) a[c] = fma(f, piv[c * kRow], a[c]);
+            }
+        }
+    }
+    if (w < nq) {
+        double diag = a[0], rhs = a[NA - 1];
+#pragma unroll
+        for (int c = 0; c < NA; ++c) {
+            if (c == w) diag = a[c];
+            if (c == nq) rhs = a[c];
+        }
+        const double x = -rhs / diag;
+        if (Cq && t.store) Cq[(int64_t)w * n + t.i] = x;
+        if (RATES) {
+            double *row = lds + 2 * const_table(m.qsp)[w] * kRow + lane;
+            row[kRow] = x * krcp(row[0]);
+        }
+    }
+    if (RATES) {
+        __syncthreads();
+        rates_of_rows<false, NW, true>(ex, m, t, q, n, lds, wdot);
+    }
+}
+
+template <bool RATES> const void *qss_wide_instance(int nw)
+{
+    return nw == 4    ? (const void *)qss_wide_kernel<4, RATES>
+           : nw == 8  ? (const void *)qss_wide_kernel<8, RATES>
+           : nw == 12 ? (const void *)qss_wide_kernel<12, RATES>
+                      : (const void *)qss_wide_kernel<16, RATES>;
+}
+
 template <class K>
 kx_status set_lds(K kern, size_t lds)
 {
@@ -383,6 +494,25 @@ kx_status launch_qss(const kx_mech *mech, int64_t n, const double *T, const doub
                      const double *Y, double *wdot, double *Cq, hipStream_t s)
 {
     const MechDev &m = mech->dev;
+    // Up to 4096 points every point has a wave of its own resident at once, and one
+    // wave per point has the shorter chain (53 species: 19 us at 1000 points, 41 at
+    // 5000, the one-lane-per-point kernel 34 at both).
+    if (m.wnqr && n > 4096) {
+        const int64_t nblk = (n + kRow - 1) / kRow;
+        if (nblk > 0x7fffffff) return fail(KX_EINVAL, "QSS rates: n too large");
+        // as the rates kernel: 16 waves a tile where every tile has a CU of its own
+        const int nw = nblk <= 256 ? 16 : m.wnw;
+        const void *kern = wdot ? qss_wide_instance<true>(nw) : qss_wide_instance<false>(nw);
+        const size_t lds = qss_wide_lds_bytes(m, nw);
+        hipError_t e =
+            hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute (qss LDS)");
+        void *args[] = {(void *)&m, (void *)&n,    (void *)&T, (void *)&p,
+                        (void *)&Y, (void *)&wdot, (void *)&Cq};
+        e = hipLaunchKernel(kern, dim3((unsigned)nblk), dim3(nw * kWave), args, lds, s);
+        if (e != hipSuccess) return hip_fail(e, "QSS rates kernel launch");
+        return ok();
+    }
     const size_t lds = qss_lds_bytes(m);
     if (lds > 160 * 1024)
         return fail(KX_EUNSUPPORTED, "QSS rates: mechanism too large for one workgroup's LDS");

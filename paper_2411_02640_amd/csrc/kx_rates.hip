@@ -367,18 +367,6 @@ __device__ __forceinline__ double gibbs(const double (&g)[7], double T, double l
     return fma(g[0], 1.0 - lnT, poly) + fma(g[5], invT, g[6]);
 }
 
-template <bool MIXED>
-__device__ __forceinline__ void accumulate(double &acc, double &cmp, double t)
-{
-    if (MIXED) {
-        const double sum = acc + t;
-        cmp += (fabs(acc) >= fabs(t)) ? (acc - sum) + t : (t - sum) + acc;
-        acc = sum;
-    } else {
-        acc += t;
-    }
-}
-
 // Two groups' partial sums ga, gb per trip of a gather loop: FP64 adds each to
 // the running sum as it is formed (first_of_pair, then second_of_pair); the
 // mixed path adds their sum with one compensated step (the two groups' plain
@@ -823,75 +811,19 @@ __global__ __launch_bounds__(kWave, SPL == 1 ? 3 : 2) void rates_items_kernel(
 
 // ---------------------------------------------------------------------------
 // One lane per point (mechanisms of up to kWideMaxSpecies species, see
-// kx_wide.h): one tile of 64 points by NW waves.  i0: first point; points past
-// npts repeat the last one and are not stored.
-template <bool MIXED, int NW, bool CQ>
+// kx_wide.h): one tile of 64 points by NW waves.
+template <bool MIXED, int NW>
 __device__ __forceinline__ void rates_wide_tile(const MechDev &m, int64_t ld, int64_t i0, int npts,
                                                 const double *__restrict__ T,
                                                 const double *__restrict__ P,
                                                 const double *__restrict__ Y,
-                                                const double *__restrict__ cq,
                                                 double *__restrict__ wdot)
 {
-#pragma clang fp contract(off)
     extern __shared__ double lds[];
-    constexpr int NS = wide_species(NW);
-    const int lane = threadIdx.x & (kWave - 1);
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const WideMap &wm = m.wmaps[NW == 16 ? (MIXED ? 1 : 2) : 0];
-    const int nr = m.nr, chunk = wm.chunk;
-    const int64_t i = i0 + min(lane, npts - 1);
-    double *sq = lds + 2 * (m.ns + 2) * kRow;  // rate rows
+    const WideTile<NW> t(m, m.wmaps[NW == 16 ? (MIXED ? 1 : 2) : 0], i0, npts);
     const Exp2 ex;
-    int ks[NS];  // species of this wave
-#pragma unroll
-    for (int s = 0; s < NS; ++s) ks[s] = const_table(wm.species)[8 * w + s];
-    const WidePoint q =
-        species_rows<MIXED, NW, CQ>(ex, m, ks, w, lane, ld, i, T, P, Y, cq, lds, sq);
-    if (w == 0) sq[chunk * kRow + lane] = 0.0;
-
-    KX_CONST DevWide *rx = const_table(MIXED ? m.wrx32 : m.wrx);
-    KX_CONST uint32_t *g =
-        (KX_CONST uint32_t *)(const_table(wm.gather) + const_table(wm.start)[w]);
-    const unsigned lane8 = 8u * (unsigned)lane;
-    double acc[NS], cmp[NS];
-#pragma unroll
-    for (int s = 0; s < NS; ++s) acc[s] = cmp[s] = 0.0;
-    for (int c = 0; c < wm.nchunks; ++c) {
-        const int base = c * chunk, cnt = min(chunk, nr - base);
-        const uint32_t h0 = g[0], h1 = g[1];  // groups of each species
-        for (int r = w; r < cnt; r += NW) {
-            const WideTerms t = reaction_wide<MIXED>(ex, m, rx + base + r, lds, lane8, q);
-            sq[r * kRow + lane] = t.ckf * t.A * (t.Bf - t.Br);
-        }
-        __syncthreads();
-        g += 4;
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-#pragma clang loop unroll(disable)
-            for (int n = ((s < 4 ? h0 : h1) >> 8 * (s & 3)) & 255u; n > 0; --n, g += 4) {
-                double v[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = row_val(sq, g[e], lane8);
-                auto nu = [&](int e) { return (int)g[e] < 0 ? -1.0 : 1.0; };
-                if (MIXED) {
-                    double t = v[0] * nu(0);
-#pragma unroll
-                    for (int e = 1; e < 4; ++e) t = fma(v[e], nu(e), t);
-                    accumulate<true>(acc[s], cmp[s], t);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[s] = fma(v[e], nu(e), acc[s]);
-                }
-            }
-        }
-        if (c + 1 < wm.nchunks) __syncthreads();
-    }
-    if (lane < npts) {
-#pragma unroll
-        for (int s = 0; s < NS; ++s)
-            if (ks[s] >= 0) wdot[(int64_t)ks[s] * ld + i] = MIXED ? acc[s] + cmp[s] : acc[s];
-    }
+    const WidePoint q = species_rows<MIXED, NW, false>(ex, m, t, ld, T, P, Y, lds);
+    rates_of_rows<MIXED, NW, false>(ex, m, t, q, ld, lds, wdot);
 }
 
 template <bool MIXED, int NW>
@@ -900,8 +832,7 @@ __global__ __launch_bounds__(NW *kWave, wide_waves(NW)) void rates_wide_kernel(
     const double *__restrict__ Y, double *__restrict__ wdot)
 {
     const int64_t i0 = (int64_t)blockIdx.x * kRow;
-    rates_wide_tile<MIXED, NW, false>(m, n, i0, (int)min((int64_t)kRow, n - i0), T, P, Y, nullptr,
-                                      wdot);
+    rates_wide_tile<MIXED, NW>(m, n, i0, (int)min((int64_t)kRow, n - i0), T, P, Y, wdot);
 }
 
 // Batched requests, one tile per workgroup.
@@ -914,8 +845,8 @@ __global__ __launch_bounds__(NW *kWave, wide_waves(NW)) void rates_wide_items_ke
     const int r = work_item_ballot(wl, 0, t);
     const WorkItem it = wl->items[r];
     const int64_t i0 = (int64_t)(t - wl->start[0][r]) * kRow;
-    rates_wide_tile<MIXED, NW, false>(m, it.n, i0, (int)min((int64_t)kRow, it.n - i0), it.T, it.p,
-                                      it.Y, nullptr, it.wdot);
+    rates_wide_tile<MIXED, NW>(m, it.n, i0, (int)min((int64_t)kRow, it.n - i0), it.T, it.p,
+                                it.Y, it.wdot);
 }
 
 // Batched requests, persistent workgroups taking one tile at a time from one
@@ -936,8 +867,8 @@ __global__ __launch_bounds__(NW *kWave, wide_waves(NW)) void rates_wide_batch_ke
         r = work_item_of(wl, 0, t, r);
         const WorkItem it = wl->items[r];
         const int64_t i0 = (int64_t)(t - wl->start[0][r]) * kRow;
-        rates_wide_tile<MIXED, NW, false>(m, it.n, i0, (int)min((int64_t)kRow, it.n - i0), it.T,
-                                          it.p, it.Y, nullptr, it.wdot);
+        rates_wide_tile<MIXED, NW>(m, it.n, i0, (int)min((int64_t)kRow, it.n - i0), it.T,
+                                    it.p, it.Y, it.wdot);
     }
 }
 

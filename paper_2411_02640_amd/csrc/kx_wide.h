@@ -52,6 +52,18 @@ __device__ __forceinline__ float log10_wide(double v)
     return (__log2f((float)mant) + (float)ex) * 0.30102999566398120f;
 }
 
+template <bool MIXED>
+__device__ __forceinline__ void accumulate(double &acc, double &cmp, double t)
+{
+    if (MIXED) {
+        const double sum = acc + t;
+        cmp += (fabs(acc) >= fabs(t)) ? (acc - sum) + t : (t - sum) + acc;
+        acc = sum;
+    } else {
+        acc += t;
+    }
+}
+
 // the FP64 steps round the same way in every instance (number of waves, batch
 // or direct launch): fused multiply-adds only where written
 #pragma float_control(push)
@@ -276,24 +288,49 @@ __device__ __forceinline__ WideTerms reaction_wide(const Exp2 &ex, const MechDev
     return t;
 }
 
-// Phase 1 of a tile: the point constants (returned) and the species rows.
-// `part` are the tile's rate rows (not yet in use), four of which carry partial
-// sums of Y_k / W_k: the sums are the same whatever the number of waves, so a
-// point's results are too.  CQ: the mechanism has QSS species; their 1/W in wsp
-// is 0 (the mixture is that of the transported species) and their
-// concentrations come from cq[j][i] (null: the slot's C is 1).
-template <bool MIXED, int NW, bool CQ>
+// A workgroup's tile of 64 points: this lane's point (points past npts repeat
+// the last one and are not stored), this wave's species, and the LDS rows.
+template <int NW> struct WideTile {
+    static constexpr int NS = wide_species(NW);
+    const WideMap &wm;
+    int lane, w;
+    int64_t i;
+    bool store;
+    int ks[NS];  // species of this wave (-1: none)
+    __device__ __forceinline__ WideTile(const MechDev &m, const WideMap &map, int64_t i0, int npts)
+        : wm(map)
+    {
+        lane = threadIdx.x & (kWave - 1);
+        w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+        i = i0 + min(lane, npts - 1);
+        store = lane < npts;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) ks[s] = const_table(wm.species)[8 * w + s];
+    }
+    // the rate rows
+    __device__ __forceinline__ double *rates(const MechDev &m, double *lds) const
+    {
+        return lds + 2 * (m.ns + 2) * kRow;
+    }
+};
+
+// Phase 1 of a tile: the point constants (returned) and the species rows.  Four
+// of the rate rows (not yet in use) carry partial sums of Y_k / W_k: the sums are
+// the same whatever the number of waves, so a point's results are too.  QSS: the
+// mechanism has QSS species; their 1/W in wsp is 0 (the mixture is that of the
+// transported species) and C = 1 in their rows.
+template <bool MIXED, int NW, bool QSS>
 __device__ __forceinline__ WidePoint species_rows(const Exp2 &ex, const MechDev &m,
-                                                  const int (&ks)[wide_species(NW)], int w,
-                                                  int lane, int64_t ld, int64_t i,
+                                                  const WideTile<NW> &tile, int64_t ld,
                                                   const double *__restrict__ T,
                                                   const double *__restrict__ P,
-                                                  const double *__restrict__ Y,
-                                                  const double *__restrict__ cq, double *lds,
-                                                  double *part)
+                                                  const double *__restrict__ Y, double *lds)
 {
     constexpr int NS = wide_species(NW);
-    const int ns = m.ns;
+    const int ns = m.ns, w = tile.w, lane = tile.lane;
+    const int64_t i = tile.i;
+    const int(&ks)[NS] = tile.ks;
+    double *part = tile.rates(m, lds);
     KX_CONST double *sp = const_table(m.wsp);
     WidePoint q;
     q.T = T[i];
@@ -305,7 +342,7 @@ __device__ __forceinline__ WidePoint species_rows(const Exp2 &ex, const MechDev 
     for (int s = 0; s < NS; ++s) {
         if (ks[s] >= 0) {
             const double iw = sp[16 * ks[s] + 15];
-            y[s] = CQ && iw == 0.0 ? 0.0 : y[s] * iw;  // a QSS entry of Y is not read
+            y[s] = QSS && iw == 0.0 ? 0.0 : y[s] * iw;  // a QSS entry of Y is not read
             lds[2 * ks[s] * kRow + lane] = y[s];
         }
     }
@@ -348,10 +385,7 @@ __device__ __forceinline__ WidePoint species_rows(const Exp2 &ex, const MechDev 
     for (int s = 0; s < NS; ++s) {
         if (ks[s] >= 0) {
             double C = y[s] * cf;
-            if (CQ) {
-                const int jq = const_table(m.qidx)[ks[s]];
-                if (jq >= 0) C = cq ? cq[(int64_t)jq * ld + i] : 1.0;
-            }
+            if (QSS && sp[16 * ks[s] + 15] == 0.0) C = 1.0;
             double *row = lds + 2 * ks[s] * kRow + lane;
             row[0] = a[s];
             row[kRow] = C * krcp(a[s]);
@@ -364,6 +398,77 @@ __device__ __forceinline__ WidePoint species_rows(const Exp2 &ex, const MechDev 
     }
     __syncthreads();
     return q;
+}
+
+// One chunk's part of a wave's sums: acc[s] += sum of +-1 times the rate rows
+// that the stream at g lists for accumulator s; h0, h1: its header's counts.
+template <bool MIXED, int NS>
+__device__ __forceinline__ KX_CONST uint32_t *gather_stream(KX_CONST uint32_t *g, uint32_t h0,
+                                                            uint32_t h1, const double *sq,
+                                                            unsigned lane8, double (&acc)[NS],
+                                                            double (&cmp)[NS])
+{
+    g += 4;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+#pragma clang loop unroll(disable)
+        for (int n = ((s < 4 ? h0 : h1) >> 8 * (s & 3)) & 255u; n > 0; --n, g += 4) {
+            double v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = row_val(sq, g[e], lane8);
+            auto nu = [&](int e) { return (int)g[e] < 0 ? -1.0 : 1.0; };
+            if (MIXED) {
+                double t = v[0] * nu(0);
+#pragma unroll
+                for (int e = 1; e < 4; ++e) t = fma(v[e], nu(e), t);
+                accumulate<true>(acc[s], cmp[s], t);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[s] = fma(v[e], nu(e), acc[s]);
+            }
+        }
+    }
+    return g;
+}
+
+// Phases 2 and 3: the rates of progress of every reaction from the species rows,
+// chunk by chunk, and wdot.  QSS: the QSS rows of wdot are written as 0.
+template <bool MIXED, int NW, bool QSS>
+__device__ __forceinline__ void rates_of_rows(const Exp2 &ex, const MechDev &m,
+                                              const WideTile<NW> &t, const WidePoint &q, int64_t ld,
+                                              double *lds, double *__restrict__ wdot)
+{
+    constexpr int NS = wide_species(NW);
+    const int nr = m.nr, chunk = t.wm.chunk;
+    double *sq = t.rates(m, lds);
+    if (t.w == 0) sq[chunk * kRow + t.lane] = 0.0;
+    KX_CONST DevWide *rx = const_table(MIXED ? m.wrx32 : m.wrx);
+    KX_CONST uint32_t *g =
+        (KX_CONST uint32_t *)(const_table(t.wm.gather) + const_table(t.wm.start)[t.w]);
+    const unsigned lane8 = 8u * (unsigned)t.lane;
+    double acc[NS], cmp[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) acc[s] = cmp[s] = 0.0;
+    for (int c = 0; c < t.wm.nchunks; ++c) {
+        const int base = c * chunk, cnt = min(chunk, nr - base);
+        const uint32_t h0 = g[0], h1 = g[1];  // groups of each species
+        for (int r = t.w; r < cnt; r += NW) {
+            const WideTerms x = reaction_wide<MIXED>(ex, m, rx + base + r, lds, lane8, q);
+            sq[r * kRow + t.lane] = x.ckf * x.A * (x.Bf - x.Br);
+        }
+        __syncthreads();
+        g = gather_stream<MIXED>(g, h0, h1, sq, lane8, acc, cmp);
+        if (c + 1 < t.wm.nchunks) __syncthreads();
+    }
+    if (t.store) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+            if (t.ks[s] >= 0) {
+                double x = MIXED ? acc[s] + cmp[s] : acc[s];
+                if (QSS && const_table(m.qidx)[t.ks[s]] >= 0) x = 0.0;
+                wdot[(int64_t)t.ks[s] * ld + t.i] = x;
+            }
+    }
 }
 
 #pragma float_control(pop)

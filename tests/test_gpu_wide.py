@@ -45,3 +45,32 @@ def test_shapes_against_the_oracle(ns, n):
         m = min(n, 100)
         assert np.array_equal(_run(kx, dm, T[:m], p[:m], Y[:, :m], prec), w[:, :m])
     dm.close()
+
+
+@pytest.mark.parametrize("spec,n", [(I.MECH_53Q, 16385 + 7), (I.MECH_53XQ, 16385)],
+                         ids=lambda v: getattr(v, "name", str(v)))
+def test_qss_kernels_agree(spec, n):
+    """C_Q and the rates of a QSS mechanism: the same bits from calls of few tiles
+    (16 waves a tile) and of many; one wave per point (small calls) against the
+    oracle's bound through the rates' own term sizes."""
+    from paper_2411_02640_amd import kx
+    print("[gpu-case] wide qss", spec.name, n, flush=True)
+    mech = I.make_mechanism(spec)
+    T, p, Y = I.make_states(53, I.StateSpec(n, seed=79, p_atm_range=(1.0, 40.0), dirichlet_alpha=0.3))
+    dm = kx.Mechanism(mech, 0)
+    d = [torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0") for a in (T, p, Y)]
+
+    def first(m):
+        return d[0][:m].clone(), d[1][:m].clone(), d[2][:, :m].contiguous()
+
+    C, w = kx.qss_concentrations(dm, *d), kx.production_rates(dm, *d)
+    s = first(4097)
+    assert torch.equal(kx.qss_concentrations(dm, *s), C[:, :4097])
+    assert torch.equal(kx.production_rates(dm, *s), w[:, :4097])
+    assert bool((w[np.flatnonzero(mech["qss"]).tolist()] == 0).all())
+    # two evaluations of one balance differ by rounding times its condition, at
+    # most 2e6 for these states, of terms good to 3e-13
+    c1 = kx.qss_concentrations(dm, *first(4096))
+    assert bool(((c1 - C[:, :4096]).abs() <= 6e-7 * C[:, :4096].abs()).all())
+    assert float(((c1 - C[:, :4096]).abs() / C[:, :4096].abs()).median()) <= 1e-12
+    dm.close()
