@@ -238,6 +238,15 @@ struct MechDev {
     const uint4 *qgather;      // accumulators the columns of [A | b]
 };
 
+// Tables read through the constant address space: scalar loads also where the
+// compiler cannot prove that no store of the kernel reaches them.
+#define KX_CONST __attribute__((address_space(4))) const
+
+template <class T> __device__ __forceinline__ KX_CONST T *const_table(const T *p)
+{
+    return (KX_CONST T *)(uintptr_t)p;
+}
+
 // Work list of one batch of served requests (device memory, written by the
 // host before the batch launches).  start[op][r] is the first tile of item r
 // for op 0 (rates) and op 1 (transport); start[op][nitems] = ntiles[op].

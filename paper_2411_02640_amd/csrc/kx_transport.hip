@@ -797,6 +797,12 @@ __global__ void zero_kernel(int *p, int count)
 }
 
 // Mixture thermo (App. A.1): cp_k = Cp_k/W_k, h_k = H_k/W_k, cp = sum Y_k cp_k.
+// Bound by memory (one row read and two written per species).  The four waves of
+// a workgroup take every fourth species of its 64 points, four Y rows of a wave in
+// flight: a call of few points has four times the waves at a quarter of the chain
+// (53 species, 1000 points 27 -> 12 us), a large one more loads in flight (2^20
+// points 327 -> 281 us, 4.8 TB/s; 200 species, 100003 points 273 -> 147 us).  The
+// outputs are not read again here: non-temporal stores (131072 points 35 -> 29 us).
 __global__ __launch_bounds__(kBlock) void thermo_kernel(MechDev m, int64_t n,
                                                         const double *__restrict__ T,
                                                         const double *__restrict__ Y,
@@ -804,27 +810,57 @@ __global__ __launch_bounds__(kBlock) void thermo_kernel(MechDev m, int64_t n,
                                                         double *__restrict__ hk,
                                                         double *__restrict__ cpmix)
 {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    const double Ti = T[i], invT = 1.0 / Ti;
+    constexpr int NW = kBlock / kWave;
+    __shared__ double part[NW][kWave];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t i = (int64_t)blockIdx.x * kWave + lane;
+    const int64_t ic = min(i, n - 1);  // lanes past the end repeat the last point
+    const bool act = i < n;
+    const double t = T[ic], invT = 1.0 / t;
     double cp = 0.0;
-    for (int k = 0; k < m.ns; ++k) {
-        const DevSpecies &S = m.sp[k];
-        const double *a = (Ti < S.t_mid) ? S.nasa_lo : S.nasa_hi;
-        const double cpr = fma(Ti, fma(Ti, fma(Ti, fma(Ti, a[4], a[3]), a[2]), a[1]), a[0]);
-        const double c = cpr * kRu * S.inv_W;
-        if (cpk) cpk[(int64_t)k * n + i] = c;
-        if (hk) {
-            const double hrt =
-                fma(Ti, fma(Ti, fma(Ti, fma(Ti, a[4] * 0.2, a[3] * 0.25), a[2] * (1.0 / 3.0)),
-                            a[1] * 0.5),
-                    a[0]) +
-                a[5] * invT;
-            hk[(int64_t)k * n + i] = hrt * kRu * Ti * S.inv_W;
+    constexpr int U = 4;  // species per trip
+    for (int k0 = w; k0 < m.ns; k0 += U * NW) {
+        double y[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) y[u] = Y[(int64_t)min(k0 + u * NW, m.ns - 1) * n + ic];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = k0 + u * NW;
+            if (k >= m.ns) break;
+            KX_CONST DevSpecies &S = const_table(m.sp)[k];
+            const bool lo = t < S.t_mid;
+            // both ranges' values, one kept: cheaper than selecting coefficients (the
+            // asm keeps the compiler from selecting the table's address instead, and
+            // reading the coefficients per lane)
+            auto pick = [&](double a, double b) {
+                asm("" : "+v"(a), "+v"(b));
+                return lo ? a : b;
+            };
+            auto cpr = [&](KX_CONST double *a) {
+                return fma(t, fma(t, fma(t, fma(t, a[4], a[3]), a[2]), a[1]), a[0]);
+            };
+            const double c = pick(cpr(S.nasa_lo), cpr(S.nasa_hi)) * kRu * S.inv_W;
+            cp = fma(y[u], c, cp);
+            if (cpk && act) __builtin_nontemporal_store(c, cpk + (int64_t)k * n + i);
+            if (hk) {
+                auto hrt = [&](KX_CONST double *a) {
+                    return fma(t, fma(t, fma(t, fma(t, a[4] * 0.2, a[3] * 0.25), a[2] * (1.0 / 3.0)),
+                                      a[1] * 0.5),
+                               a[0]) +
+                           a[5] * invT;
+                };
+                const double h = pick(hrt(S.nasa_lo), hrt(S.nasa_hi)) * kRu * t * S.inv_W;
+                if (act) __builtin_nontemporal_store(h, hk + (int64_t)k * n + i);
+            }
         }
-        cp = fma(Y[(int64_t)k * n + i], c, cp);
     }
-    if (cpmix) cpmix[i] = cp;
+    if (cpmix) {
+        part[w][lane] = cp;
+        __syncthreads();
+        if (w == 0 && act)
+            cpmix[i] = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
+    }
 }
 
 // Points per lane and k-block size, measured on the 53-species workload:
@@ -1050,10 +1086,10 @@ kx_status launch_zero(int *p, int count, hipStream_t s)
 kx_status launch_thermo(const kx_mech *mech, int64_t n, const double *T, const double *Y,
                         double *cpk, double *hk, double *cpmix, hipStream_t s)
 {
-    const int64_t nblk = (n + kBlock - 1) / kBlock;
+    const int64_t nblk = (n + kWave - 1) / kWave;
     if (nblk > 0x7fffffff) return fail(KX_EINVAL, "thermo: n too large");
-    hipLaunchKernelGGL(thermo_kernel, dim3((unsigned)nblk), dim3(kBlock), 0, s, mech->dev, n,
-                       T, Y, cpk, hk, cpmix);
+    hipLaunchKernelGGL(thermo_kernel, dim3((unsigned)nblk), dim3(kBlock), 0, s, mech->dev, n, T, Y,
+                       cpk, hk, cpmix);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "thermo kernel launch");
     return ok();

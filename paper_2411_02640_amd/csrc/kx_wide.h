@@ -25,15 +25,6 @@
 
 namespace kx {
 
-// Tables read through the constant address space: scalar loads also where the
-// compiler cannot prove that no store of the kernel reaches them.
-#define KX_CONST __attribute__((address_space(4))) const
-
-template <class T> __device__ __forceinline__ KX_CONST T *const_table(const T *p)
-{
-    return (KX_CONST T *)(uintptr_t)p;
-}
-
 // exp(x) for the mixed path: the argument stays in FP64, is reduced by n ln 2
 // in FP64 and only exp(r), |r| <= ln2/2, is evaluated in FP32.
 __device__ __forceinline__ double exp_mixed(double x)
