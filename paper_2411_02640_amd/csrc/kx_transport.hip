@@ -4,13 +4,10 @@
 //  * the matrix-core kernel (tables holding fits of 1/D_kj and at least 24
 //    species): the pair sums as products of fixed matrices with per-point
 //    stacks on 16x16x4 MFMAs, described where it is defined below;
-//  * the vector-ALU kernel (tables of D_kj fits, or fewer species): each lane
-//    evaluates P grid points, every mechanism constant is wave-uniform and read
-//    with scalar loads into scalar registers, used directly as an instruction
-//    operand (one fetched coefficient serves the P points of all 64 lanes); the
-//    quadratic sums run over a block of KB species k held in registers while j
-//    streams over all species, and X_j is recomputed from Y_j (a coalesced
-//    re-read) instead of being held per lane;
+//  * the vector-ALU kernel (tables of D_kj fits, or fewer species): lane = point,
+//    the waves of a workgroup divide the species k, whose sums they hold in
+//    registers while j streams over all species; X_j and rho_j come from LDS rows,
+//    every mechanism constant from scalar loads, as an instruction operand;
 //  * the symmetric evaluation of D_kj fits (KX_DKJ_SYMMETRIC, §2.2.2 / §2.3.2),
 //    described where it is defined below.
 // Common to them:
@@ -114,157 +111,228 @@ template <> struct Tabs<float> {
     static __device__ const float *ddiag(const MechDev &m) { return m.ddiag32; }
 };
 
-// One tile of kBlock * P points starting at point `base` of arrays with n
-// points (species rows of stride n).
-template <class F, int ORDER, int KIND, int P, int KB>
-__device__ __forceinline__ void transport_tile(const MechDev &m, int64_t n, int64_t base,
-                                               const double *__restrict__ T,
-                                               const double *__restrict__ Pp,
-                                               const double *__restrict__ Y,
-                                               double *__restrict__ mu,
-                                               double *__restrict__ lam,
-                                               double *__restrict__ Dmix)
+// Horner with the coefficients read through the constant address space.
+template <int ORDER, class F>
+__device__ __forceinline__ F horner_c(KX_CONST F *c, F u, int order)
+{
+    const int o = ORDER > 0 ? ORDER : order;
+    if (o == 1) return c[0];
+    F r = fma(u, c[o - 1], c[o - 2]);
+#pragma unroll
+    for (int q = ORDER - 3; q >= 0; --q) r = fma_u(r, u, c[q]);
+    if (ORDER == 0)
+        for (int q = o - 3; q >= 0; --q) r = fma_u(r, u, c[q]);
+    return r;
+}
+
+// Vector-ALU kernel: one tile of 64 points (lane = point) starting at point
+// `base` of arrays with n points, by ceil(ns / RW) waves; wave w owns the species
+// k = RW w .. RW w + RW - 1.  Per chunk of kRowsChunk species j the waves put X_j
+// and rho_j of every j into LDS rows (each wave its share), then every wave adds
+// the chunk to the Wilke and D_km sums of its species.  F is the arithmetic type
+// of the fits and mixing sums (double: FP64 path; float: mixed path); KIND is the
+// diffusion fit kind (0: D_kj, 1: 1/D_kj).
+//
+// It is bound by vector issue (about 11 FP64 operations and half a reciprocal per
+// pair for kind 0: two neighbouring j share one, X1/f1 + X2/f2 = (X1 f2 + X2 f1) /
+// (f1 f2)) and by the scalar stream of coefficients (48 bytes per pair and 64
+// points).  The form before it (one thread per four points, all k in turn) ran a
+// chain of ns^2 pairs per wave and recomputed X_j and rho_j per four species k:
+// KX_T_ROWS.
+constexpr int kRowsChunk = 32;
+
+template <class F>
+__host__ __device__ constexpr size_t rows_lds_bytes(int ns, int nw)
+{
+    // the waves' partial sums; X, rho (and for the mixed path lambda_j,
+    // 1 / lambda_j) rows of a chunk, which later hold, with further rows, the
+    // factors X_k eta_k and 1 / den_k of the mixed path's viscosity terms
+    const size_t rows = (size_t)(ns < kRowsChunk ? ns : kRowsChunk) * (sizeof(F) == 8 ? 2 : 4);
+    return (size_t)nw * (sizeof(F) == 8 ? 4 : 1) * kWave * sizeof(double) +
+           (sizeof(F) == 8 || rows > 2 * (size_t)ns ? rows : 2 * (size_t)ns) * kWave * sizeof(F);
+}
+
+template <class F, int ORDER, int KIND, int RW>
+__device__ __forceinline__ void transport_rows_tile(const MechDev &m, int64_t n, int64_t base,
+                                                    const double *__restrict__ T,
+                                                    const double *__restrict__ Pp,
+                                                    const double *__restrict__ Y,
+                                                    double *__restrict__ mu,
+                                                    double *__restrict__ lam,
+                                                    double *__restrict__ Dmix)
 {
     using Tb = Tabs<F>;
+    constexpr bool F64 = std::is_same<F, double>::value;
+    constexpr int NROW = F64 ? 2 : 4;  // LDS rows per species of a chunk
+    extern __shared__ double smem_d[];
     const int ns = m.ns, order = m.fit_order;
-    // point q of this lane: i[q] (clamped to n - 1 past the end; not stored)
-    int64_t idx[P];
-    bool act[P];
-    F u[P];
-    double pr[P], xf[P], wbar[P];
-#pragma unroll
-    for (int q = 0; q < P; ++q) {
-        const int64_t ir = base + threadIdx.x + (int64_t)kBlock * q;
-        act[q] = ir < n;
-        idx[q] = act[q] ? ir : n - 1;
-        const double Ti = T[idx[q]];
-        u[q] = (F)((log(Ti) - m.fit_L0) * m.inv_fit_h);
-        pr[q] = Pp[idx[q]] / kPatm;
-    }
-    auto Yat = [&](int k, int q) { return Y[(int64_t)k * n + idx[q]]; };
+    const int lane = threadIdx.x & (kWave - 1);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int nw = (ns + RW - 1) / RW;
+    constexpr int NPART = F64 ? 4 : 1;
+    double *part = smem_d + lane;
+    F *rows = reinterpret_cast<F *>(smem_d + (size_t)nw * NPART * kWave) + lane;
+    KX_CONST DevSpecies *sp = const_table(m.sp);
+    KX_CONST double *Wt = const_table(m.W);
+    KX_CONST F *visc_t = const_table(Tb::visc(m)), *cond_t = const_table(Tb::cond(m));
+    KX_CONST F *wq_t = const_table(Tb::wq(m));
 
-    // X_k = (Y_k / W_k) xf; W-bar = sum_k X_k W_k; Mathur conductivity
+    const bool act = base + lane < n;
+    const int64_t i = act ? base + lane : n - 1;
+    const F u = (F)((kln(T[i]) - m.fit_L0) * m.inv_fit_h);
+    const double pr = Pp[i] * (1.0 / kPatm);
+    auto Yat = [&](int k) { return Y[(int64_t)k * n + i]; };
     {
-        double sYW[P];
-#pragma unroll
-        for (int q = 0; q < P; ++q) sYW[q] = 0.0;
-        for (int k = 0; k < ns; ++k) {
-            const double iw = m.sp[k].inv_W;
-#pragma unroll
-            for (int q = 0; q < P; ++q) sYW[q] = fma(Yat(k, q), iw, sYW[q]);
-        }
-        F s1[P], s2[P];
-#pragma unroll
-        for (int q = 0; q < P; ++q) {
-            xf[q] = 1.0 / sYW[q];
-            wbar[q] = 0.0;
-            s1[q] = s2[q] = (F)0;
-        }
-        for (int k = 0; k < ns; ++k) {
-            const double iw = m.sp[k].inv_W, Wk = m.W[k];
-            const F *cf = Tb::cond(m) + k * order;
-#pragma unroll
-            for (int q = 0; q < P; ++q) {
-                const double X = Yat(k, q) * iw * xf[q];
-                const F lk = horner<ORDER>(cf, u[q], order);
-                s1[q] = fma((F)X, lk, s1[q]);
-                s2[q] = fma((F)X, rcp_acc(lk), s2[q]);
-                wbar[q] = fma(X, Wk, wbar[q]);
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < P; ++q)
-            if (act[q]) lam[idx[q]] = (double)((F)0.5 * (s1[q] + rcp_acc(s2[q])));
+        double s = 0.0;
+        for (int k = w; k < ns; k += nw) s = fma(Yat(k), sp[k].inv_W, s);
+        part[w * kWave] = s;
     }
+    __syncthreads();
+    double sYW = 0.0;
+    for (int q = 0; q < nw; ++q) sYW += part[q * kWave];
+    const double xf = krcp(sYW);
 
-    F visc[P];
+    F sig[RW], den[RW], acc[RW];
 #pragma unroll
-    for (int q = 0; q < P; ++q) visc[q] = (F)0;
-    const int nkb = (ns + KB - 1) / KB;
-    for (int kb = 0; kb < nkb; ++kb) {
-        // table rows of this block inside the kKB-blocked tables
-        const int tb = (kb * KB) / kKB, toff = (kb * KB) % kKB;
-        F sig[P][KB], den[P][KB], acc[P][KB];
-#pragma unroll
-        for (int kk = 0; kk < KB; ++kk) {
-            const int k = kb * KB + kk;
-            const bool valid = k < ns;
-            const int kc = valid ? k : 0;
-            const F wk = Tb::wq(m)[kc];
-#pragma unroll
-            for (int q = 0; q < P; ++q) {
-                const F ek = horner<ORDER>(Tb::visc(m) + kc * order, u[q], order);
-                // sigma_k = sqrt(eta_k) / W_k^(1/4)
-                sig[q][kk] = valid ? ek * rsqrt_acc(ek) * rcp_acc(wk) : (F)0;
-                den[q][kk] = acc[q][kk] = (F)0;
+    for (int r = 0; r < RW; ++r) {
+        const int k = w * RW + r, kc = min(k, ns - 1);
+        const F ek = horner_c<ORDER>(visc_t + kc * order, u, order);
+        // sigma_k = sqrt(eta_k) / W_k^(1/4)
+        sig[r] = k < ns ? ek * rsqrt_acc(ek) * rcp_acc((F)wq_t[kc]) : (F)0;
+        den[r] = acc[r] = (F)0;
+    }
+    // FP64: this wave's shares of W-bar and Mathur's sums; mixed: Mathur's FP32 sums
+    // in species order by wave 0
+    double wb = 0.0;
+    F s1 = (F)0, s2 = (F)0;
+    for (int j0 = 0; j0 < ns; j0 += kRowsChunk) {
+        const int j1 = min(j0 + kRowsChunk, ns);
+        __syncthreads();  // the previous chunk's rows (and `part`) are read
+        for (int j = j0 + w; j < j1; j += nw) {
+            F *row = rows + (j - j0) * NROW * kWave;
+            const double X = Yat(j) * sp[j].inv_W * xf;
+            row[0] = (F)X;
+            // rho_j = W_j^(1/4) / sqrt(eta_j)
+            row[kWave] = (F)wq_t[j] * rsqrt_acc(horner_c<ORDER>(visc_t + j * order, u, order));
+            const F lk = horner_c<ORDER>(cond_t + j * order, u, order);
+            if constexpr (F64) {
+                s1 = fma(X, lk, s1);
+                s2 = fma(X, rcp_acc(lk), s2);
+            } else {
+                row[2 * kWave] = lk;
+                row[3 * kWave] = rcp_acc(lk);
+            }
+            wb = fma(X, Wt[j], wb);
+        }
+        __syncthreads();
+        if (!F64 && w == 0) {
+            for (int j = 0; j < j1 - j0; ++j) {
+                const F *row = rows + j * NROW * kWave;
+                s1 = fma(row[0], row[2 * kWave], s1);
+                s2 = fma(row[0], row[3 * kWave], s2);
             }
         }
-        const F *c1b = Tb::wilke(m) + (size_t)tb * ns * kKB + toff;
-        const F *dfb = Tb::dfit(m) + ((size_t)tb * ns * kKB + toff) * order;
-        auto steps = [&](int j0, int j1, bool diag) {
-            for (int j = j0; j < j1; ++j) {
-                const double iw = m.sp[j].inv_W;
-                const F wj = Tb::wq(m)[j];
-                const F *vj = Tb::visc(m) + j * order;
-                F Xj[P], rho[P];
+        auto c1_of = [&](int j, int r) {
+            const int k = w * RW + r;
+            return const_table(Tb::wilke(m))[((size_t)(k / kKB) * ns + j) * kKB + k % kKB];
+        };
+        auto fit_of = [&](int j, int r) {
+            const int k = w * RW + r;
+            return horner_c<ORDER>(const_table(Tb::dfit(m)) +
+                                       (((size_t)(k / kKB) * ns + j) * kKB + k % kKB) * order,
+                                   u, order);
+        };
+        auto wilke = [&](int j, int r, F X, F rho) {
+            // X_j phi_kj = c1 X_j (1 + sigma_k rho_j)^2
+            const F t = fma(sig[r], rho, (F)1);
+            const F xt = X * t;
+            den[r] = fma(c1_of(j, r), xt * t, den[r]);
+        };
+        int j = j0;
+        if constexpr (F64 && KIND == 0) {
+            for (; j + 1 < j1; j += 2) {
+                const F *row = rows + (j - j0) * NROW * kWave;
+                const F Xa = row[0], ra = row[kWave], Xb = row[2 * kWave], rb = row[3 * kWave];
 #pragma unroll
-                for (int q = 0; q < P; ++q) {
-                    Xj[q] = (F)(Yat(j, q) * iw * xf[q]);
-                    // rho_j = W_j^(1/4) / sqrt(eta_j)
-                    rho[q] = wj * rsqrt_acc(horner<ORDER>(vj, u[q], order));
-                }
-                const F *c1 = c1b + (size_t)j * kKB;
-                const F *df = dfb + (size_t)j * kKB * order;
-#pragma unroll
-                for (int kk = 0; kk < KB; ++kk) {
-                    const F c = c1[kk];
-                    const bool self = diag && kb * KB + kk == j;
-#pragma unroll
-                    for (int q = 0; q < P; ++q) {
-                        // Wilke: X_j phi_kj = c1 X_j (1 + sigma_k rho_j)^2
-                        const F t = fma(sig[q][kk], rho[q], (F)1);
-                        const F xt = Xj[q] * t;
-                        den[q][kk] = fma(c, xt * t, den[q][kk]);
-                        // D_km: X_j / D_kj (j != k)
-                        const F f = horner<ORDER>(df + kk * order, u[q], order);
-                        const F x = self ? (F)0 : Xj[q];
-                        acc[q][kk] = fma(x, KIND == 0 ? rcp_fast(f) : f, acc[q][kk]);
-                    }
+                for (int r = 0; r < RW; ++r) {
+                    const int k = w * RW + r;
+                    if (RW > 4 && k >= ns) break;
+                    wilke(j, r, Xa, ra);
+                    wilke(j + 1, r, Xb, rb);
+                    // X_j / D_kj (j != k) of both
+                    const F fa = fit_of(j, r), fb = fit_of(j + 1, r);
+                    const F xa = k == j ? (F)0 : Xa, xb = k == j + 1 ? (F)0 : Xb;
+                    acc[r] = fma(fma(xa, fb, xb * fa), rcp_fast(fa * fb), acc[r]);
                 }
             }
-        };
-        const int jd0 = kb * KB, jd1 = min(jd0 + KB, ns);
-        steps(0, jd0, false);
-        steps(jd0, jd1, true);
-        steps(jd1, ns, false);
+        }
+        for (; j < j1; ++j) {
+            const F *row = rows + (j - j0) * NROW * kWave;
+            const F X = row[0], rho = row[kWave];
 #pragma unroll
-        for (int kk = 0; kk < KB; ++kk) {
-            const int k = kb * KB + kk;
-            if (k < ns) {
-                const double iw = m.sp[k].inv_W, Wk = m.W[k];
-                const F *ek_c = Tb::visc(m) + k * order;
-#pragma unroll
-                for (int q = 0; q < P; ++q) {
-                    const double Xk = Yat(k, q) * iw * xf[q];
-                    const F ek = horner<ORDER>(ek_c, u[q], order);
-                    visc[q] = fma((F)Xk * ek, rcp_acc(den[q][kk]), visc[q]);
-                    double D;
-                    if (acc[q][kk] == (F)0) {
-                        const F f = horner<ORDER>(Tb::ddiag(m) + k * order, u[q], order);
-                        D = (KIND == 0) ? (double)f / pr[q] : 1.0 / ((double)f * pr[q]);
-                    } else {
-                        // sum_{j!=k} X_j / D_kj = (p/p_atm) acc for either fit kind;
-                        // the numerator (W-bar - X_k W_k)/W-bar is formed in FP64
-                        D = (wbar[q] - Xk * Wk) / (wbar[q] * (double)acc[q][kk] * pr[q]);
-                    }
-                    if (act[q]) Dmix[(int64_t)k * n + idx[q]] = D;
-                }
+            for (int r = 0; r < RW; ++r) {
+                const int k = w * RW + r;
+                if (RW > 4 && k >= ns) break;
+                wilke(j, r, X, rho);
+                const F f = fit_of(j, r);
+                acc[r] = fma(k == j ? (F)0 : X, KIND == 0 ? rcp_fast(f) : f, acc[r]);
             }
         }
     }
+    __syncthreads();  // `part` and the chunk's rows are free
+    part[w * NPART * kWave] = wb;
+    if constexpr (F64) {
+        part[(w * 4 + 1) * kWave] = s1;
+        part[(w * 4 + 2) * kWave] = s2;
+    }
+    __syncthreads();
+    double wbar = 0.0;
+    for (int q = 0; q < nw; ++q) wbar += part[q * NPART * kWave];
+    double visc = 0.0;
 #pragma unroll
-    for (int q = 0; q < P; ++q)
-        if (act[q]) mu[idx[q]] = (double)visc[q];
+    for (int r = 0; r < RW; ++r) {
+        const int k = w * RW + r;
+        if (k < ns) {
+            const double Xk = Yat(k) * sp[k].inv_W * xf;
+            const F ek = horner_c<ORDER>(visc_t + k * order, u, order);
+            if constexpr (F64) {
+                visc = fma(Xk * ek, rcp_acc(den[r]), visc);
+            } else {
+                rows[2 * k * kWave] = (F)Xk * ek;
+                rows[(2 * k + 1) * kWave] = rcp_acc(den[r]);
+            }
+            double D;
+            if (acc[r] == (F)0) {
+                const F f = horner_c<ORDER>(const_table(Tb::ddiag(m)) + k * order, u, order);
+                D = (KIND == 0) ? (double)f / pr : 1.0 / ((double)f * pr);
+            } else {
+                // sum_{j!=k} X_j / D_kj = (p/p_atm) acc for either fit kind; the
+                // numerator (W-bar - X_k W_k)/W-bar is formed in FP64
+                D = (wbar - Xk * Wt[k]) * krcp(wbar * (double)acc[r] * pr);
+            }
+            if (act) Dmix[(int64_t)k * n + i] = D;
+        }
+    }
+    if (F64) part[(w * 4 + 3) * kWave] = visc;
+    __syncthreads();
+    if (w == 0 && act) {
+        if constexpr (F64) {
+            double a1 = 0.0, a2 = 0.0, v = 0.0;
+            for (int q = 0; q < nw; ++q) {
+                a1 += part[(q * 4 + 1) * kWave];
+                a2 += part[(q * 4 + 2) * kWave];
+                v += part[(q * 4 + 3) * kWave];
+            }
+            lam[i] = 0.5 * (a1 + rcp_acc(a2));
+            mu[i] = v;
+        } else {
+            lam[i] = (double)((F)0.5 * (s1 + rcp_acc(s2)));
+            F v = (F)0;
+            for (int k = 0; k < ns; ++k)
+                v = fma(rows[2 * k * kWave], rows[(2 * k + 1) * kWave], v);
+            mu[i] = (double)v;
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -742,52 +810,51 @@ __global__ __launch_bounds__(kBlock) void transport_mfma_items_kernel(
                                       it.T, it.p, it.Y, it.mu, it.lam, it.Dmix);
 }
 
-template <class F, int ORDER, int KIND, int P, int KB>
-__global__ __launch_bounds__(kBlock) void transport_kernel(MechDev m, int64_t n,
-                                                           const double *__restrict__ T,
-                                                           const double *__restrict__ Pp,
-                                                           const double *__restrict__ Y,
-                                                           double *__restrict__ mu,
-                                                           double *__restrict__ lam,
-                                                           double *__restrict__ Dmix)
+template <class F, int ORDER, int KIND, int RW>
+__global__ __launch_bounds__(1024) void transport_rows_kernel(MechDev m, int64_t n,
+                                                              const double *__restrict__ T,
+                                                              const double *__restrict__ Pp,
+                                                              const double *__restrict__ Y,
+                                                              double *__restrict__ mu,
+                                                              double *__restrict__ lam,
+                                                              double *__restrict__ Dmix)
 {
-    transport_tile<F, ORDER, KIND, P, KB>(m, n, (int64_t)blockIdx.x * kBlock * P, T, Pp, Y, mu,
-                                          lam, Dmix);
+    transport_rows_tile<F, ORDER, KIND, RW>(m, n, (int64_t)blockIdx.x * kWave, T, Pp, Y, mu, lam,
+                                            Dmix);
 }
 
-// Batched requests (see rates_batch_kernel): tiles of kBlock * P points.
-template <class F, int ORDER, int KIND, int P, int KB>
-__global__ __launch_bounds__(kBlock) void transport_batch_kernel(MechDev m,
-                                                                 const WorkList *__restrict__ wl,
-                                                                 int *__restrict__ counter)
+// Batched requests: persistent workgroups taking tiles from a counter.
+template <class F, int ORDER, int KIND, int RW>
+__global__ __launch_bounds__(1024) void transport_rows_batch_kernel(MechDev m,
+                                                                    const WorkList *__restrict__ wl,
+                                                                    int *__restrict__ counter)
 {
     __shared__ int tile;
     const int ntiles = wl->ntiles[1];
     int r = 0;  // item of the previous tile
     for (;;) {
+        __syncthreads();  // the previous tile's LDS reads are done
         if (threadIdx.x == 0) tile = atomicAdd(counter, 1);
         __syncthreads();
         const int t = __builtin_amdgcn_readfirstlane(tile);  // wave-uniform
-        __syncthreads();
         if (t >= ntiles) break;
         r = work_item_of(wl, 1, t, r);
         const WorkItem it = wl->items[r];
-        transport_tile<F, ORDER, KIND, P, KB>(m, it.n,
-                                              (int64_t)(t - wl->start[1][r]) * kBlock * P, it.T,
-                                              it.p, it.Y, it.mu, it.lam, it.Dmix);
+        transport_rows_tile<F, ORDER, KIND, RW>(m, it.n, (int64_t)(t - wl->start[1][r]) * kWave,
+                                                it.T, it.p, it.Y, it.mu, it.lam, it.Dmix);
     }
 }
 
-template <class F, int ORDER, int KIND, int P, int KB>
-__global__ __launch_bounds__(kBlock) void transport_items_kernel(MechDev m,
-                                                                 const WorkList *__restrict__ wl)
+template <class F, int ORDER, int KIND, int RW>
+__global__ __launch_bounds__(1024) void transport_rows_items_kernel(MechDev m,
+                                                                    const WorkList *__restrict__ wl)
 {
     const int t = (int)blockIdx.x;
     if (t >= wl->ntiles[1]) return;
     const int r = work_item_ballot(wl, 1, t);
     const WorkItem it = wl->items[r];
-    transport_tile<F, ORDER, KIND, P, KB>(m, it.n, (int64_t)(t - wl->start[1][r]) * kBlock * P,
-                                          it.T, it.p, it.Y, it.mu, it.lam, it.Dmix);
+    transport_rows_tile<F, ORDER, KIND, RW>(m, it.n, (int64_t)(t - wl->start[1][r]) * kWave, it.T,
+                                            it.p, it.Y, it.mu, it.lam, it.Dmix);
 }
 
 __global__ void zero_kernel(int *p, int count)
@@ -863,17 +930,55 @@ __global__ __launch_bounds__(kBlock) void thermo_kernel(MechDev m, int64_t n,
     }
 }
 
-// Points per lane and k-block size, measured on the 53-species workload:
-// FP64 is bound by the scalar-coefficient stream, so four points share each
-// fetched coefficient; the FP32 path carries half the registers per value and
-// prefers wider k-blocks.
-template <class F> struct TransportShape;
-template <> struct TransportShape<double> {
-    static constexpr int P = 4, KB = 4;
-};
-template <> struct TransportShape<float> {
-    static constexpr int P = 2, KB = 8;
-};
+// Species per wave of the vector-ALU kernel: the fewest that keep it within 16
+// waves (a wave with fewer species has a shorter chain and fewer registers; 9
+// species, 2^20 points: 117 us with 4 species a wave, 146 with 8, 159 with 16).
+int rows_per_wave(const MechDev &m) { return m.ns <= 64 ? 4 : (m.ns <= 128 ? 8 : 16); }
+int rows_waves(const MechDev &m) { return (m.ns + rows_per_wave(m) - 1) / rows_per_wave(m); }
+
+template <class F> size_t rows_lds(const MechDev &m) { return rows_lds_bytes<F>(m.ns, rows_waves(m)); }
+
+// FORM 0: direct launch, 1: work-stealing batch, 2: one tile per workgroup
+template <class F, int FORM, int KIND, int RW> const void *rows_instance(bool o5)
+{
+    if (FORM == 1)
+        return o5 ? (const void *)transport_rows_batch_kernel<F, 5, KIND, RW>
+                  : (const void *)transport_rows_batch_kernel<F, 0, KIND, RW>;
+    if (FORM == 2)
+        return o5 ? (const void *)transport_rows_items_kernel<F, 5, KIND, RW>
+                  : (const void *)transport_rows_items_kernel<F, 0, KIND, RW>;
+    return o5 ? (const void *)transport_rows_kernel<F, 5, KIND, RW>
+              : (const void *)transport_rows_kernel<F, 0, KIND, RW>;
+}
+
+// The kernel of a mechanism (fits of 1/D_kj come here below kMfmaMinSpecies only).
+template <class F, int FORM> const void *rows_kernel(const MechDev &m)
+{
+    const bool o5 = m.fit_order == 5;
+    const int rw = rows_per_wave(m);
+    if (m.diff_kind == 1) return rows_instance<F, FORM, 1, 4>(o5);
+    return rw == 4   ? rows_instance<F, FORM, 0, 4>(o5)
+           : rw == 8 ? rows_instance<F, FORM, 0, 8>(o5)
+                     : rows_instance<F, FORM, 0, 16>(o5);
+}
+
+template <class F, int FORM> kx_status rows_prepare(const MechDev &m)
+{
+    hipError_t e = hipFuncSetAttribute(rows_kernel<F, FORM>(m),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)rows_lds<F>(m));
+    if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute (transport)");
+    return KX_OK;
+}
+
+template <class F, int FORM>
+kx_status rows_launch(const MechDev &m, int64_t grid, void **args, hipStream_t s, const char *what)
+{
+    hipError_t e = hipLaunchKernel(rows_kernel<F, FORM>(m), dim3((unsigned)grid),
+                                   dim3(rows_waves(m) * kWave), args, rows_lds<F>(m), s);
+    if (e != hipSuccess) return hip_fail(e, what);
+    return ok();
+}
 
 // Points per matrix-core tile: the largest of 64, 32, 16 whose LDS (X and rho
 // tiles) stays within 80 KB, i.e. two workgroups per CU.
@@ -934,12 +1039,13 @@ template <class F, int FORM> kx_status mfma_prepare(const MechDev &m, size_t *ld
 int transport_tile_points(const MechDev &m, int precision)
 {
     if (use_mfma(m)) return precision == KX_MIXED ? mfma_np<float>(m) : mfma_np<double>(m);
-    return kBlock * (precision == KX_MIXED ? TransportShape<float>::P : TransportShape<double>::P);
+    return kWave;
 }
 
 kx_status prepare_transport_batch(const MechDev &m, int precision)
 {
-    if (!use_mfma(m)) return KX_OK;
+    if (!use_mfma(m))
+        return precision == KX_MIXED ? rows_prepare<float, 1>(m) : rows_prepare<double, 1>(m);
     size_t lds = 0;
     return precision == KX_MIXED ? mfma_prepare<float, 1>(m, &lds)
                                  : mfma_prepare<double, 1>(m, &lds);
@@ -983,19 +1089,13 @@ kx_status go_transport(const MechDev &m, int64_t n, const double *T, const doubl
         if (e != hipSuccess) return hip_fail(e, "transport kernel launch");
         return ok();
     }
-    constexpr int PP = TransportShape<F>::P, KB = TransportShape<F>::KB;
-    const int64_t per = (int64_t)kBlock * PP;
-    const int64_t nblk = (n + per - 1) / per;
+    const int64_t nblk = (n + kWave - 1) / kWave;
     if (nblk > 0x7fffffff) return fail(KX_EINVAL, "transport: n too large");
-    const bool o5 = m.fit_order == 5;
-    auto k = m.diff_kind == 0
-                 ? (o5 ? transport_kernel<F, 5, 0, PP, KB> : transport_kernel<F, 0, 0, PP, KB>)
-                 : (o5 ? transport_kernel<F, 5, 1, PP, KB> : transport_kernel<F, 0, 1, PP, KB>);
-    hipLaunchKernelGGL(k, dim3((unsigned)nblk), dim3(kBlock), 0, s, m, n, T, p, Y, mu, lam,
-                       Dmix);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e, "transport kernel launch");
-    return ok();
+    kx_status st = rows_prepare<F, 0>(m);
+    if (st != KX_OK) return st;
+    void *args[] = {(void *)&m, (void *)&n,  (void *)&T,   (void *)&p,
+                    (void *)&Y, (void *)&mu, (void *)&lam, (void *)&Dmix};
+    return rows_launch<F, 0>(m, nblk, args, s, "transport kernel launch");
 }
 
 template <class F>
@@ -1011,16 +1111,8 @@ kx_status go_transport_batch(const MechDev &m, const WorkList *wl, int *counter,
         if (e != hipSuccess) return hip_fail(e, "transport batch kernel launch");
         return ok();
     }
-    constexpr int PP = TransportShape<F>::P, KB = TransportShape<F>::KB;
-    const bool o5 = m.fit_order == 5;
-    auto k = m.diff_kind == 0 ? (o5 ? transport_batch_kernel<F, 5, 0, PP, KB>
-                                    : transport_batch_kernel<F, 0, 0, PP, KB>)
-                              : (o5 ? transport_batch_kernel<F, 5, 1, PP, KB>
-                                    : transport_batch_kernel<F, 0, 1, PP, KB>);
-    hipLaunchKernelGGL(k, dim3(grid), dim3(kBlock), 0, s, m, wl, counter);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e, "transport batch kernel launch");
-    return ok();
+    void *args[] = {(void *)&m, (void *)&wl, (void *)&counter};
+    return rows_launch<F, 1>(m, grid, args, s, "transport batch kernel launch");
 }
 template <class F>
 kx_status go_transport_items(const MechDev &m, const WorkList *wl, int64_t ntiles, hipStream_t s)
@@ -1038,16 +1130,10 @@ kx_status go_transport_items(const MechDev &m, const WorkList *wl, int64_t ntile
         if (e != hipSuccess) return hip_fail(e, "transport items kernel launch");
         return ok();
     }
-    constexpr int PP = TransportShape<F>::P, KB = TransportShape<F>::KB;
-    const bool o5 = m.fit_order == 5;
-    auto k = m.diff_kind == 0 ? (o5 ? transport_items_kernel<F, 5, 0, PP, KB>
-                                    : transport_items_kernel<F, 0, 0, PP, KB>)
-                              : (o5 ? transport_items_kernel<F, 5, 1, PP, KB>
-                                    : transport_items_kernel<F, 0, 1, PP, KB>);
-    hipLaunchKernelGGL(k, dim3((unsigned)ntiles), dim3(kBlock), 0, s, m, wl);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e, "transport items kernel launch");
-    return ok();
+    kx_status st = rows_prepare<F, 2>(m);
+    if (st != KX_OK) return st;
+    void *args[] = {(void *)&m, (void *)&wl};
+    return rows_launch<F, 2>(m, ntiles, args, s, "transport items kernel launch");
 }
 }  // namespace
 
