@@ -509,14 +509,14 @@ struct MfmaPoint {
     double u, xf, wbar, pr;
 };
 
-template <class F, int NP>
+template <class F, int NP, int NT>
 __host__ __device__ constexpr size_t mfma_lds_bytes_np(int kstep)
 {
     // X and rho tiles, point table, partial sums (per (group, point) in the
     // prologue: 3 sums, and the normalisation sum in a slot of its own; 16 per
     // point for mu)
     return 2 * (size_t)(4 * kstep) * (NP + kMfmaPad) * sizeof(F) + NP * sizeof(MfmaPoint) +
-           (size_t)4 * kBlock * sizeof(double);
+           (size_t)4 * NT * sizeof(double);
 }
 
 // `tid` is threadIdx.x; the batch kernel passes it through an opaque move in
@@ -524,7 +524,7 @@ __host__ __device__ constexpr size_t mfma_lds_bytes_np(int kstep)
 // not hoisted out of the loop (kept live across tiles they cost the kernel
 // its occupancy).  LOOP: the workgroup takes another tile after this one (its
 // LDS is then reused).
-template <class F, int NP, int ORDER, bool LOOP>
+template <class F, int NP, int NT, int ORDER, bool LOOP>
 __device__ __forceinline__ void transport_mfma_tile(int tid, const MechDev &m, int64_t n,
                                                     int64_t base,
                                                     const double *__restrict__ T,
@@ -537,8 +537,11 @@ __device__ __forceinline__ void transport_mfma_tile(int tid, const MechDev &m, i
     using Tb = Tabs<F>;
     using MF = Mfma<F>;
     using V = typename MF::V;
-    constexpr int NB = NP / 16;          // 16-point column blocks
-    constexpr int NG = kBlock / NP;      // species groups of the prologue
+    constexpr int NW = NT / kWave;       // waves
+    constexpr int NBT = NP / 16;         // 16-point column blocks of the tile
+    // a wave takes NB of them, WC waves side by side share a row block
+    constexpr int WC = NT == 512 && NP == 64 ? 2 : 1, NB = NBT / WC, WR = NW / WC;
+    constexpr int NG = NT / NP;          // species groups of the prologue
     constexpr int LD = NP + kMfmaPad;    // LDS row stride of the tiles
     const int ns = m.ns, order = ORDER > 0 ? ORDER : m.fit_order;
     const int KS = m.kstep, MB = m.mblk, Kp = 4 * KS;
@@ -549,7 +552,7 @@ __device__ __forceinline__ void transport_mfma_tile(int tid, const MechDev &m, i
     F *Rs = Xs + (size_t)Kp * LD;
     MfmaPoint *pt = reinterpret_cast<MfmaPoint *>(Rs + (size_t)Kp * LD);
     double *part = reinterpret_cast<double *>(pt + NP);  // [NG][3][NP], then mu's [16][NP]
-    double *part1 = part + 3 * kBlock;                   // [NG][NP]: sum of Y_j / W_j
+    double *part1 = part + 3 * NT;                   // [NG][NP]: sum of Y_j / W_j
 
     // ---- prologue: thread = (point p, species group g)
     const int p = t % NP;
@@ -560,8 +563,8 @@ __device__ __forceinline__ void transport_mfma_tile(int tid, const MechDev &m, i
     const double Tp = T[ip];
     const double up = (kln(Tp) - m.fit_L0) * m.inv_fit_h;
     // every Y load of this thread is issued before the first is used (a
-    // thread covers at most kJmax species: ns <= 4 NP for the chosen NP)
-    constexpr int kJmax = 16;
+    // thread covers at most kJmax species: ns <= kJmax NG for the chosen tile)
+    constexpr int kJmax = NT == 512 && NP == 64 ? 8 : 16;
     double yw[kJmax];
 #pragma unroll
     for (int q = 0; q < kJmax; ++q) {
@@ -626,8 +629,10 @@ __device__ __forceinline__ void transport_mfma_tile(int tid, const MechDev &m, i
         lam[base + p] = 0.5 * (a1 + krcp(a2));  // Mathur
     }
 
-    // ---- products on the matrix cores: wave w takes row blocks w, w + 4, ...
-    const int col = lane & 15, jr = lane >> 4;
+    // ---- products on the matrix cores: wave w takes row blocks wr, wr + WR, ...
+    // and the points from c0
+    const int wr = w / WC, c0 = (w % WC) * 16 * NB;
+    const int col = c0 + (lane & 15), jr = lane >> 4;
     F uc[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) uc[nb] = (F)pt[16 * nb + col].u;
@@ -637,7 +642,7 @@ __device__ __forceinline__ void transport_mfma_tile(int tid, const MechDev &m, i
     const F *gf = MF::gfrag(m), *cf = MF::c1frag(m);
     constexpr int MO = ORDER > 0 ? ORDER : kMaxFitOrder;  // A fragments per K-step
     const size_t ostride = (size_t)MB * KS * 64;           // between fit orders
-    for (int mb = w; mb < MB; mb += 4) {
+    for (int mb = wr; mb < MB; mb += WR) {
         V S[NB], A[NB], B[NB], C[NB];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) S[nb] = A[nb] = B[nb] = C[nb] = V{0, 0, 0, 0};
@@ -742,22 +747,28 @@ __device__ __forceinline__ void transport_mfma_tile(int tid, const MechDev &m, i
             }
         }
     }
-    // mu: 16 partial sums per point (4 waves x 4 row groups), fixed order
+    // mu: 4 WR partial sums per point (waves x 4 row groups), fixed order
     __syncthreads();
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) part[(w * 4 + jr) * NP + 16 * nb + col] = mup[nb];
+    for (int nb = 0; nb < NB; ++nb) part[(wr * 4 + jr) * NP + 16 * nb + col] = mup[nb];
     __syncthreads();
     if (t < NP && base + t < n) {
         double v = 0.0;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) v += part[q * NP + t];
+        for (int q = 0; q < 4 * WR; ++q) v += part[q * NP + t];
         mu[base + t] = v;
     }
     if (LOOP) __syncthreads();  // LDS reused by the next tile
 }
 
-template <class F, int NP, int ORDER>
-__global__ __launch_bounds__(kBlock) void transport_mfma_kernel(MechDev m, int64_t n,
+// Waves per SIMD: four for 512-thread workgroups of which two share a CU, else two.
+template <class F> constexpr int mfma_waves(int nt, int np)
+{
+    return nt == 512 && (np == 64 || sizeof(F) == 4) ? 4 : 2;
+}
+
+template <class F, int NP, int NT, int ORDER>
+__global__ __launch_bounds__(NT, mfma_waves<F>(NT, NP)) void transport_mfma_kernel(MechDev m, int64_t n,
                                                                 const double *__restrict__ T,
                                                                 const double *__restrict__ Pp,
                                                                 const double *__restrict__ Y,
@@ -765,14 +776,14 @@ __global__ __launch_bounds__(kBlock) void transport_mfma_kernel(MechDev m, int64
                                                                 double *__restrict__ lam,
                                                                 double *__restrict__ Dmix)
 {
-    transport_mfma_tile<F, NP, ORDER, false>(threadIdx.x, m, n, (int64_t)blockIdx.x * NP, T, Pp, Y, mu,
-                                      lam, Dmix);
+    transport_mfma_tile<F, NP, NT, ORDER, false>(threadIdx.x, m, n, (int64_t)blockIdx.x * NP, T, Pp,
+                                                 Y, mu, lam, Dmix);
 }
 
 // At most 256 VGPRs (two waves per SIMD): the FP64 form for fits of any order
 // would otherwise take 258 and run one wave per SIMD.
-template <class F, int NP, int ORDER>
-__global__ __launch_bounds__(kBlock, 2) void transport_mfma_batch_kernel(
+template <class F, int NP, int NT, int ORDER>
+__global__ __launch_bounds__(NT, mfma_waves<F>(NT, NP)) void transport_mfma_batch_kernel(
     MechDev m, const WorkList *__restrict__ wl, int *__restrict__ counter)
 {
     __shared__ int tile;
@@ -790,7 +801,7 @@ __global__ __launch_bounds__(kBlock, 2) void transport_mfma_batch_kernel(
         const WorkItem it = wl->items[r];
         int tid;
         asm volatile("v_mov_b32 %0, %1" : "=v"(tid) : "v"((int)threadIdx.x));
-        transport_mfma_tile<F, NP, ORDER, true>(tid, m, it.n, (int64_t)(t - wl->start[1][r]) * NP, it.T,
+        transport_mfma_tile<F, NP, NT, ORDER, true>(tid, m, it.n, (int64_t)(t - wl->start[1][r]) * NP, it.T,
                                           it.p, it.Y, it.mu, it.lam, it.Dmix);
     }
 }
@@ -798,15 +809,15 @@ __global__ __launch_bounds__(kBlock, 2) void transport_mfma_batch_kernel(
 // Batched requests, one tile per workgroup (grid = the batch's transport
 // tiles).  Uniform per workgroup, so a workgroup past the last tile returns
 // before any barrier.
-template <class F, int NP, int ORDER>
-__global__ __launch_bounds__(kBlock) void transport_mfma_items_kernel(
+template <class F, int NP, int NT, int ORDER>
+__global__ __launch_bounds__(NT, mfma_waves<F>(NT, NP)) void transport_mfma_items_kernel(
     MechDev m, const WorkList *__restrict__ wl)
 {
     const int t = (int)blockIdx.x;
     if (t >= wl->ntiles[1]) return;
     const int r = work_item_ballot(wl, 1, t);
     const WorkItem it = wl->items[r];
-    transport_mfma_tile<F, NP, ORDER, false>(threadIdx.x, m, it.n, (int64_t)(t - wl->start[1][r]) * NP,
+    transport_mfma_tile<F, NP, NT, ORDER, false>(threadIdx.x, m, it.n, (int64_t)(t - wl->start[1][r]) * NP,
                                       it.T, it.p, it.Y, it.mu, it.lam, it.Dmix);
 }
 
@@ -980,23 +991,54 @@ kx_status rows_launch(const MechDev &m, int64_t grid, void **args, hipStream_t s
     return ok();
 }
 
-// Points per matrix-core tile: the largest of 64, 32, 16 whose LDS (X and rho
-// tiles) stays within 80 KB, i.e. two workgroups per CU.
-// The prologue gives each thread at most 16 species (256 / NP groups), so NP
-// also bounds the species count: NP = 64 up to 64 species, 32 up to 128.
-template <class F> int mfma_np(const MechDev &m)
+// Shape of the matrix-core tile: points and threads.  The prologue gives each
+// thread at most 16 species (8 in a 64-point tile of 512 threads).
+//  * up to 64 species: 64 points; 512 threads below four row blocks (48 species),
+//    where four waves would leave one or two without a block (30 species, 500000
+//    points 0.38 -> 0.24 ms, mixed 0.22 -> 0.18); with four blocks four waves
+//    already keep the FP64 datapath busy that the products and the vector work
+//    share (53 species, 2^20 points: 1.22 ms with 256 threads, 1.24 with 512, mixed
+//    0.71 and 0.74);
+//  * up to 128: 32 points, 256 threads, two workgroups per CU;
+//  * above, mixed: 32 points, 512 threads, two workgroups per CU (200 species,
+//    100003 points 0.80 -> 0.75 ms against 16 points and 256 threads);
+//  * above, FP64: 16 points, 256 threads (32 points leave one workgroup per CU:
+//    1.68 against 1.58 ms).
+struct MfmaShape {
+    int np, nt;
+};
+template <class F> MfmaShape mfma_shape(const MechDev &m)
 {
     const int kp = 4 * m.kstep;
-    if (kp <= 64 && mfma_lds_bytes_np<F, 64>(m.kstep) <= 80 * 1024) return 64;
-    if (kp <= 128 && mfma_lds_bytes_np<F, 32>(m.kstep) <= 80 * 1024) return 32;
-    return 16;
+    if (kp <= 64) return {64, m.mblk < 4 ? 512 : 256};
+    if (kp <= 128) return {32, 256};
+    if (sizeof(F) == 4) return {32, 512};
+    return {16, 256};
+}
+template <class F> int mfma_np(const MechDev &m) { return mfma_shape<F>(m).np; }
+template <class F> int mfma_nt(const MechDev &m) { return mfma_shape<F>(m).nt; }
+
+// f(NP, NT) of the shape, as compile-time values.
+template <class F, class Fn> auto with_mfma_shape(const MechDev &m, Fn f)
+{
+    const MfmaShape s = mfma_shape<F>(m);
+    using std::integral_constant;
+    if (s.np == 64)
+        return s.nt == 512 ? f(integral_constant<int, 64>{}, integral_constant<int, 512>{})
+                           : f(integral_constant<int, 64>{}, integral_constant<int, 256>{});
+    if (s.np == 32 && s.nt == 256)
+        return f(integral_constant<int, 32>{}, integral_constant<int, 256>{});
+    if constexpr (sizeof(F) == 4)
+        return f(integral_constant<int, 32>{}, integral_constant<int, 512>{});
+    else
+        return f(integral_constant<int, 16>{}, integral_constant<int, 256>{});
 }
 
-template <class F> size_t mfma_lds(const MechDev &m, int np)
+template <class F> size_t mfma_lds(const MechDev &m)
 {
-    return np == 64 ? mfma_lds_bytes_np<F, 64>(m.kstep)
-                    : (np == 32 ? mfma_lds_bytes_np<F, 32>(m.kstep)
-                                : mfma_lds_bytes_np<F, 16>(m.kstep));
+    return with_mfma_shape<F>(m, [&](auto np, auto nt) {
+        return mfma_lds_bytes_np<F, decltype(np)::value, decltype(nt)::value>(m.kstep);
+    });
 }
 
 // Below about two dozen species the padded 16 x 4 MFMA tiles are mostly empty
@@ -1008,27 +1050,31 @@ bool use_mfma(const MechDev &m)
 }
 
 // FORM 0: direct launch, 1: work-stealing batch, 2: one tile per workgroup
-template <class F, int FORM> const void *mfma_kernel(const MechDev &m, int np)
+template <class F, int FORM, int NP, int NT> const void *mfma_instance(bool o5)
+{
+    if (FORM == 1)
+        return o5 ? (const void *)transport_mfma_batch_kernel<F, NP, NT, 5>
+                  : (const void *)transport_mfma_batch_kernel<F, NP, NT, 0>;
+    if (FORM == 2)
+        return o5 ? (const void *)transport_mfma_items_kernel<F, NP, NT, 5>
+                  : (const void *)transport_mfma_items_kernel<F, NP, NT, 0>;
+    return o5 ? (const void *)transport_mfma_kernel<F, NP, NT, 5>
+              : (const void *)transport_mfma_kernel<F, NP, NT, 0>;
+}
+template <class F, int FORM> const void *mfma_kernel(const MechDev &m)
 {
     const bool o5 = m.fit_order == 5;
-#define KX_PICK(NPV)                                                                        \
-    (FORM == 1 ? (o5 ? (const void *)transport_mfma_batch_kernel<F, NPV, 5>                 \
-                     : (const void *)transport_mfma_batch_kernel<F, NPV, 0>)                \
-     : FORM == 2 ? (o5 ? (const void *)transport_mfma_items_kernel<F, NPV, 5>               \
-                       : (const void *)transport_mfma_items_kernel<F, NPV, 0>)              \
-                 : (o5 ? (const void *)transport_mfma_kernel<F, NPV, 5>                     \
-                       : (const void *)transport_mfma_kernel<F, NPV, 0>))
-    return np == 64 ? KX_PICK(64) : (np == 32 ? KX_PICK(32) : KX_PICK(16));
-#undef KX_PICK
+    return with_mfma_shape<F>(m, [&](auto np, auto nt) {
+        return mfma_instance<F, FORM, decltype(np)::value, decltype(nt)::value>(o5);
+    });
 }
 
 template <class F, int FORM> kx_status mfma_prepare(const MechDev &m, size_t *lds)
 {
-    const int np = mfma_np<F>(m);
-    *lds = mfma_lds<F>(m, np);
+    *lds = mfma_lds<F>(m);
     if (*lds > 160 * 1024)
         return fail(KX_EUNSUPPORTED, "transport: mechanism too large for the LDS tiles");
-    hipError_t e = hipFuncSetAttribute(mfma_kernel<F, FORM>(m, np),
+    hipError_t e = hipFuncSetAttribute(mfma_kernel<F, FORM>(m),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)*lds);
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute (transport)");
     return KX_OK;
@@ -1084,8 +1130,8 @@ kx_status go_transport(const MechDev &m, int64_t n, const double *T, const doubl
         if (nblk > 0x7fffffff) return fail(KX_EINVAL, "transport: n too large");
         void *args[] = {(void *)&m, (void *)&n, (void *)&T, (void *)&p, (void *)&Y,
                         (void *)&mu, (void *)&lam, (void *)&Dmix};
-        hipError_t e = hipLaunchKernel(mfma_kernel<F, 0>(m, np), dim3((unsigned)nblk),
-                                       dim3(kBlock), args, lds, s);
+        hipError_t e = hipLaunchKernel(mfma_kernel<F, 0>(m), dim3((unsigned)nblk),
+                                       dim3(mfma_nt<F>(m)), args, lds, s);
         if (e != hipSuccess) return hip_fail(e, "transport kernel launch");
         return ok();
     }
@@ -1103,10 +1149,9 @@ kx_status go_transport_batch(const MechDev &m, const WorkList *wl, int *counter,
                              hipStream_t s)
 {
     if (use_mfma(m)) {
-        const int np = mfma_np<F>(m);
-        const size_t lds = mfma_lds<F>(m, np);
+        const size_t lds = mfma_lds<F>(m);
         void *args[] = {(void *)&m, (void *)&wl, (void *)&counter};
-        hipError_t e = hipLaunchKernel(mfma_kernel<F, 1>(m, np), dim3(grid), dim3(kBlock),
+        hipError_t e = hipLaunchKernel(mfma_kernel<F, 1>(m), dim3(grid), dim3(mfma_nt<F>(m)),
                                        args, lds, s);
         if (e != hipSuccess) return hip_fail(e, "transport batch kernel launch");
         return ok();
@@ -1123,10 +1168,9 @@ kx_status go_transport_items(const MechDev &m, const WorkList *wl, int64_t ntile
         size_t lds = 0;
         kx_status st = mfma_prepare<F, 2>(m, &lds);
         if (st != KX_OK) return st;
-        const int np = mfma_np<F>(m);
         void *args[] = {(void *)&m, (void *)&wl};
-        hipError_t e = hipLaunchKernel(mfma_kernel<F, 2>(m, np), dim3((unsigned)ntiles),
-                                       dim3(kBlock), args, lds, s);
+        hipError_t e = hipLaunchKernel(mfma_kernel<F, 2>(m), dim3((unsigned)ntiles),
+                                       dim3(mfma_nt<F>(m)), args, lds, s);
         if (e != hipSuccess) return hip_fail(e, "transport items kernel launch");
         return ok();
     }

@@ -37,3 +37,24 @@ def test_shapes_against_the_oracle(ns, kind, order, n):
         for g, r in zip(out, ref):
             assert PM.rel_report(g.cpu().numpy(), r, tol)["ok"], (prec, PM.rel_report(g.cpu().numpy(), r, tol))
     dm.close()
+
+
+@pytest.mark.parametrize("ns,order,n", [(24, 5, 65), (33, 4, 64), (48, 5, 63), (49, 5, 1),
+                                        (129, 5, 33), (200, 4, 17)])
+def test_matrix_core_shapes_against_the_oracle(ns, order, n):
+    """The matrix-core kernel at the edges of its tile shapes (512 threads below
+    four row blocks; above 128 species 16 points in FP64, 32 in the mixed path)."""
+    from paper_2411_02640_amd import kx
+    print("[gpu-case] transport mfma", ns, order, n, flush=True)
+    mech = I.make_mechanism(I.MechSpec(ns, 5 * ns, ns // 2, 0, 2, seed=9000 + ns, fit_order=order))
+    T, p, Y = I.make_states(ns, I.StateSpec(n, seed=82, p_atm_range=(1.0, 40.0), dirichlet_alpha=0.3))
+    Y[:, 0] = 0.0
+    Y[ns - 1, 0] = 1.0
+    ref = O.OracleMech(mech).transport(T, p, Y)
+    dm = kx.Mechanism(mech, 0)
+    d = [torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0") for a in (T, p, Y)]
+    for prec, tol in (("fp64", PM.REL_FP64), ("mixed", PM.REL_MIXED)):
+        for g, r in zip(kx.transport(dm, *d, precision=prec), ref):
+            rep = PM.rel_report(g.cpu().numpy(), r, tol)
+            assert rep["ok"], (prec, rep)
+    dm.close()
