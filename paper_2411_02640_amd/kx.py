@@ -174,15 +174,16 @@ class Mechanism:
 def _stream_ptr(stream, device):
     if stream is None:
         stream = torch.cuda.current_stream(device)
-    return C.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
 def _dev_tensor(t, device, shape, name):
-    if not isinstance(t, torch.Tensor) or t.device.type != "cuda" or t.device.index != device:
+    # one attribute or method per property: these checks run up to ten times a call
+    if not isinstance(t, torch.Tensor) or not t.is_cuda or t.get_device() != device:
         raise ValueError(f"{name} must be a torch tensor on cuda:{device}")
-    if t.dtype != torch.float64 or not t.is_contiguous() or tuple(t.shape) != tuple(shape):
+    if t.dtype is not torch.float64 or t.shape != shape or not t.is_contiguous():
         raise ValueError(f"{name} must be a contiguous float64 tensor of shape {shape}")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def production_rates(mech: Mechanism, T, p, Y, out=None, precision: str = "fp64",
@@ -194,8 +195,10 @@ def production_rates(mech: Mechanism, T, p, Y, out=None, precision: str = "fp64"
     args = [_dev_tensor(T, dev, (n,), "T"), _dev_tensor(p, dev, (n,), "p"),
             _dev_tensor(Y, dev, (ns, n), "Y")]
     if out is None:
-        out = torch.empty((ns, n), dtype=torch.float64, device=f"cuda:{dev}")
-    w = _dev_tensor(out, dev, (ns, n), "out")
+        out = torch.empty((ns, n), dtype=torch.float64, device=T.device)
+        w = out.data_ptr()
+    else:
+        w = _dev_tensor(out, dev, (ns, n), "out")
     check(lib().kx_production_rates_ex(mech.handle, n, *args, w, PRECISION[precision],
                                        _stream_ptr(stream, dev)))
     return out
@@ -215,11 +218,13 @@ def transport(mech: Mechanism, T, p, Y, out=None, precision: str = "fp64", strea
     args = [_dev_tensor(T, dev, (n,), "T"), _dev_tensor(p, dev, (n,), "p"),
             _dev_tensor(Y, dev, (ns, n), "Y")]
     if out is None:
-        kw = dict(dtype=torch.float64, device=f"cuda:{dev}")
+        kw = dict(dtype=torch.float64, device=T.device)
         out = (torch.empty(n, **kw), torch.empty(n, **kw), torch.empty((ns, n), **kw))
-    mu, lam, Dm = out
-    ptrs = [_dev_tensor(mu, dev, (n,), "mu"), _dev_tensor(lam, dev, (n,), "lambda"),
-            _dev_tensor(Dm, dev, (ns, n), "Dmix")]
+        ptrs = [t.data_ptr() for t in out]
+    else:
+        mu, lam, Dm = out
+        ptrs = [_dev_tensor(mu, dev, (n,), "mu"), _dev_tensor(lam, dev, (n,), "lambda"),
+                _dev_tensor(Dm, dev, (ns, n), "Dmix")]
     flag = PRECISION[precision] | (KX_DKJ_SYMMETRIC if symmetric else 0)
     check(lib().kx_transport_ex(mech.handle, n, *args, *ptrs, flag, _stream_ptr(stream, dev)))
     return out
@@ -233,8 +238,8 @@ def thermo(mech: Mechanism, T, Y, stream=None):
     kw = dict(dtype=torch.float64, device=f"cuda:{dev}")
     cpk, hk, cp = torch.empty((ns, n), **kw), torch.empty((ns, n), **kw), torch.empty(n, **kw)
     check(lib().kx_thermo(mech.handle, n, _dev_tensor(T, dev, (n,), "T"),
-                          _dev_tensor(Y, dev, (ns, n), "Y"), C.c_void_p(cpk.data_ptr()),
-                          C.c_void_p(hk.data_ptr()), C.c_void_p(cp.data_ptr()),
+                          _dev_tensor(Y, dev, (ns, n), "Y"), cpk.data_ptr(),
+                          hk.data_ptr(), cp.data_ptr(),
                           _stream_ptr(stream, dev)))
     return cpk, hk, cp
 
@@ -247,8 +252,10 @@ def jacobian(mech: Mechanism, T, p, Y, out=None, stream=None):
     args = [_dev_tensor(T, dev, (n,), "T"), _dev_tensor(p, dev, (n,), "p"),
             _dev_tensor(Y, dev, (ns, n), "Y")]
     if out is None:
-        out = torch.empty((n, ns, ns), dtype=torch.float64, device=f"cuda:{dev}")
-    j = _dev_tensor(out, dev, (n, ns, ns), "out")
+        out = torch.empty((n, ns, ns), dtype=torch.float64, device=T.device)
+        j = out.data_ptr()
+    else:
+        j = _dev_tensor(out, dev, (n, ns, ns), "out")
     check(lib().kx_jacobian(mech.handle, n, *args, j, _stream_ptr(stream, dev)))
     return out
 
@@ -332,7 +339,7 @@ def batch_noalloc(mech: Mechanism, items, transport: bool = False, precision: st
             mu = lam = Dm = None
             if transport:
                 mu, lam, Dm = torch.empty(n, **kw), torch.empty(n, **kw), torch.empty((ns, n), **kw)
-        ptr = lambda t, shape, name: _dev_tensor(t, mech.device, shape, name).value
+        ptr = lambda t, shape, name: _dev_tensor(t, mech.device, shape, name)
         arr[r].n = n
         arr[r].T = ptr(T, (n,), "T")
         arr[r].p = ptr(p, (n,), "p")
@@ -440,9 +447,9 @@ class Server:
         r.precision = PRECISION[precision]
         if T is not None:
             n = T.shape[0]
-            r.T = _dev_tensor(T, self.device, (n,), "T").value
-            r.p = _dev_tensor(p, self.device, (n,), "p").value
-            r.Y = _dev_tensor(Y, self.device, (mech.n_species, n), "Y").value
+            r.T = _dev_tensor(T, self.device, (n,), "T")
+            r.p = _dev_tensor(p, self.device, (n,), "p")
+            r.Y = _dev_tensor(Y, self.device, (mech.n_species, n), "Y")
         r.n = int(n)
         r.arrival_s = -1.0 if arrival is None else float(arrival)
         r.inputs_ready = inputs_ready.cuda_event if inputs_ready is not None else None
