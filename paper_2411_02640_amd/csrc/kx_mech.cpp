@@ -61,7 +61,7 @@ struct WideShape {
 WideShape wide_shape(int ns, int nr)
 {
     WideShape s;
-    if (ns > kWideMaxSpecies || nr == 0) return s;
+    if (ns > kWideMaxSpecies) return s;
     s.nw = ns <= 16 ? 4 : (ns <= 32 ? 8 : (ns <= 56 ? 12 : 16));
     const int need = std::min(24, nr);
     int groups = (s.nw == 16 ? 16 : 24) / s.nw, rows = 0;
@@ -82,7 +82,7 @@ WideShape wide_shape_alone(int ns, int nr)
     WideShape s;
     s.nw = 16;
     const int rows = (160 * 1024 - 256) / 512 - (2 * (ns + 2) + 1);
-    s.chunk = std::min({rows, kChunkMax, nr + s.nw - 1}) / s.nw * s.nw;
+    s.chunk = std::max(s.nw, std::min({rows, kChunkMax, nr + s.nw - 1}) / s.nw * s.nw);
     s.nchunks = (nr + s.chunk - 1) / s.chunk;
     return s;
 }
@@ -98,35 +98,59 @@ int net_nu(const kx_mech_desc *d, int i, int k)
     return nu;
 }
 
-// The species of each wave of a shape and the waves' gather streams (WideMap).
-void wide_gather(const kx_mech_desc *d, const std::vector<int> &perm, const WideShape &ws,
-                 std::vector<int32_t> &species, std::vector<uint32_t> &start,
-                 std::vector<uint32_t> &gather)
+// (reaction in kernel order, net nu) of every species, one species after another:
+// those of species k are row[first[k]] .. row[first[k + 1]] (exclusive).
+struct SpeciesRows {
+    std::vector<std::pair<int, int>> row;
+    std::vector<int> first;
+};
+SpeciesRows species_rows(const kx_mech_desc *d, const std::vector<int> &perm)
 {
-    const int ns = d->n_species, nr = d->n_reactions, nw = ws.nw;
-    // (reaction in kernel order, net nu) of every species
-    std::vector<std::vector<std::pair<int, int>>> rows(ns);
+    const int ns = d->n_species, nr = d->n_reactions;
+    struct Item {
+        int k, s, nu;
+    };
+    std::vector<Item> items;
+    items.reserve((size_t)6 * nr);
+    SpeciesRows r;
+    r.first.assign(ns + 1, 0);
     for (int s = 0; s < nr; ++s) {
         const int i = perm[s];
+        const size_t own = items.size();
         for (int side = 0; side < 2; ++side) {
             const int32_t *ptr = side ? d->prod_ptr : d->reac_ptr;
             const int32_t *sp = side ? d->prod_sp : d->reac_sp;
             const int32_t *nu = side ? d->prod_nu : d->reac_nu;
             for (int e = ptr[i]; e < ptr[i + 1]; ++e) {
-                auto &r = rows[sp[e]];
                 const int v = side ? nu[e] : -nu[e];
-                if (!r.empty() && r.back().first == s)
-                    r.back().second += v;
-                else
-                    r.push_back({s, v});
+                size_t q = own;
+                while (q < items.size() && items[q].k != sp[e]) ++q;
+                if (q < items.size()) {
+                    items[q].nu += v;
+                } else {
+                    items.push_back({sp[e], s, v});
+                    ++r.first[sp[e] + 1];
+                }
             }
         }
     }
+    for (int k = 0; k < ns; ++k) r.first[k + 1] += r.first[k];
+    r.row.resize(items.size());
+    std::vector<int> at(r.first.begin(), r.first.end() - 1);
+    for (const Item &i : items) r.row[at[i.k]++] = {i.s, i.nu};
+    return r;
+}
+
+// The species of each wave of a shape and the waves' gather streams (WideMap).
+void wide_gather(const SpeciesRows &rows, const WideShape &ws, std::vector<int32_t> &species,
+                 std::vector<uint32_t> &start, std::vector<uint32_t> &gather)
+{
+    const int ns = (int)rows.first.size() - 1, nw = ws.nw;
     // longest list first, to the wave with the shortest total so far that has a
     // slot free (a list costs about four entries more than it holds)
     std::vector<int> len(ns, 0), order(ns), load(nw, 0), used(nw, 0);
     for (int k = 0; k < ns; ++k)
-        for (auto &e : rows[k]) len[k] += std::abs(e.second);
+        for (int e = rows.first[k]; e < rows.first[k + 1]; ++e) len[k] += std::abs(rows.row[e].second);
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return len[a] > len[b]; });
     species.assign((size_t)nw * 8, -1);
@@ -140,7 +164,9 @@ void wide_gather(const kx_mech_desc *d, const std::vector<int> &perm, const Wide
     }
     for (int w = 0; w < nw; ++w) {
         start.push_back((uint32_t)(gather.size() / 4));
-        std::vector<size_t> at(8, 0);  // next entry of each species' list
+        int at[8] = {};  // next entry of each species' list
+        for (int q = 0; q < 8; ++q)
+            if (species[w * 8 + q] >= 0) at[q] = rows.first[species[w * 8 + q]];
         for (int c = 0; c < ws.nchunks; ++c) {
             const size_t head = gather.size();
             gather.resize(head + 4, 0);
@@ -148,8 +174,9 @@ void wide_gather(const kx_mech_desc *d, const std::vector<int> &perm, const Wide
                 const int k = species[w * 8 + q];
                 if (k < 0) continue;
                 const size_t first = gather.size();
-                for (; at[q] < rows[k].size() && rows[k][at[q]].first < (c + 1) * ws.chunk; ++at[q]) {
-                    const auto &e = rows[k][at[q]];
+                for (; at[q] < rows.first[k + 1] && rows.row[at[q]].first < (c + 1) * ws.chunk;
+                     ++at[q]) {
+                    const auto &e = rows.row[at[q]];
                     for (int u = 0; u < std::abs(e.second); ++u)
                         gather.push_back((uint32_t)(e.first - c * ws.chunk) |
                                          (e.second < 0 ? 0x80000000u : 0u));
@@ -386,8 +413,15 @@ void jac_tables(const kx_mech_desc *d, const std::vector<int> &perm, const std::
     const int ns = d->n_species, nr = d->n_reactions;
     if (ns > kJacBlockSpecies || nr == 0 || d->qss) return;
     const int dense = ns;  // pseudo column
-    // contributions to (row, column): slot derivative and sign, |nu| times
-    std::vector<std::vector<uint16_t>> el((size_t)ns * (ns + 1));
+    // contributions to (row, column), |nu| times: slot derivative and sign
+    struct Item {
+        uint32_t el;
+        uint16_t val;
+    };
+    std::vector<Item> items;
+    items.reserve((size_t)32 * nr);
+    std::vector<uint32_t> first((size_t)ns * (ns + 1) + 1, 0);  // of an element's list
+    t.val.reserve(nr);
     std::vector<std::pair<int, int>> net;
     for (int s = 0; s < nr; ++s) {
         const DevRxn &r = rx[s];
@@ -411,9 +445,11 @@ void jac_tables(const kx_mech_desc *d, const std::vector<int> &perm, const std::
                 return;
             }
             for (auto &q : net)
-                for (int u = 0; u < std::abs(q.second); ++u)
-                    el[(size_t)q.first * (ns + 1) + column].push_back(
-                        (uint16_t)(t.nv | (q.second < 0 ? 0x8000 : 0)));
+                for (int u = 0; u < std::abs(q.second); ++u) {
+                    const uint32_t e = (uint32_t)(q.first * (ns + 1) + column);
+                    items.push_back({e, (uint16_t)(t.nv | (q.second < 0 ? 0x8000 : 0))});
+                    ++first[e + 1];
+                }
             ++t.nv;
         };
         const DevAux *ax = r.aux == 0xFFFF ? nullptr : &aux[r.aux];
@@ -451,36 +487,45 @@ void jac_tables(const kx_mech_desc *d, const std::vector<int> &perm, const std::
         t = JacTables();
         return;
     }
+    // the lists one after another
+    for (size_t e = 1; e < first.size(); ++e) first[e] += first[e - 1];
+    std::vector<uint16_t> el(items.size() + 1);
+    {
+        std::vector<uint32_t> at(first.begin(), first.end() - 1);
+        for (const Item &i : items) el[at[i.el]++] = i.val;
+    }
+    auto length = [&](int e) { return first[e + 1] - first[e]; };
     t.nblk = (ns + rows - 1) / rows;
     t.rows = (ns + t.nblk - 1) / t.nblk;
     t.ptr.push_back(0);
     std::vector<int> order;
+    std::vector<uint32_t> bucket;
     for (int b = 0; b < t.nblk; ++b) {
         // the elements of the block, longest list first, 64 to a lane block
         const int r0 = b * t.rows, r1 = std::min(ns, r0 + t.rows);
-        order.clear();
-        for (int k = r0; k < r1; ++k)
-            for (int j = 0; j <= ns; ++j) order.push_back(k * (ns + 1) + j);
-        std::stable_sort(order.begin(), order.end(),
-                         [&](int a, int c) { return el[a].size() > el[c].size(); });
+        const int e0 = r0 * (ns + 1), e1 = r1 * (ns + 1);
+        uint32_t longest = 0;
+        for (int e = e0; e < e1; ++e) longest = std::max(longest, length(e));
+        bucket.assign(longest + 2, 0);
+        for (int e = e0; e < e1; ++e) ++bucket[longest - length(e) + 1];
+        for (uint32_t l = 1; l <= longest; ++l) bucket[l] += bucket[l - 1];
+        order.resize(e1 - e0);
+        for (int e = e0; e < e1; ++e) order[bucket[longest - length(e)]++] = e;
         for (size_t o = 0; o < order.size(); o += 64) {
-            const size_t len = el[order[o]].size(), words = (len + 3) / 4, first = t.ent.size();
-            t.list.push_back(uint2{(uint32_t)(first / 64), (uint32_t)len});
-            t.ent.resize(first + 64 * words);
-            for (size_t l = 0; l < 64; ++l) {
-                const bool in = o + l < order.size();
-                const int k = in ? order[o + l] / (ns + 1) : 0, j = in ? order[o + l] % (ns + 1) : 0;
-                t.tgt.push_back(!in ? 0xFFFF
-                                    : (uint16_t)(j < ns ? (k - r0) * ns + j : t.rows * ns + k - r0));
-                for (size_t w = 0; w < words; ++w) {
-                    uint16_t e4[4];
-                    for (int u = 0; u < 4; ++u) {
-                        const size_t e = 4 * w + u;
-                        e4[u] = in && e < el[order[o + l]].size() ? el[order[o + l]][e]
-                                                                  : (uint16_t)t.nv;
-                    }
-                    t.ent[first + 64 * w + l] = uint2{(uint32_t)e4[0] | (uint32_t)e4[1] << 16,
-                                                      (uint32_t)e4[2] | (uint32_t)e4[3] << 16};
+            const size_t len = length(order[o]), words = (len + 3) / 4, at = t.ent.size();
+            t.list.push_back(uint2{(uint32_t)(at / 64), (uint32_t)len});
+            const uint32_t zero = (uint32_t)t.nv | (uint32_t)t.nv << 16;
+            t.ent.resize(at + 64 * words, uint2{zero, zero});
+            t.tgt.resize(t.tgt.size() + 64, 0xFFFF);
+            uint16_t *tgt = t.tgt.data() + t.tgt.size() - 64;
+            for (size_t l = 0; l < std::min<size_t>(64, order.size() - o); ++l) {
+                const int e = order[o + l], k = e / (ns + 1), j = e % (ns + 1);
+                tgt[l] = (uint16_t)(j < ns ? (k - r0) * ns + j : t.rows * ns + k - r0);
+                for (uint32_t u = 0; u < length(e); ++u) {
+                    uint2 &w = t.ent[at + 64 * (u / 4) + l];
+                    uint32_t &half = u & 2 ? w.y : w.x;
+                    const uint32_t v = el[first[e] + u];
+                    half = u & 1 ? (half & 0xFFFFu) | v << 16 : (half & 0xFFFF0000u) | v;
                 }
             }
         }
@@ -896,7 +941,8 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
         wsh[0] = wsh[1] = ws;
         wsh[1].nw = 16;
         wsh[2] = wide_shape_alone(ns, nr);
-        for (int v = 0; v < 3; ++v) wide_gather(d, perm, wsh[v], wmap[v], wstart[v], wgat[v]);
+        const SpeciesRows rows = species_rows(d, perm);
+        for (int v = 0; v < 3; ++v) wide_gather(rows, wsh[v], wmap[v], wstart[v], wgat[v]);
     }
     if (wrx.empty()) wrx.resize(1), wrx32.resize(1);
     if (waux.empty()) waux.resize(1);

@@ -406,8 +406,7 @@ struct PointConst {
 
 // LDS layout of one workgroup (one wave), PS = points per step:
 //   sq    rates of progress of the current chunk for the points of a step:
-//         PS = 2: [chunk + 1][2], the two points side by side;
-//         PS = 4: two such arrays kSqHalf bytes apart (points 0, 1 and 2, 3);
+//         [chunk + 1][2], the two points side by side;
 //         slot `chunk` is zero and absorbs the gather padding; at byte 0 so that
 //         the gather offsets are LDS addresses
 //   pairs [PS][ns + 1] {a, b} per point (entry ns is the dummy species, {1, 1})
@@ -417,10 +416,15 @@ struct PointConst {
 // species rows have stride ld, PS points per step:
 //   phase 1 -- lane = species, every point of the step;
 //   phase 2 -- lane = (reaction, point): lanes 2r and 2r+1 take reaction r, lane
-//              2r + j for the points j (and j + 2 when PS = 4) of the step, so a
-//              group of 32 falloff reactions fills a whole 64-lane iteration;
-//   phase 3 -- lane = species: one 16-byte LDS read per list entry (two when
-//              PS = 4) returns the rate of progress of the reaction at the points.
+//              2r + j for point j of the step, so a group of 32 falloff
+//              reactions fills a whole 64-lane iteration;
+//   phase 3 -- lane = species: one 16-byte LDS read per list entry returns the
+//              rate of progress of the reaction at both points.
+// Two other forms were measured against this one for 200 species (1500 reactions,
+// 100003 points, 1.13 ms): one lane per point as below with 40 points per tile (what
+// the LDS holds, so 24 lanes idle and four waves per SIMD) 1.27 ms, also with the
+// tables read ahead by vector loads (1.29); half a wave per species and reaction
+// with 32 points per tile 1.31 ms.
 // A 16-byte LDS read at a byte address (the gather lists hold addresses
 // relative to the dynamic LDS, which starts at 0 when the kernel has no static
 // LDS; rates_tile<..., true> is only entered after checking that).
@@ -440,8 +444,7 @@ __device__ __forceinline__ unsigned lds_base()
 // ---- phase 3: wdot_k = sum_i nu_ki R_i for the PS points of a step, one
 // chunk of reactions.  Lane = species (SPL per lane); a group is eight list
 // entries, summed plainly per point (the mixed path compensates the running
-// sum once per two groups).  All reads of a group (or of each half of it, for four
-// points) are issued before the first sum (left to itself the scheduler waits
+// sum once per two groups).  All reads of a group are issued before the first sum (left to itself the scheduler waits
 // for each read in turn), and two groups are handled per trip with
 // alternating offset registers (the next group's offsets in flight).
 //

@@ -14,7 +14,7 @@
 //     kx_rates.hip); species ns is the dummy of unused molecule slots
 //     (a = b = 1), species ns + 1 the products of irreversible reactions
 //     (a = 1, b = 0);
-//   rate rows, m.wchunk + 1: R of the current chunk's reactions and one row of
+//   rate rows, WideMap::chunk + 1: R of the current chunk's reactions and one row of
 //     zeros that absorbs the padding of the gather lists.
 #pragma once
 

@@ -74,3 +74,15 @@ def test_qss_kernels_agree(spec, n):
     assert bool(((c1 - C[:, :4096]).abs() <= 6e-7 * C[:, :4096].abs()).all())
     assert float(((c1 - C[:, :4096]).abs() / C[:, :4096].abs()).median()) <= 1e-12
     dm.close()
+
+
+@pytest.mark.parametrize("ns", [9, 53, 128])
+def test_no_reactions(ns):
+    """A mechanism without reactions: wdot is 0."""
+    from paper_2411_02640_amd import kx
+    print("[gpu-case] wide rates without reactions", ns, flush=True)
+    dm = kx.Mechanism(I.make_mechanism(I.MechSpec(ns, 0, 0, 0, 0, seed=1)), 0)
+    T, p, Y = I.make_states(ns, I.StateSpec(70, seed=77, p_atm_range=(1.0, 40.0), dirichlet_alpha=0.3))
+    for prec in ("fp64", "mixed"):
+        assert np.all(_run(kx, dm, T, p, Y, prec) == 0.0)
+    dm.close()
