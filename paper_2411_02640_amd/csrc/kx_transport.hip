@@ -138,11 +138,38 @@ __device__ __forceinline__ F horner_c(KX_CONST F *c, F u, int order)
 // (f1 f2)) and by the scalar stream of coefficients (48 bytes per pair and 64
 // points).  The form before it (one thread per four points, all k in turn) ran a
 // chain of ns^2 pairs per wave and recomputed X_j and rho_j per four species k:
-// KX_T_ROWS.
+// 53 species, 1000 points 803 -> 38 us, 300007 points 1240 -> 745 us.
 constexpr int kRowsChunk = 32;
 
+// Kind 0: a wave copies the coefficients of its species, kStage species j and four
+// species k at a time, from the tables into LDS of its own and reads them there
+// (one address per wave: a broadcast).  Through the scalar cache each pair's 48
+// bytes (24 mixed) were a load the wave waited for: 200 species, 2^20 points 56 -> 39
+// ms, mixed 39 -> 22; 53 species mixed 2.16 -> 1.89.  FP64 with four species per wave
+// keeps the scalar loads: there the stages' LDS leaves one workgroup per CU (53
+// species, 2^20 points: 2.41 ms scalar, 3.16 staged).  The form of one thread per
+// four points took 35, 21 and 1.58 ms at that size, but 13.0, 5.5 and 0.46 ms for
+// 1000 points, where this one takes 0.56, 0.33 and 0.03 (262144: 16.6 -> 9.9, 9.6 ->
+// 5.6, 0.65 -> 0.46).
+constexpr int kStage = 8;
+static_assert(kRowsChunk % kStage == 0 && kStage % 2 == 0, "whole stages of pairs");
+
+// Waves per SIMD: two workgroups of 14 waves (53 species) where the registers allow.
+template <class F> constexpr int rows_min_waves(int kind, int rw)
+{
+    return kind == 0 && rw == 4 && sizeof(F) == 4 ? 7 : 4;
+}
+template <class F> __host__ __device__ constexpr bool rows_staged(int kind, int rw)
+{
+    return kind == 0 && (rw > 4 || sizeof(F) == 4);
+}
+// elements of a wave's stage: the fits [j][kStageK][order], then the Wilke factors
+constexpr int kStageK = 4;
+static_assert(kKB % kStageK == 0, "a stage lies in one block of the tables");
+__host__ __device__ constexpr int stage_size(int order) { return kStage * kStageK * (order + 1); }
+
 template <class F>
-__host__ __device__ constexpr size_t rows_lds_bytes(int ns, int nw)
+__host__ __device__ constexpr size_t rows_lds_bytes(int ns, int nw)  // without the stages
 {
     // the waves' partial sums; X, rho (and for the mixed path lambda_j,
     // 1 / lambda_j) rows of a chunk, which later hold, with further rows, the
@@ -248,34 +275,120 @@ __device__ __forceinline__ void transport_rows_tile(const MechDev &m, int64_t n,
             const F xt = X * t;
             den[r] = fma(c1_of(j, r), xt * t, den[r]);
         };
-        int j = j0;
-        if constexpr (F64 && KIND == 0) {
-            for (; j + 1 < j1; j += 2) {
-                const F *row = rows + (j - j0) * NROW * kWave;
-                const F Xa = row[0], ra = row[kWave], Xb = row[2 * kWave], rb = row[3 * kWave];
+        if constexpr (rows_staged<F>(KIND, RW)) {
+            const int o = ORDER > 0 ? ORDER : order;
+            const int nfit = kStageK * o;  // coefficients of one j
+            F *stage = reinterpret_cast<F *>(reinterpret_cast<char *>(smem_d) +
+                                             rows_lds_bytes<F>(ns, nw)) +
+                       w * stage_size(o);
+            F *wstage = stage + kStage * nfit;
+            for (int js = j0; js < j1; js += kStage) {
+                const int nj = min(kStage, j1 - js);
 #pragma unroll
-                for (int r = 0; r < RW; ++r) {
-                    const int k = w * RW + r;
-                    if (RW > 4 && k >= ns) break;
-                    wilke(j, r, Xa, ra);
-                    wilke(j + 1, r, Xb, rb);
-                    // X_j / D_kj (j != k) of both
-                    const F fa = fit_of(j, r), fb = fit_of(j + 1, r);
-                    const F xa = k == j ? (F)0 : Xa, xb = k == j + 1 ? (F)0 : Xb;
-                    acc[r] = fma(fma(xa, fb, xb * fa), rcp_fast(fa * fb), acc[r]);
+                for (int b = 0; b < RW / kStageK; ++b) {
+                    const int k0 = w * RW + b * kStageK;
+                    if (RW > kStageK && k0 >= ns) break;
+                    // j and coefficient of element e: the tables hold kKB species per j
+                    const size_t at = ((size_t)(k0 / kKB) * ns + js) * kKB + k0 % kKB;
+                    const F *fsrc = Tb::dfit(m) + at * o;
+                    const F *wsrc = Tb::wilke(m) + at;
+                    auto src = [&](int e) { return e / nfit * kKB * o + e % nfit; };
+                    const F wv = lane < nj * kStageK
+                                     ? wsrc[lane / kStageK * kKB + lane % kStageK] : (F)0;
+                    if constexpr (ORDER > 0) {
+                        constexpr int NL = (kStage * kStageK * ORDER + kWave - 1) / kWave;
+                        F v[NL];
+#pragma unroll
+                        for (int e = 0; e < NL; ++e)
+                            v[e] = e * kWave + lane < nj * nfit ? fsrc[src(e * kWave + lane)] : (F)0;
+#pragma unroll
+                        for (int e = 0; e < NL; ++e)
+                            if (e * kWave + lane < kStage * nfit) stage[e * kWave + lane] = v[e];
+                    } else {
+                        for (int e = lane; e < nj * nfit; e += kWave) stage[e] = fsrc[src(e)];
+                    }
+                    if (lane < kStage * kStageK) wstage[lane] = wv;
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    auto staged_wilke = [&](int jj, int r, F X, F rho) {
+                        // X_j phi_kj = c1 X_j (1 + sigma_k rho_j)^2
+                        const F t = fma(sig[b * kStageK + r], rho, (F)1);
+                        const F xt = X * t;
+                        den[b * kStageK + r] = fma(wstage[jj * kStageK + r], xt * t, den[b * kStageK + r]);
+                    };
+                    auto staged_fit = [&](int jj, int r) {
+                        const F *c = stage + jj * nfit + r * o;
+                        F f = c[o - 1];
+#pragma unroll
+                        for (int q = ORDER - 2; q >= 0; --q) f = fma(f, u, c[q]);
+                        if (ORDER == 0)
+                            for (int q = o - 2; q >= 0; --q) f = fma(f, u, c[q]);
+                        return f;
+                    };
+                    int jj = 0;
+                    if constexpr (F64) {
+#pragma clang loop unroll(disable)
+                        for (; jj + 1 < nj; jj += 2) {
+                            const int j = js + jj;
+                            const F *row = rows + (j - j0) * NROW * kWave;
+                            const F Xa = row[0], ra = row[kWave];
+                            const F Xb = row[2 * kWave], rb = row[3 * kWave];
+#pragma unroll
+                            for (int r = 0; r < kStageK; ++r) {
+                                const int k = k0 + r, q = b * kStageK + r;
+                                staged_wilke(jj, r, Xa, ra);
+                                staged_wilke(jj + 1, r, Xb, rb);
+                                // X_j / D_kj (j != k) of both
+                                const F fa = staged_fit(jj, r), fb = staged_fit(jj + 1, r);
+                                const F xa = k == j ? (F)0 : Xa, xb = k == j + 1 ? (F)0 : Xb;
+                                acc[q] = fma(fma(xa, fb, xb * fa), rcp_fast(fa * fb), acc[q]);
+                            }
+                        }
+                    }
+#pragma clang loop unroll(disable)
+                    for (; jj < nj; ++jj) {
+                        const int j = js + jj;
+                        const F *row = rows + (j - j0) * NROW * kWave;
+                        const F X = row[0], rho = row[kWave];
+#pragma unroll
+                        for (int r = 0; r < kStageK; ++r) {
+                            const int k = k0 + r, q = b * kStageK + r;
+                            staged_wilke(jj, r, X, rho);
+                            acc[q] = fma(k == j ? (F)0 : X, rcp_fast(staged_fit(jj, r)), acc[q]);
+                        }
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();  // the stage is read
                 }
             }
-        }
-        for (; j < j1; ++j) {
-            const F *row = rows + (j - j0) * NROW * kWave;
-            const F X = row[0], rho = row[kWave];
+        } else {
+            int j = j0;
+            if constexpr (F64 && KIND == 0) {
+                for (; j + 1 < j1; j += 2) {
+                    const F *row = rows + (j - j0) * NROW * kWave;
+                    const F Xa = row[0], ra = row[kWave], Xb = row[2 * kWave], rb = row[3 * kWave];
 #pragma unroll
-            for (int r = 0; r < RW; ++r) {
-                const int k = w * RW + r;
-                if (RW > 4 && k >= ns) break;
-                wilke(j, r, X, rho);
-                const F f = fit_of(j, r);
-                acc[r] = fma(k == j ? (F)0 : X, KIND == 0 ? rcp_fast(f) : f, acc[r]);
+                    for (int r = 0; r < RW; ++r) {
+                        const int k = w * RW + r;
+                        wilke(j, r, Xa, ra);
+                        wilke(j + 1, r, Xb, rb);
+                        // X_j / D_kj (j != k) of both
+                        const F fa = fit_of(j, r), fb = fit_of(j + 1, r);
+                        const F xa = k == j ? (F)0 : Xa, xb = k == j + 1 ? (F)0 : Xb;
+                        acc[r] = fma(fma(xa, fb, xb * fa), rcp_fast(fa * fb), acc[r]);
+                    }
+                }
+            }
+            for (; j < j1; ++j) {
+                const F *row = rows + (j - j0) * NROW * kWave;
+                const F X = row[0], rho = row[kWave];
+#pragma unroll
+                for (int r = 0; r < RW; ++r) {
+                    wilke(j, r, X, rho);
+                    const F f = fit_of(j, r);
+                    acc[r] = fma(w * RW + r == j ? (F)0 : X, KIND == 0 ? rcp_fast(f) : f, acc[r]);
+                }
             }
         }
     }
@@ -822,7 +935,7 @@ __global__ __launch_bounds__(NT, mfma_waves<F>(NT, NP)) void transport_mfma_item
 }
 
 template <class F, int ORDER, int KIND, int RW>
-__global__ __launch_bounds__(1024) void transport_rows_kernel(MechDev m, int64_t n,
+__global__ __launch_bounds__(1024, rows_min_waves<F>(KIND, RW)) void transport_rows_kernel(MechDev m, int64_t n,
                                                               const double *__restrict__ T,
                                                               const double *__restrict__ Pp,
                                                               const double *__restrict__ Y,
@@ -836,7 +949,7 @@ __global__ __launch_bounds__(1024) void transport_rows_kernel(MechDev m, int64_t
 
 // Batched requests: persistent workgroups taking tiles from a counter.
 template <class F, int ORDER, int KIND, int RW>
-__global__ __launch_bounds__(1024) void transport_rows_batch_kernel(MechDev m,
+__global__ __launch_bounds__(1024, rows_min_waves<F>(KIND, RW)) void transport_rows_batch_kernel(MechDev m,
                                                                     const WorkList *__restrict__ wl,
                                                                     int *__restrict__ counter)
 {
@@ -857,7 +970,7 @@ __global__ __launch_bounds__(1024) void transport_rows_batch_kernel(MechDev m,
 }
 
 template <class F, int ORDER, int KIND, int RW>
-__global__ __launch_bounds__(1024) void transport_rows_items_kernel(MechDev m,
+__global__ __launch_bounds__(1024, rows_min_waves<F>(KIND, RW)) void transport_rows_items_kernel(MechDev m,
                                                                     const WorkList *__restrict__ wl)
 {
     const int t = (int)blockIdx.x;
@@ -947,7 +1060,12 @@ __global__ __launch_bounds__(kBlock) void thermo_kernel(MechDev m, int64_t n,
 int rows_per_wave(const MechDev &m) { return m.ns <= 64 ? 4 : (m.ns <= 128 ? 8 : 16); }
 int rows_waves(const MechDev &m) { return (m.ns + rows_per_wave(m) - 1) / rows_per_wave(m); }
 
-template <class F> size_t rows_lds(const MechDev &m) { return rows_lds_bytes<F>(m.ns, rows_waves(m)); }
+template <class F> size_t rows_lds(const MechDev &m)
+{
+    const int nw = rows_waves(m);
+    const size_t stages = rows_staged<F>(m.diff_kind, rows_per_wave(m)) ? nw * stage_size(m.fit_order) * sizeof(F) : 0;
+    return rows_lds_bytes<F>(m.ns, nw) + stages;
+}
 
 // FORM 0: direct launch, 1: work-stealing batch, 2: one tile per workgroup
 template <class F, int FORM, int KIND, int RW> const void *rows_instance(bool o5)
