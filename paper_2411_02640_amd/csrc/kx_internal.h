@@ -134,6 +134,13 @@ static_assert(sizeof(DevSpecies) == 256, "DevSpecies layout");
 // one (k-block, j) step are contiguous for scalar loads.
 constexpr int kKB = 8;
 
+// Entries of the lists of the one-point-per-workgroup kernels (kx_few.h).
+enum : uint32_t {
+    kFewIndex = 0x3FFFFFFFu,
+    kFewLast = 0x40000000u,   // ends a group of the one-lane-per-point kernels' streams
+    kFewMinus = 0x80000000u,
+};
+
 // Shape of a one-lane-per-point workgroup and how its waves divide the species.
 struct WideMap {
     int32_t chunk, nchunks;  // reactions per chunk (rate rows in LDS), chunks
@@ -184,6 +191,11 @@ struct MechDev {
     // the same chunks (so that the mixed path's compensated groups stay the same);
     // 2: 16 waves, as many rate rows as the LDS holds
     WideMap wmaps[3];
+    // One point per workgroup (kx_few.h): a species' list of rates, words of four
+    // entries (reaction in kernel order, listed |nu| times, and kFew* bits; padding
+    // entries name the zero slot nr)
+    const int32_t *fptr;       // [ns + 1] first word of a species' list
+    const uint4 *fent;
     // Jacobian in row blocks (kx_jacobian.hip); jrows = 0: not laid out (more than
     // 128 species, QSS species, or more slot derivatives than the LDS holds)
     int32_t jnv;               // slot derivatives of all reactions (a zero follows them)
@@ -236,6 +248,12 @@ struct MechDev {
     const int32_t *qlist;      // [wnqr] kernel order
     const uint32_t *qstart;    // [nq], qgather: the streams of a balance row (WideMap), its
     const uint4 *qgather;      // accumulators the columns of [A | b]
+    // The same for one point per workgroup: the entries of [A | b] as lists over
+    // the forward (2 r) and reverse (2 r + 1) terms of the wnqr reactions
+    const int32_t *qfptr;      // [nq * (nq + 1) + 1]
+    const uint4 *qfent;
+    const int32_t *qinfo;      // [nr] kernel order: index in qlist, -1: no QSS species,
+                               // -2: one on both sides (not in the balances)
 };
 
 // Tables read through the constant address space: scalar loads also where the

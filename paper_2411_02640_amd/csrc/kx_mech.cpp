@@ -188,6 +188,35 @@ void wide_gather(const SpeciesRows &rows, const WideShape &ws, std::vector<int32
     }
 }
 
+// The species' lists of the one-point-per-workgroup kernels; an entry is the last
+// of its group where the streams of wide_gather end one: after four entries of a
+// chunk, or at the chunk's end.
+void few_lists(const SpeciesRows &rows, int nr, int chunk, std::vector<int32_t> &ptr,
+               std::vector<uint32_t> &ent)
+{
+    const int ns = (int)rows.first.size() - 1;
+    for (int k = 0; k < ns; ++k) {
+        ptr.push_back((int32_t)(ent.size() / 4));
+        int group = 0;  // entries of the current group
+        for (int e = rows.first[k]; e < rows.first[k + 1]; ++e) {
+            const int s = rows.row[e].first, nu = rows.row[e].second;
+            for (int u = 0; u < std::abs(nu); ++u) {
+                ent.push_back((uint32_t)s | (nu < 0 ? kFewMinus : 0u));
+                if (++group == 4) {
+                    ent.back() |= kFewLast;
+                    group = 0;
+                }
+            }
+            if (group && (e + 1 == rows.first[k + 1] || rows.row[e + 1].first / chunk != s / chunk)) {
+                ent.back() |= kFewLast;
+                group = 0;
+            }
+        }
+        while (ent.size() % 4) ent.push_back((uint32_t)nr);
+    }
+    ptr.push_back((int32_t)(ent.size() / 4));
+}
+
 // QSS species of one side of reaction i (the first one) and their molecule count.
 int qss_side(const kx_mech_desc *d, int i, bool prod, int *count)
 {
@@ -785,7 +814,8 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
     // them, and per balance row the streams of its columns (rate rows 2 r and
     // 2 r + 1 hold the forward and reverse terms of reaction r of a chunk)
     std::vector<int32_t> qsp, qlist;
-    std::vector<uint32_t> qstart, qgather;
+    std::vector<uint32_t> qstart, qgather, qfent;
+    std::vector<int32_t> qfptr, qinfo;
     int qchunk = 0;
     {
         const WideShape q = wide_shape(ns, nr);
@@ -824,6 +854,26 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
                     }
                 }
             }
+            // one point per workgroup: the same entries, a list per (row, column)
+            qinfo.assign(nr, -1);
+            for (int s = 0; s < nr; ++s)
+                if (qrx[s].x >= 0 || qrx[s].y >= 0) qinfo[s] = seen[s] < 0 ? -2 : seen[s];
+            for (int j = 0; j < nq; ++j)
+                for (int col = 0; col <= nq; ++col) {
+                    qfptr.push_back((int32_t)(qfent.size() / 4));
+                    for (int r = 0; r < nqr; ++r) {
+                        const int s = qlist[r], nu = net_nu(d, perm[s], qsp[j]);
+                        for (int side = 0; nu != 0 && side < 2; ++side) {
+                            const int at = side ? qrx[s].y : qrx[s].x;
+                            if ((at >= 0 ? at : nq) != col) continue;
+                            for (int u = 0; u < std::abs(nu); ++u)
+                                qfent.push_back((uint32_t)(2 * r + side) |
+                                                ((nu < 0) != (side == 1) ? kFewMinus : 0u));
+                        }
+                    }
+                    while (qfent.size() % 4) qfent.push_back((uint32_t)(2 * nqr));
+                }
+            qfptr.push_back((int32_t)(qfent.size() / 4));
         }
     }
 
@@ -869,6 +919,8 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
     WideShape wsh[3];
     std::vector<int32_t> wmap[3];
     std::vector<uint32_t> wstart[3], wgat[3];
+    std::vector<int32_t> fptr;
+    std::vector<uint32_t> fent;
     int nplog = 0;
     if (ws.nw > 0) {
         for (int s = 0; s < nr; ++s) {
@@ -943,6 +995,7 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
         wsh[2] = wide_shape_alone(ns, nr);
         const SpeciesRows rows = species_rows(d, perm);
         for (int v = 0; v < 3; ++v) wide_gather(rows, wsh[v], wmap[v], wstart[v], wgat[v]);
+        few_lists(rows, nr, ws.chunk, fptr, fent);
     }
     if (wrx.empty()) wrx.resize(1), wrx32.resize(1);
     if (waux.empty()) waux.resize(1);
@@ -1022,6 +1075,9 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
     const size_t o_jval = add_vec(b, jt.val), o_jptr = add_vec(b, jt.ptr);
     const size_t o_jlist = add_vec(b, jt.list), o_jent = add_vec(b, jt.ent);
     const size_t o_jtgt = add_vec(b, jt.tgt);
+    const size_t o_fptr = add_vec(b, fptr), o_fent = add_vec(b, fent);
+    const size_t o_qfptr = add_vec(b, qfptr), o_qfent = add_vec(b, qfent);
+    const size_t o_qinfo = add_vec(b, qinfo);
     size_t o_wmap[3], o_wstart[3], o_wgat[3];
     for (int v = 0; v < 3; ++v) {
         o_wmap[v] = add_vec(b, wmap[v]);
@@ -1108,6 +1164,11 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
     v.waux = (const DevAux *)at(o_waux);
     v.wplog = (const DevPlog *)at(o_wplog);
     v.wsp = (const double *)at(o_wsp);
+    v.fptr = (const int32_t *)at(o_fptr);
+    v.fent = (const uint4 *)at(o_fent);
+    v.qfptr = (const int32_t *)at(o_qfptr);
+    v.qfent = (const uint4 *)at(o_qfent);
+    v.qinfo = (const int32_t *)at(o_qinfo);
     for (int q = 0; q < 3; ++q) {
         v.wmaps[q].chunk = wsh[q].chunk;
         v.wmaps[q].nchunks = wsh[q].nchunks;
@@ -1163,6 +1224,7 @@ bool rebase_tables(const kx_mech *m, const void *base, MechDev *out)
     KX_REBASE(gpos); KX_REBASE(gneg); KX_REBASE(goff); KX_REBASE(gent);
     KX_REBASE(wrx); KX_REBASE(wrx32); KX_REBASE(waux); KX_REBASE(wplog); KX_REBASE(wsp);
     KX_REBASE(jval); KX_REBASE(jptr); KX_REBASE(jlist); KX_REBASE(jent); KX_REBASE(jtgt);
+    KX_REBASE(fptr); KX_REBASE(fent); KX_REBASE(qfptr); KX_REBASE(qfent); KX_REBASE(qinfo);
     for (int q = 0; q < 3; ++q) {
         KX_REBASE(wmaps[q].species); KX_REBASE(wmaps[q].start); KX_REBASE(wmaps[q].gather);
     }

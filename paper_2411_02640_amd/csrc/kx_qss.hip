@@ -10,8 +10,10 @@
 // sums run over transported species (a QSS species may not carry an
 // efficiency; [M] = p/(R_u T) is their total concentration).
 //
-// Two kernels: one lane per point (below), for up to kWideQss QSS species and
-// calls of more than a few thousand points, and one wave per point:
+// Up to kWideQss QSS species (and as many waves): one lane per point, or for calls
+// of up to about 4096 points one point per workgroup, with the same arithmetic
+// (both below), so that a point's results do not depend on the size of the call.
+// Beyond that one wave per point:
 //
 // Work decomposition: one workgroup of one wave per point.
 //  1. species (thread = k): a_k = (p_atm/RT) e^{-g_k} (eq:K_p, eq:Ck) and C_k;
@@ -45,6 +47,7 @@
 
 #include "kx_internal.h"
 #include "kx_math.h"
+#include "kx_few.h"
 #include "kx_wide.h"
 
 namespace kx {
@@ -383,7 +386,7 @@ __global__ __launch_bounds__(kWave) void qss_kernel(MechDev m, int64_t n,
 // of every reaction follow as in the rates kernel.
 //
 // Against one wave per point (the kernel above): 53 species with 6 QSS species,
-// 2^18 points, 1.48 -> 0.37 ms (20000 points 117 -> 52 us): lanes no longer idle in
+// 2^18 points, 1.50 -> 0.39 ms (20000 points 117 -> 52 us): lanes no longer idle in
 // the species, row and gather phases.  The reactions that enter the balances (a
 // third) are evaluated twice, which costs less than keeping their terms per point.
 // It is bound as the rates kernel is, by vector issue and scalar-load latency.
@@ -424,7 +427,7 @@ __global__ __launch_bounds__(NW *kWave, wide_waves(NW)) void qss_wide_kernel(
         const uint32_t h0 = g[0], h1 = g[1];
         for (int r = w; r < cnt; r += NW) {
             const WideTerms x = reaction_wide<false>(
-                ex, m, const_table(m.wrx) + const_table(m.qlist)[c0 + r], lds, lane8, q);
+                ex, m, const_table(m.wrx) + const_table(m.qlist)[c0 + r], RowPairs{lds, lane8}, q);
             const double k = x.ckf * x.A;
             sq[2 * r * kRow + lane] = k * x.Bf;
             sq[(2 * r + 1) * kRow + lane] = k * x.Br;
@@ -472,12 +475,96 @@ __global__ __launch_bounds__(NW *kWave, wide_waves(NW)) void qss_wide_kernel(
     }
 }
 
+// ---------------------------------------------------------------------------
+// One point per workgroup (kx_few.h), for calls of few points: lanes over the
+// reactions; the forward and reverse terms of the balances' reactions with C = 1 in
+// the QSS pairs, wave 0 with one entry of [A | b] per lane (at most 56), its
+// Gauss-Jordan steps by shuffles, C_Q into the pairs, and the brackets of the
+// reactions that hold a QSS species again.  The terms, their sums and the steps of
+// the elimination are those of qss_wide_kernel, operation by operation: C_Q and
+// wdot of a point are the same bits in a call of any size.
+size_t qss_few_lds_bytes(const MechDev &m)
+{
+    return sizeof(AB) * ((size_t)m.ns + 2) + sizeof(double) * ((size_t)m.nr + 1 + 2 * m.wnqr + 1 + 4);
+}
+
+#pragma float_control(push)
+#pragma clang fp contract(off)
+template <int NT, bool RATES>
+__global__ __launch_bounds__(NT, 4) void qss_few_kernel(
+    MechDev m, int64_t n, const double *__restrict__ T, const double *__restrict__ P,
+    const double *__restrict__ Y, double *__restrict__ wdot, double *__restrict__ Cq)
+{
+    extern __shared__ double lds[];
+    const int ns = m.ns, nr = m.nr, nq = m.nq, tid = threadIdx.x;
+    AB *sp = reinterpret_cast<AB *>(lds);
+    double *R = reinterpret_cast<double *>(sp + ns + 2);  // [nr + 1]
+    double *fb = R + nr + 1;                              // [2 wnqr + 1]
+    const int64_t i = blockIdx.x;
+    const Exp2 ex;
+    const WidePoint q = few_species<false, true, NT>(ex, m, i, n, T, P, Y, sp, fb + 2 * m.wnqr + 1);
+    const PointPairs at{sp};
+    for (int r = tid; r < nr; r += NT) {
+        const int qi = const_table(m.qinfo)[r];
+        if (!RATES && qi < 0) continue;
+        const WideTerms t = reaction_wide<false>(ex, m, const_table(m.wrx) + r, at, q);
+        const double k = t.ckf * t.A;
+        R[r] = qi == -1 ? k * (t.Bf - t.Br) : k;
+        if (qi >= 0) {
+            fb[2 * qi] = k * t.Bf;
+            fb[2 * qi + 1] = k * t.Br;
+        }
+    }
+    if (tid == 0) R[nr] = fb[2 * m.wnqr] = 0.0;
+    __syncthreads();
+    if (tid < kWave) {
+        const int ld = nq + 1;
+        const bool act = tid < nq * ld;
+        const int j = act ? tid / ld : nq - 1, c = act ? tid - j * ld : 0;
+        double a = 0.0;
+        if (act) a = few_gather<false>(m.qfent, m.qfptr[tid], m.qfptr[tid + 1], fb);
+        for (int k = 0; k < nq; ++k) {
+            const double akk = __shfl(a, k * ld + k, kWave);
+            const double ajk = __shfl(a, j * ld + k, kWave);
+            const double akc = __shfl(a, k * ld + c, kWave);
+            if (act && j != k && c > k) a = fma(-(ajk / akk), akc, a);
+        }
+        const double ajj = __shfl(a, j * ld + j, kWave);
+        if (act && c == nq) {
+            const double x = -a / ajj;
+            if (Cq) Cq[(int64_t)j * n + i] = x;
+            if (RATES) {
+                AB &p = sp[m.qsp[j]];
+                p.b = x * krcp(p.a);
+            }
+        }
+    }
+    if (RATES) {
+        __syncthreads();
+        for (int r = tid; r < nr; r += NT)
+            if (const_table(m.qinfo)[r] != -1) R[r] *= bracket_wide(const_table(m.wrx) + r, at);
+        __syncthreads();
+        for (int k = tid; k < ns; k += NT)
+            wdot[(int64_t)k * n + i] =
+                m.qidx[k] >= 0 ? 0.0 : few_gather<false>(m.fent, m.fptr[k], m.fptr[k + 1], R);
+    }
+}
+#pragma float_control(pop)
+
 template <bool RATES> const void *qss_wide_instance(int nw)
 {
     return nw == 4    ? (const void *)qss_wide_kernel<4, RATES>
            : nw == 8  ? (const void *)qss_wide_kernel<8, RATES>
            : nw == 12 ? (const void *)qss_wide_kernel<12, RATES>
                       : (const void *)qss_wide_kernel<16, RATES>;
+}
+
+template <bool RATES> const void *qss_few_instance(int nt)
+{
+    return nt == 64    ? (const void *)qss_few_kernel<64, RATES>
+           : nt == 128 ? (const void *)qss_few_kernel<128, RATES>
+           : nt == 256 ? (const void *)qss_few_kernel<256, RATES>
+                       : (const void *)qss_few_kernel<512, RATES>;
 }
 
 template <class K>
@@ -494,22 +581,34 @@ kx_status launch_qss(const kx_mech *mech, int64_t n, const double *T, const doub
                      const double *Y, double *wdot, double *Cq, hipStream_t s)
 {
     const MechDev &m = mech->dev;
-    // Up to 4096 points every point has a wave of its own resident at once, and one
-    // wave per point has the shorter chain (53 species: 19 us at 1000 points, 41 at
-    // 5000, the one-lane-per-point kernel 34 at both).
-    if (m.wnqr && n > 4096) {
+    // A call whose points can all be resident with a workgroup each has the shorter
+    // chain that way (see kx_few.h; below 64 reactions the one-lane-per-point kernel
+    // is as fast from 2500 points on: 12 species, 9.8 and 9.6 us, at 4096 11.3 and 9.6)
+    const int nt = m.wnqr && (m.nr > 64 || n <= 2048) ? few_threads(n, qss_few_lds_bytes(m)) : 0;
+    if (nt) {
+        const void *kern = wdot ? qss_few_instance<true>(nt) : qss_few_instance<false>(nt);
+        kx_status st = set_lds(kern, qss_few_lds_bytes(m));
+        if (st != KX_OK) return st;
+        void *args[] = {(void *)&m, (void *)&n,    (void *)&T, (void *)&p,
+                        (void *)&Y, (void *)&wdot, (void *)&Cq};
+        hipError_t e = hipLaunchKernel(kern, dim3((unsigned)n), dim3(nt), args,
+                                       qss_few_lds_bytes(m), s);
+        if (e != hipSuccess) return hip_fail(e, "QSS rates kernel launch");
+        return ok();
+    }
+    if (m.wnqr) {
         const int64_t nblk = (n + kRow - 1) / kRow;
         if (nblk > 0x7fffffff) return fail(KX_EINVAL, "QSS rates: n too large");
         // as the rates kernel: 16 waves a tile where every tile has a CU of its own
         const int nw = nblk <= 256 ? 16 : m.wnw;
         const void *kern = wdot ? qss_wide_instance<true>(nw) : qss_wide_instance<false>(nw);
-        const size_t lds = qss_wide_lds_bytes(m, nw);
-        hipError_t e =
-            hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute (qss LDS)");
+        const size_t wide_lds = qss_wide_lds_bytes(m, nw);
+        kx_status st = set_lds(kern, wide_lds);
+        if (st != KX_OK) return st;
         void *args[] = {(void *)&m, (void *)&n,    (void *)&T, (void *)&p,
                         (void *)&Y, (void *)&wdot, (void *)&Cq};
-        e = hipLaunchKernel(kern, dim3((unsigned)nblk), dim3(nw * kWave), args, lds, s);
+        hipError_t e =
+            hipLaunchKernel(kern, dim3((unsigned)nblk), dim3(nw * kWave), args, wide_lds, s);
         if (e != hipSuccess) return hip_fail(e, "QSS rates kernel launch");
         return ok();
     }

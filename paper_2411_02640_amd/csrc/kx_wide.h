@@ -73,20 +73,26 @@ __device__ __forceinline__ double row_val(const double *lds, unsigned row, unsig
     return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(lds) +
                                              ((row << 9) + lane8));
 }
-// a and b of species k: rows 2 k and 2 k + 1 (one ds_read2st64_b64).
-struct AB {
+// a and b of a species.
+struct alignas(16) AB {
     double a, b;
 };
-__device__ __forceinline__ AB species_val(const double *lds, unsigned k, unsigned lane8)
-{
-    const char *p = reinterpret_cast<const char *>(lds) + ((k << 10) + lane8);
-    return AB{*reinterpret_cast<const double *>(p), *reinterpret_cast<const double *>(p + 512)};
-}
-__device__ __forceinline__ double species_b(const double *lds, unsigned k, unsigned lane8)
-{
-    return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(lds) +
-                                             ((k << 10) + lane8) + 512);
-}
+// Where a lane reads them: the species rows (lane = point, one ds_read2st64_b64
+// per pair), or one point's pairs side by side (kx_few.h).
+struct RowPairs {
+    const double *lds;
+    unsigned lane8;
+    __device__ __forceinline__ AB pair(unsigned k) const
+    {
+        const char *p = reinterpret_cast<const char *>(lds) + ((k << 10) + lane8);
+        return AB{*reinterpret_cast<const double *>(p), *reinterpret_cast<const double *>(p + 512)};
+    }
+    __device__ __forceinline__ double b(unsigned k) const
+    {
+        return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(lds) +
+                                                 ((k << 10) + lane8) + 512);
+    }
+};
 
 // What a lane knows about a point of its own.  L is log2 T on the FP64 path and
 // ln T on the mixed path, whose FP32 exponential cores take natural arguments.
@@ -171,12 +177,13 @@ __device__ __forceinline__ unsigned offsets16(KX_CONST uint16_t *o, int pair)
 }
 
 // [X]_i = default [M] + sum over listed species of (alpha - default) C_k.
+template <class Pairs>
 __device__ __forceinline__ double third_body_wide(const MechDev &m, KX_CONST DevAux *ax,
-                                                  const double *lds, unsigned lane8, double M)
+                                                  const Pairs &sp, double M)
 {
     double X = ax->eff_default * M;
     auto add = [&](double d, unsigned k) {
-        const AB s = species_val(lds, k, lane8);
+        const AB s = sp.pair(k);
         X = fma(d, s.a * s.b, X);
     };
 #pragma unroll
@@ -197,18 +204,18 @@ struct WideTerms {
     double ckf, A, Bf, Br;
 };
 
-template <bool MIXED>
+template <bool MIXED, class Pairs>
 __device__ __forceinline__ WideTerms reaction_wide(const Exp2 &ex, const MechDev &m,
-                                                   KX_CONST DevWide *r, const double *lds,
-                                                   unsigned lane8, const WidePoint &q)
+                                                   KX_CONST DevWide *r, const Pairs &sp,
+                                                   const WidePoint &q)
 {
     const unsigned meta = r->meta;
     const unsigned r01 = r->r01, p01 = r->p01;
     // the LDS reads are issued first; the exponential covers their latency
-    const AB r0 = species_val(lds, r01 & 0xFFFFu, lane8);
-    const AB r1 = species_val(lds, r01 >> 16, lane8);
-    const double p0 = species_b(lds, p01 & 0xFFFFu, lane8);
-    const double p1 = species_b(lds, p01 >> 16, lane8);
+    const AB r0 = sp.pair(r01 & 0xFFFFu);
+    const AB r1 = sp.pair(r01 >> 16);
+    const double p0 = sp.b(p01 & 0xFFFFu);
+    const double p1 = sp.b(p01 >> 16);
     KX_CONST DevAux *ax = const_table(MIXED ? m.aux : m.waux) + (meta >> 16);
     WideTerms t;
     double x;
@@ -228,10 +235,10 @@ __device__ __forceinline__ WideTerms reaction_wide(const Exp2 &ex, const MechDev
     t.Br = p0 * p1;
     if (meta & kWideThird) {
         const unsigned rp2 = r->rp2;
-        const AB r2 = species_val(lds, rp2 & 0xFFFFu, lane8);
+        const AB r2 = sp.pair(rp2 & 0xFFFFu);
         t.A *= r2.a;
         t.Bf *= r2.b;
-        t.Br *= species_b(lds, rp2 >> 16, lane8);
+        t.Br *= sp.b(rp2 >> 16);
     }
     if (meta & kWideOrders) {
         // explicit forward orders (irreversible): prod_k C_k^o_k, C_k = a_k b_k
@@ -242,7 +249,7 @@ __device__ __forceinline__ WideTerms reaction_wide(const Exp2 &ex, const MechDev
             const double o = ax->oval[e];
             if (o != 0.0) {
                 const unsigned w = offsets16(ax->ooff, e / 2) >> 16 * (e & 1);
-                const AB c = species_val(lds, (w & 0xFFFFu) / 16u, lane8);
+                const AB c = sp.pair((w & 0xFFFFu) / 16u);
                 const double C = c.a * c.b;
                 zero = zero || !(C > 0.0);
                 s = fma(o, kl2(fmax(C, DBL_MIN)), s);
@@ -253,7 +260,7 @@ __device__ __forceinline__ WideTerms reaction_wide(const Exp2 &ex, const MechDev
         t.Br = 0.0;
     }
     if (meta & kWideThirdBody) {
-        const double X = third_body_wide(m, ax, lds, lane8, q.M);
+        const double X = third_body_wide(m, ax, sp, q.M);
         double c = X;
         if (meta & kWideFalloff) {
             // P_r = k_0 [X] / k_inf = e0 [X] with e0 from the difference of the exponents
@@ -277,6 +284,21 @@ __device__ __forceinline__ WideTerms reaction_wide(const Exp2 &ex, const MechDev
         t.ckf *= c;
     }
     return t;
+}
+
+// B' - B'' of a reaction alone, as reaction_wide forms the two products.
+template <class Pairs>
+__device__ __forceinline__ double bracket_wide(KX_CONST DevWide *r, const Pairs &sp)
+{
+    const unsigned meta = r->meta, r01 = r->r01, p01 = r->p01;
+    double f = sp.b(r01 & 0xFFFFu) * sp.b(r01 >> 16);
+    double b = sp.b(p01 & 0xFFFFu) * sp.b(p01 >> 16);
+    if (meta & kWideThird) {
+        const unsigned rp2 = r->rp2;
+        f *= sp.b(rp2 & 0xFFFFu);
+        b *= sp.b(rp2 >> 16);
+    }
+    return (meta & kWideOrders) ? 1.0 : f - b;
 }
 
 // A workgroup's tile of 64 points: this lane's point (points past npts repeat
@@ -333,7 +355,7 @@ __device__ __forceinline__ WidePoint species_rows(const Exp2 &ex, const MechDev 
     for (int s = 0; s < NS; ++s) {
         if (ks[s] >= 0) {
             const double iw = sp[16 * ks[s] + 15];
-            y[s] = QSS && iw == 0.0 ? 0.0 : y[s] * iw;  // a QSS entry of Y is not read
+            y[s] = QSS && iw == 0.0 ? 0.0 : y[s] * iw;  // a QSS entry of Y does not enter
             lds[2 * ks[s] * kRow + lane] = y[s];
         }
     }
@@ -437,6 +459,7 @@ __device__ __forceinline__ void rates_of_rows(const Exp2 &ex, const MechDev &m,
     KX_CONST uint32_t *g =
         (KX_CONST uint32_t *)(const_table(t.wm.gather) + const_table(t.wm.start)[t.w]);
     const unsigned lane8 = 8u * (unsigned)t.lane;
+    const RowPairs sp{lds, lane8};
     double acc[NS], cmp[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) acc[s] = cmp[s] = 0.0;
@@ -444,7 +467,7 @@ __device__ __forceinline__ void rates_of_rows(const Exp2 &ex, const MechDev &m,
         const int base = c * chunk, cnt = min(chunk, nr - base);
         const uint32_t h0 = g[0], h1 = g[1];  // groups of each species
         for (int r = t.w; r < cnt; r += NW) {
-            const WideTerms x = reaction_wide<MIXED>(ex, m, rx + base + r, lds, lane8, q);
+            const WideTerms x = reaction_wide<MIXED>(ex, m, rx + base + r, sp, q);
             sq[r * kRow + t.lane] = x.ckf * x.A * (x.Bf - x.Br);
         }
         __syncthreads();

@@ -1,0 +1,53 @@
+"""A point's results do not depend on how many points a call has: the forms that a
+call's size selects (one point per workgroup, one lane per point with every tile on
+a CU of its own or with several to a CU) give the same bits."""
+import numpy as np
+import pytest
+
+from paper_2411_02640_amd import inputs as I
+
+from . import tiny_mechs as TM
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _mech(ns, nq=0, seed=0, **kw):
+    nr = 7 * ns
+    fall, three, lind = max(1, nr * 6 // 100), nr // 10, nr // 50
+    return I.make_mechanism(I.MechSpec(ns, nr - fall - three - lind, three, lind, fall,
+                                       seed=seed or 9000 + ns, n_qss=nq, **kw))
+
+
+def _states(ns, n, seed=91):
+    s = I.make_states(ns, I.StateSpec(n, seed=seed, p_atm_range=(0.2, 40.0), dirichlet_alpha=0.3))
+    return [torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0") for a in s]
+
+
+def _first(d, m):
+    return d[0][:m].clone(), d[1][:m].clone(), d[2][:, :m].contiguous()
+
+
+QSS = {"chain2": lambda: TM.qss_chain_mechanism((TM.Q1_, TM.Q2_)),  # 4 waves
+       "24sp-4": lambda: _mech(24, 4, 9031),                        # 8 waves
+       "53Q": lambda: I.make_mechanism(I.MECH_53Q),                 # 12 waves
+       "53XQ": lambda: I.make_mechanism(I.MECH_53XQ),
+       "56sp-7": lambda: _mech(56, 7),                              # every column of [A | b]
+       "80sp-7": lambda: _mech(80, 7)}                              # 16 waves
+
+
+@pytest.mark.parametrize("name", list(QSS))
+def test_qss(name):
+    from paper_2411_02640_amd import kx
+    mech = QSS[name]()
+    n = 16384 + 70
+    dm = kx.Mechanism(mech, 0)
+    d = _states(mech["n_species"], n)
+    print("[gpu-case] qss call sizes", name, flush=True)
+    C, w = kx.qss_concentrations(dm, *d), kx.production_rates(dm, *d)
+    for m in (1, 512, 513, 1025, 2049, 4096, 4097, 16384):
+        s = _first(d, m)
+        assert torch.equal(kx.qss_concentrations(dm, *s), C[:, :m]), m
+        assert torch.equal(kx.production_rates(dm, *s), w[:, :m]), m
+    dm.close()
