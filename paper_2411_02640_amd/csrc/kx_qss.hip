@@ -581,6 +581,10 @@ kx_status launch_qss(const kx_mech *mech, int64_t n, const double *T, const doub
                      const double *Y, double *wdot, double *Cq, hipStream_t s)
 {
     const MechDev &m = mech->dev;
+    // the limit of the kernel for any number of QSS species, whatever n is
+    const size_t lds = qss_lds_bytes(m);
+    if (lds > 160 * 1024)
+        return fail(KX_EUNSUPPORTED, "QSS rates: mechanism too large for one workgroup's LDS");
     // A call whose points can all be resident with a workgroup each has the shorter
     // chain that way (see kx_few.h; below 64 reactions the one-lane-per-point kernel
     // is as fast from 2500 points on: 12 species, 9.8 and 9.6 us, at 4096 11.3 and 9.6)
@@ -612,9 +616,6 @@ kx_status launch_qss(const kx_mech *mech, int64_t n, const double *T, const doub
         if (e != hipSuccess) return hip_fail(e, "QSS rates kernel launch");
         return ok();
     }
-    const size_t lds = qss_lds_bytes(m);
-    if (lds > 160 * 1024)
-        return fail(KX_EUNSUPPORTED, "QSS rates: mechanism too large for one workgroup's LDS");
     // One wave per point.  A point's work is a chain of dependent loads and
     // barriers rather than arithmetic, so more points in flight per CU beat more
     // threads per point: 2.8x faster than 256-thread groups on 53 species with

@@ -51,3 +51,36 @@ def test_qss(name):
         assert torch.equal(kx.qss_concentrations(dm, *s), C[:, :m]), m
         assert torch.equal(kx.production_rates(dm, *s), w[:, :m]), m
     dm.close()
+
+
+def _repeated(mech, times):
+    """The mechanism with every reaction listed `times` times."""
+    m, nr = dict(mech), mech["n_reactions"]
+    for key in ("reac", "prod", "eff"):
+        cnt = np.diff(m[key + "_ptr"])
+        m[key + "_ptr"] = np.concatenate([[0], np.cumsum(np.tile(cnt, times))]).astype(np.int32)
+        for part in ("_sp", "_nu", "_val"):
+            if key + part in m:
+                m[key + part] = np.tile(m[key + part], times)
+    for key, v in mech.items():
+        if isinstance(v, np.ndarray) and v.shape[:1] == (nr,) and key not in ("qss", "t_mid") \
+                and not key.endswith(("_sp", "_nu", "_val", "fit")) and "nasa" not in key \
+                and key != "composition":
+            m[key] = np.tile(v, (times,) + (1,) * (v.ndim - 1))
+    m["n_reactions"] = nr * times
+    return m
+
+
+def test_qss_mechanism_too_large():
+    """A mechanism whose reaction terms exceed one workgroup's LDS is refused whatever
+    the number of points."""
+    from paper_2411_02640_amd import kx
+    mech = _repeated(TM.qss_chain_mechanism((TM.Q1_, TM.Q2_)), 2500)
+    assert mech["n_reactions"] * 16 > 160 * 1024
+    dm = kx.Mechanism(mech, 0)
+    for n in (10, 5000):
+        print("[gpu-case] qss too large", n, flush=True)
+        with pytest.raises(kx.KxError) as e:
+            kx.production_rates(dm, *_states(5, n))
+        assert e.value.code == kx.KX_EUNSUPPORTED
+    dm.close()
