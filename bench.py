@@ -34,7 +34,7 @@ def log(*a):
 
 # Sources whose change invalidates a committed traffic measurement of a kernel.
 KERNEL_SOURCES = {
-    "rates": ["kx_rates.hip", "kx_wide.h", "kx_math.h", "kx_internal.h"],
+    "rates": ["kx_rates.hip", "kx_wide.h", "kx_few.h", "kx_math.h", "kx_internal.h"],
     "transport": ["kx_transport.hip", "kx_math.h", "kx_internal.h"],
 }
 

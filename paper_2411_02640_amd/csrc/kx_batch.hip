@@ -12,6 +12,7 @@
 // Every call on a device uses that device's one copy of the array.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 
@@ -95,7 +96,9 @@ extern "C" kx_status kx_batch_noalloc(const kx_mech *mech, int32_t ops, int32_t 
                                    std::to_string(KX_BATCH_MAX_ITEMS));
     if (nitems > 0 && !items) return fail(KX_EINVAL, "kx_batch_noalloc: items is NULL");
     const bool tr = (ops & KX_OP_TRANSPORT) != 0;
-    const int rtp = rates_tile_points(mech->dev);
+    int64_t points = 0;
+    for (int r = 0; r < nitems; ++r) points += std::max<int64_t>(items[r].n, 0);
+    const int rtp = rates_items_tile_points(mech->dev, points);
     const int ttp = transport_tile_points(mech->dev, precision);
     BatchArgs a;
     std::memset(&a, 0, sizeof a);
@@ -151,7 +154,7 @@ extern "C" kx_status kx_batch_noalloc(const kx_mech *mech, int32_t ops, int32_t 
     hipLaunchKernelGGL(batch_setup_kernel, dim3(1), dim3(64), 0, stream, a, wl);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "kx_batch_noalloc: setup kernel launch");
-    st = launch_rates_items(mech->dev, wl, tiles_r, precision, stream);
+    st = launch_rates_items(mech->dev, rtp == 1 ? &mech->few : nullptr, wl, tiles_r, precision, stream);
     if (st == KX_OK && tr) st = launch_transport_items(mech->dev, wl, tiles_t, precision, stream);
     if (st != KX_OK) return st;
     return ok();

@@ -191,11 +191,6 @@ struct MechDev {
     // the same chunks (so that the mixed path's compensated groups stay the same);
     // 2: 16 waves, as many rate rows as the LDS holds
     WideMap wmaps[3];
-    // One point per workgroup (kx_few.h): a species' list of rates, words of four
-    // entries (reaction in kernel order, listed |nu| times, and kFew* bits; padding
-    // entries name the zero slot nr)
-    const int32_t *fptr;       // [ns + 1] first word of a species' list
-    const uint4 *fent;
     // Jacobian in row blocks (kx_jacobian.hip); jrows = 0: not laid out (more than
     // 128 species, QSS species, or more slot derivatives than the LDS holds)
     int32_t jnv;               // slot derivatives of all reactions (a zero follows them)
@@ -248,10 +243,20 @@ struct MechDev {
     const int32_t *qlist;      // [wnqr] kernel order
     const uint32_t *qstart;    // [nq], qgather: the streams of a balance row (WideMap), its
     const uint4 *qgather;      // accumulators the columns of [A | b]
-    // The same for one point per workgroup: the entries of [A | b] as lists over
-    // the forward (2 r) and reverse (2 r + 1) terms of the wnqr reactions
-    const int32_t *qfptr;      // [nq * (nq + 1) + 1]
-    const uint4 *qfent;
+};
+
+// Tables of the one-point-per-workgroup kernels (kx_few.h).  Not in MechDev: five
+// pointers more there cost the one-lane-per-point kernels, whose workgroups read
+// their arguments anew, 2 % (53 species, 2^18 points: 282 -> 288 us).
+struct FewDev {
+    // a species' list of rates, words of four entries (reaction in kernel order,
+    // listed |nu| times, and kFew* bits; padding entries name the zero slot nr)
+    const int32_t *ptr;        // [ns + 1] first word of a species' list
+    const uint4 *ent;
+    // QSS: the entries of [A | b] as lists over the forward (2 r) and reverse
+    // (2 r + 1) terms of the MechDev::wnqr reactions
+    const int32_t *qptr;       // [nq * (nq + 1) + 1]
+    const uint4 *qent;
     const int32_t *qinfo;      // [nr] kernel order: index in qlist, -1: no QSS species,
                                // -2: one on both sides (not in the balances)
 };
@@ -311,6 +316,7 @@ static_assert(kMaxBatch <= 64, "work_item_ballot covers the items with one wave"
 struct kx_mech {
     int device;
     kx::MechDev dev;
+    kx::FewDev few;
     void *blob;          // single device allocation holding every table
     int64_t bytes;
     int32_t n_species, n_reactions;
@@ -341,6 +347,9 @@ kx_status launch_qss(const kx_mech *m, int64_t n, const double *T, const double 
 // serving work lists are cut in the same tiles as a direct call, so a request
 // gives bit-identical results alone and in a batch).
 int rates_tile_points(const MechDev &m);
+// The same for launch_rates_items with `points` points in all (one-point tiles for
+// few points).
+int rates_items_tile_points(const MechDev &m, int64_t points);
 int transport_tile_points(const MechDev &m, int precision);
 // Batched (work-list) launches; `counter` must be zero at launch.
 // prepare_rates_batch sets the kernel's dynamic-LDS limit (call it before
@@ -348,9 +357,9 @@ int transport_tile_points(const MechDev &m, int precision);
 kx_status prepare_rates_batch(const MechDev &m, int precision);
 // One workgroup per tile of the work list (`ntiles` = wl->ntiles[0] for rates,
 // wl->ntiles[1] for transport, known to the host that wrote the list); no
-// counters.
-kx_status launch_rates_items(const MechDev &m, const WorkList *wl, int64_t ntiles, int precision,
-                             hipStream_t s);
+// counters.  few: the list is cut in tiles of one point (null: rates_tile_points).
+kx_status launch_rates_items(const MechDev &m, const FewDev *few, const WorkList *wl,
+                             int64_t ntiles, int precision, hipStream_t s);
 kx_status launch_transport_items(const MechDev &m, const WorkList *wl, int64_t ntiles,
                                  int precision, hipStream_t s);
 kx_status launch_rates_batch(const MechDev &m, const WorkList *wl, int *counter, int precision,

@@ -1075,9 +1075,6 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
     const size_t o_jval = add_vec(b, jt.val), o_jptr = add_vec(b, jt.ptr);
     const size_t o_jlist = add_vec(b, jt.list), o_jent = add_vec(b, jt.ent);
     const size_t o_jtgt = add_vec(b, jt.tgt);
-    const size_t o_fptr = add_vec(b, fptr), o_fent = add_vec(b, fent);
-    const size_t o_qfptr = add_vec(b, qfptr), o_qfent = add_vec(b, qfent);
-    const size_t o_qinfo = add_vec(b, qinfo);
     size_t o_wmap[3], o_wstart[3], o_wgat[3];
     for (int v = 0; v < 3; ++v) {
         o_wmap[v] = add_vec(b, wmap[v]);
@@ -1094,6 +1091,9 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
     const size_t o_gf32 = add_vec(b, to32(gfrag)), o_c1f32 = add_vec(b, to32(c1frag));
     const size_t o_qidx = add_vec(b, qidx), o_qrx = add_vec(b, qrx);
     const size_t o_qptr = add_vec(b, qrow_ptr), o_qent = add_vec(b, qrow_ent);
+    const size_t o_fptr = add_vec(b, fptr), o_fent = add_vec(b, fent);
+    const size_t o_qfptr = add_vec(b, qfptr), o_qfent = add_vec(b, qfent);
+    const size_t o_qinfo = add_vec(b, qinfo);
 
     void *blob = nullptr;
     if (!host_only) {
@@ -1164,11 +1164,6 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
     v.waux = (const DevAux *)at(o_waux);
     v.wplog = (const DevPlog *)at(o_wplog);
     v.wsp = (const double *)at(o_wsp);
-    v.fptr = (const int32_t *)at(o_fptr);
-    v.fent = (const uint4 *)at(o_fent);
-    v.qfptr = (const int32_t *)at(o_qfptr);
-    v.qfent = (const uint4 *)at(o_qfent);
-    v.qinfo = (const int32_t *)at(o_qinfo);
     for (int q = 0; q < 3; ++q) {
         v.wmaps[q].chunk = wsh[q].chunk;
         v.wmaps[q].nchunks = wsh[q].nchunks;
@@ -1207,6 +1202,11 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
     v.qrx = (const int2 *)at(o_qrx);
     v.qrow_ptr = (const int32_t *)at(o_qptr);
     v.qrow_ent = (const int4 *)at(o_qent);
+    m->few.ptr = (const int32_t *)at(o_fptr);
+    m->few.ent = (const uint4 *)at(o_fent);
+    m->few.qptr = (const int32_t *)at(o_qfptr);
+    m->few.qent = (const uint4 *)at(o_qfent);
+    m->few.qinfo = (const int32_t *)at(o_qinfo);
     *out = m;
     return ok();
 }
@@ -1224,7 +1224,6 @@ bool rebase_tables(const kx_mech *m, const void *base, MechDev *out)
     KX_REBASE(gpos); KX_REBASE(gneg); KX_REBASE(goff); KX_REBASE(gent);
     KX_REBASE(wrx); KX_REBASE(wrx32); KX_REBASE(waux); KX_REBASE(wplog); KX_REBASE(wsp);
     KX_REBASE(jval); KX_REBASE(jptr); KX_REBASE(jlist); KX_REBASE(jent); KX_REBASE(jtgt);
-    KX_REBASE(fptr); KX_REBASE(fent); KX_REBASE(qfptr); KX_REBASE(qfent); KX_REBASE(qinfo);
     for (int q = 0; q < 3; ++q) {
         KX_REBASE(wmaps[q].species); KX_REBASE(wmaps[q].start); KX_REBASE(wmaps[q].gather);
     }

@@ -492,7 +492,7 @@ size_t qss_few_lds_bytes(const MechDev &m)
 #pragma clang fp contract(off)
 template <int NT, bool RATES>
 __global__ __launch_bounds__(NT, 4) void qss_few_kernel(
-    MechDev m, int64_t n, const double *__restrict__ T, const double *__restrict__ P,
+    MechDev m, FewDev f, int64_t n, const double *__restrict__ T, const double *__restrict__ P,
     const double *__restrict__ Y, double *__restrict__ wdot, double *__restrict__ Cq)
 {
     extern __shared__ double lds[];
@@ -505,7 +505,7 @@ __global__ __launch_bounds__(NT, 4) void qss_few_kernel(
     const WidePoint q = few_species<false, true, NT>(ex, m, i, n, T, P, Y, sp, fb + 2 * m.wnqr + 1);
     const PointPairs at{sp};
     for (int r = tid; r < nr; r += NT) {
-        const int qi = const_table(m.qinfo)[r];
+        const int qi = const_table(f.qinfo)[r];
         if (!RATES && qi < 0) continue;
         const WideTerms t = reaction_wide<false>(ex, m, const_table(m.wrx) + r, at, q);
         const double k = t.ckf * t.A;
@@ -522,7 +522,7 @@ __global__ __launch_bounds__(NT, 4) void qss_few_kernel(
         const bool act = tid < nq * ld;
         const int j = act ? tid / ld : nq - 1, c = act ? tid - j * ld : 0;
         double a = 0.0;
-        if (act) a = few_gather<false>(m.qfent, m.qfptr[tid], m.qfptr[tid + 1], fb);
+        if (act) a = few_gather<false>(f.qent, f.qptr[tid], f.qptr[tid + 1], fb);
         for (int k = 0; k < nq; ++k) {
             const double akk = __shfl(a, k * ld + k, kWave);
             const double ajk = __shfl(a, j * ld + k, kWave);
@@ -542,11 +542,11 @@ __global__ __launch_bounds__(NT, 4) void qss_few_kernel(
     if (RATES) {
         __syncthreads();
         for (int r = tid; r < nr; r += NT)
-            if (const_table(m.qinfo)[r] != -1) R[r] *= bracket_wide(const_table(m.wrx) + r, at);
+            if (const_table(f.qinfo)[r] != -1) R[r] *= bracket_wide(const_table(m.wrx) + r, at);
         __syncthreads();
         for (int k = tid; k < ns; k += NT)
             wdot[(int64_t)k * n + i] =
-                m.qidx[k] >= 0 ? 0.0 : few_gather<false>(m.fent, m.fptr[k], m.fptr[k + 1], R);
+                m.qidx[k] >= 0 ? 0.0 : few_gather<false>(f.ent, f.ptr[k], f.ptr[k + 1], R);
     }
 }
 #pragma float_control(pop)
@@ -593,8 +593,8 @@ kx_status launch_qss(const kx_mech *mech, int64_t n, const double *T, const doub
         const void *kern = wdot ? qss_few_instance<true>(nt) : qss_few_instance<false>(nt);
         kx_status st = set_lds(kern, qss_few_lds_bytes(m));
         if (st != KX_OK) return st;
-        void *args[] = {(void *)&m, (void *)&n,    (void *)&T, (void *)&p,
-                        (void *)&Y, (void *)&wdot, (void *)&Cq};
+        void *args[] = {(void *)&m, (void *)&mech->few, (void *)&n,    (void *)&T,
+                        (void *)&p, (void *)&Y,         (void *)&wdot, (void *)&Cq};
         hipError_t e = hipLaunchKernel(kern, dim3((unsigned)n), dim3(nt), args,
                                        qss_few_lds_bytes(m), s);
         if (e != hipSuccess) return hip_fail(e, "QSS rates kernel launch");

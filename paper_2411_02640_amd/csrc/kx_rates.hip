@@ -1,8 +1,9 @@
 // kx_rates.hip -- species net production rates on gfx950.
 //
-// Two kernels.  Mechanisms of up to kWideMaxSpecies species: one lane per point,
-// every species and reaction wave-uniform (kx_wide.h, rates_wide_tile below).
-// Larger ones, whose species rows for 64 points exceed the LDS: lanes over
+// Three kernels.  Mechanisms of up to kWideMaxSpecies species: one lane per point,
+// every species and reaction wave-uniform (kx_wide.h, rates_wide_tile below), or for
+// calls of few points one point per workgroup with the same arithmetic (kx_few.h,
+// rates_few_point).  Larger ones, whose species rows for 64 points exceed the LDS: lanes over
 // species and (reaction, point) pairs (rates_tile).
 //
 // Both evaluate, per point,
@@ -36,6 +37,7 @@
 
 #include <type_traits>
 
+#include "kx_few.h"
 #include "kx_internal.h"
 #include "kx_math.h"
 #include "kx_wide.h"
@@ -921,6 +923,113 @@ kx_status launch_wide(const MechDev &m, int precision, int nw, int64_t grid, voi
     return ok();
 }
 
+// ---------------------------------------------------------------------------
+// One point per workgroup (kx_few.h), for calls of few points.
+size_t few_lds_bytes(const MechDev &m)
+{
+    return sizeof(AB) * ((size_t)m.ns + 2) + sizeof(double) * ((size_t)m.nr + 1 + 4);
+}
+
+#pragma float_control(push)
+#pragma clang fp contract(off)
+template <bool MIXED, int NT>
+__device__ __forceinline__ void rates_few_point(const MechDev &m, const FewDev &f, int64_t i,
+                                                int64_t ld,
+                                                const double *__restrict__ T,
+                                                const double *__restrict__ P,
+                                                const double *__restrict__ Y,
+                                                double *__restrict__ wdot)
+{
+    extern __shared__ double lds[];
+    const int ns = m.ns, nr = m.nr, tid = threadIdx.x;
+    AB *sp = reinterpret_cast<AB *>(lds);
+    double *R = reinterpret_cast<double *>(sp + ns + 2);  // [nr + 1]
+    const Exp2 ex;
+    const WidePoint q = few_species<MIXED, false, NT>(ex, m, i, ld, T, P, Y, sp, R + nr + 1);
+    KX_CONST DevWide *rx = const_table(MIXED ? m.wrx32 : m.wrx);
+    for (int r = tid; r < nr; r += NT) {
+        const WideTerms t = reaction_wide<MIXED>(ex, m, rx + r, PointPairs{sp}, q);
+        R[r] = t.ckf * t.A * (t.Bf - t.Br);
+    }
+    if (tid == 0) R[nr] = 0.0;
+    __syncthreads();
+    for (int k = tid; k < ns; k += NT)
+        wdot[(int64_t)k * ld + i] = few_gather<MIXED>(f.ent, f.ptr[k], f.ptr[k + 1], R);
+}
+#pragma float_control(pop)
+
+template <bool MIXED, int NT>
+__global__ __launch_bounds__(NT, 4) void rates_few_kernel(MechDev m, FewDev f, int64_t ld,
+                                                          const double *__restrict__ T,
+                                                          const double *__restrict__ P,
+                                                          const double *__restrict__ Y,
+                                                          double *__restrict__ wdot)
+{
+    rates_few_point<MIXED, NT>(m, f, blockIdx.x, ld, T, P, Y, wdot);
+}
+
+// Batched requests of few points together: a tile is a point.
+template <bool MIXED, int NT>
+__global__ __launch_bounds__(NT, 4) void rates_few_items_kernel(MechDev m, FewDev f,
+                                                                const WorkList *__restrict__ wl)
+{
+    const int t = (int)blockIdx.x;
+    if (t >= wl->ntiles[0]) return;
+    const int r = work_item_ballot(wl, 0, t);
+    const WorkItem it = wl->items[r];
+    rates_few_point<MIXED, NT>(m, f, t - wl->start[0][r], it.n, it.T, it.p, it.Y, it.wdot);
+}
+
+template <bool ITEMS, bool MIXED, int NT> const void *few_instance()
+{
+    return ITEMS ? (const void *)rates_few_items_kernel<MIXED, NT>
+                 : (const void *)rates_few_kernel<MIXED, NT>;
+}
+
+template <bool ITEMS>
+kx_status launch_few(const MechDev &m, int precision, int nt, int64_t points, void **args,
+                     hipStream_t s)
+{
+    auto pick = [&](auto mixed) {
+        constexpr bool M = decltype(mixed)::value;
+        return nt == 64    ? few_instance<ITEMS, M, 64>()
+               : nt == 128 ? few_instance<ITEMS, M, 128>()
+               : nt == 256 ? few_instance<ITEMS, M, 256>()
+                           : few_instance<ITEMS, M, 512>();
+    };
+    const void *kern = precision == KX_MIXED ? pick(std::true_type{}) : pick(std::false_type{});
+    const size_t lds = few_lds_bytes(m);
+    hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute (rates)");
+    e = hipLaunchKernel(kern, dim3((unsigned)points), dim3(nt), args, lds, s);
+    if (e != hipSuccess) return hip_fail(e, "rates kernel launch");
+    return ok();
+}
+
+// Threads per point of a call of `points` points, 0: tiles of 64 points.  A tile's
+// chain grows with the number of reactions, a point's hardly does, so the line
+// depends on it (FP64, us a call, one point per workgroup / tiles): 9 species (21
+// reactions) 7.0 / 6.6 at any size; 17 (119) 8.1 / 10.1 at 2000 points, 11.2 / 10.1
+// at 4096; 53 (371) 6.6 / 22.7 at 1 point, 9.0 / 23.1 at 1000, 18.9 / 23.2 at 4096,
+// 25.6 / 23.3 at 5000; 128 (896) 8.1 / 64.6 at 1 point, 37 / 66 at 4096.
+int rates_few_threads(const MechDev &m, int64_t points)
+{
+    const int64_t most = m.wnw == 0 || m.nr <= 64 ? 0 : (m.nr <= 160 ? 2048 : 4096);
+    return points <= most ? few_threads(points, few_lds_bytes(m)) : 0;
+}
+
+// Points at the end of a call of n points that go one to a workgroup, after tiles
+// on every CU: a few tiles more than CUs cost a second round (one workgroup per CU)
+// or take the CUs' shared shape, which is slower per tile.  FP64, us a call with /
+// without: 57 species, 16500 points 33.7 / 49.8; 128 species
+// 77 / 131; 53 species 31 / 40 (17 species 16.9 / 14.6, hence the number of reactions).
+int64_t rates_tail(const MechDev &m, int64_t n)
+{
+    const int64_t tail = n - 256 * kRow;
+    const int64_t most = m.wnw == 16 ? 4096 : (m.nr > 300 ? 2048 : 0);
+    return tail > 0 && tail <= most && rates_few_threads(m, tail) ? tail : 0;
+}
+
 size_t rates_lds_bytes(const MechDev &m, int tp)
 {
     const int ps = rates_step_points_for(m.gpass);
@@ -934,6 +1043,11 @@ size_t rates_lds_bytes(const MechDev &m, int tp)
 int rates_tile_points(const MechDev &m)
 {
     return m.wnw ? kRow : rates_tile_points_for(m.gpass);
+}
+
+int rates_items_tile_points(const MechDev &m, int64_t points)
+{
+    return rates_few_threads(m, points) ? 1 : rates_tile_points(m);
 }
 
 namespace {
@@ -964,11 +1078,19 @@ kx_status launch_rates(const kx_mech *mech, int64_t n, const double *T, const do
     const MechDev &m = mech->dev;
     const int tp = rates_tile_points(m);
     if (m.wnw) {
-        const int64_t nblk = (n + kRow - 1) / kRow;
+        const int64_t tail = rates_few_threads(m, n) ? n : rates_tail(m, n), body = n - tail;
+        const int64_t nblk = (body + kRow - 1) / kRow;
         if (nblk > 0x7fffffff) return fail(KX_EINVAL, "production rates: n too large");
-        void *args[] = {(void *)&m, (void *)&n, (void *)&T, (void *)&p, (void *)&Y, (void *)&wdot};
-        return launch_wide<0>(m, precision, wide_launch_waves(m, nblk), nblk, args, s,
-                              "rates kernel launch");
+        if (body) {  // whole tiles if there is a tail
+            void *args[] = {(void *)&m, (void *)&n, (void *)&T, (void *)&p, (void *)&Y, (void *)&wdot};
+            kx_status st = launch_wide<0>(m, precision, wide_launch_waves(m, nblk), nblk, args, s,
+                                          "rates kernel launch");
+            if (st != KX_OK || !tail) return st;
+        }
+        T += body, p += body, Y += body, wdot += body;
+        void *args[] = {(void *)&m, (void *)&mech->few, (void *)&n,   (void *)&T,
+                        (void *)&p, (void *)&Y,         (void *)&wdot};
+        return launch_few<false>(m, precision, rates_few_threads(m, tail), tail, args, s);
     }
     const size_t lds = rates_lds_bytes(m, tp);
     if (lds > 160 * 1024)
@@ -1011,11 +1133,15 @@ auto pick_items(const MechDev &m, int precision)
 }
 }  // namespace
 
-kx_status launch_rates_items(const MechDev &m, const WorkList *wl, int64_t ntiles, int precision,
-                             hipStream_t s)
+kx_status launch_rates_items(const MechDev &m, const FewDev *few, const WorkList *wl,
+                             int64_t ntiles, int precision, hipStream_t s)
 {
     if (ntiles <= 0) return ok();
     if (ntiles > 0x7fffffff) return fail(KX_EINVAL, "production rates: too many tiles");
+    if (few) {
+        void *args[] = {(void *)&m, (void *)few, (void *)&wl};
+        return launch_few<true>(m, precision, rates_few_threads(m, ntiles), ntiles, args, s);
+    }
     if (m.wnw) {
         void *args[] = {(void *)&m, (void *)&wl};
         return launch_wide<2>(m, precision, wide_launch_waves(m, ntiles), ntiles, args, s,

@@ -288,7 +288,7 @@ bool enqueue_batch(kx_server *s, Slot &sl, const ServedMech &sm, hipGraphExec_t 
     *new_graph = nullptr;
     if (ok_launch && sl.big) {
         // one workgroup per tile, rates then transport
-        ok_launch = launch_rates_items(sm.dev, sl.d_wl, tr, prec, sl.stream) == KX_OK &&
+        ok_launch = launch_rates_items(sm.dev, nullptr, sl.d_wl, tr, prec, sl.stream) == KX_OK &&
                     (!(ops & KX_OP_TRANSPORT) ||
                      launch_transport_items(sm.dev, sl.d_wl, tt, prec, sl.stream) == KX_OK);
     } else if (ok_launch) {

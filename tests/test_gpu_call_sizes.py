@@ -84,3 +84,57 @@ def test_qss_mechanism_too_large():
             kx.production_rates(dm, *_states(5, n))
         assert e.value.code == kx.KX_EUNSUPPORTED
     dm.close()
+
+
+RATES = {"17sp": lambda: _mech(17),                    # 8 waves a tile, 119 reactions
+         "24sp": lambda: _mech(24),
+         "53X": lambda: I.make_mechanism(I.MECH_53X),  # 12 waves, every reaction form
+         "53O": lambda: I.make_mechanism(I.MECH_53O),
+         "57sp": lambda: _mech(57),                    # 16 waves
+         "128sp": lambda: _mech(128)}
+
+
+@pytest.mark.parametrize("name", ["9sp", "200sp"] + list(RATES))
+def test_rates(name):
+    """Also the points past the first tile of every CU, and the batched call."""
+    from paper_2411_02640_amd import kx
+    mech = {"9sp": lambda: I.make_mechanism(I.MECH_9),
+            "200sp": lambda: I.make_mechanism(I.MECH_200), **RATES}[name]()
+    ns, n = mech["n_species"], 16384 + 4097
+    dm = kx.Mechanism(mech, 0)
+    d = _states(ns, n)
+    d[2][:, 3] = 0.0
+    d[2][ns - 1, 3] = 1.0  # a pure species, and an absent one
+    d[2][0, 5] = 0.0
+    for prec in ("fp64", "mixed"):
+        print("[gpu-case] rates call sizes", name, prec, flush=True)
+        w = kx.production_rates(dm, *d, precision=prec)
+        assert bool(torch.isfinite(w).all())
+        for m in (1, 512, 513, 1025, 2048, 2049, 4096, 4097, 16384, 16385, 16384 + 2048, n - 1):
+            assert torch.equal(kx.production_rates(dm, *_first(d, m), precision=prec), w[:, :m]), m
+        for sizes in ((1, 700, 0, 65), (2048, 2049)):
+            sets = [_first(d, m) for m in sizes]
+            for out, m in zip(kx.batch_noalloc(dm, sets, precision=prec), sizes):
+                assert torch.equal(out[0], w[:, :m]), m
+    dm.close()
+
+
+@pytest.mark.parametrize("name", list(RATES))
+def test_small_calls_against_the_oracle(name):
+    """One point per workgroup (the oracle checks the first 70 of 700 points)."""
+    from oracle import oracle as O
+    from paper_2411_02640_amd import kx
+
+    from . import parity as PM
+    mech = RATES[name]()
+    T, p, Y = I.make_states(mech["n_species"], I.StateSpec(700, seed=92, p_atm_range=(1.0, 40.0),
+                                                           dirichlet_alpha=0.3))
+    ref, s = O.OracleMech(mech).production_rates(T[:70], p[:70], np.ascontiguousarray(Y[:, :70]))
+    dm = kx.Mechanism(mech, 0)
+    d = [torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0") for a in (T, p, Y)]
+    print("[gpu-case] rates small calls", name, flush=True)
+    r = PM.wdot_report(kx.production_rates(dm, *d)[:, :70].cpu().numpy(), ref, s)
+    assert r["ok"], r
+    w = kx.production_rates(dm, *d, precision="mixed")[:, :70].cpu().numpy()
+    assert np.all(np.abs(w - ref) <= 1e-5 * s + 1e-300)
+    dm.close()
