@@ -329,6 +329,30 @@ kx_status fail(kx_status code, const std::string &msg);
 kx_status ok();
 kx_status hip_fail(hipError_t e, const char *what);
 
+// Workgroups of `threads` threads that one launch takes: HIP allows fewer than 2^32
+// threads per grid dimension.
+inline int64_t max_workgroups(int threads) { return 0xFFFFFFFFll / threads; }
+
+// launch(first point, workgroups) over tiles of `per` of n points, as often as the
+// grid limit asks for.  A launch past the first one gets arrays that start at its
+// first point (rows still n apart) and whole tiles only: the last one ends at n, so
+// its first tile may repeat points of the launch before, with the same results.
+// (Tiles over two grid dimensions instead cost the rates kernels 2 % and a small call
+// 0.3 us, from the second workgroup index alone.)
+template <class F> kx_status launch_tiles(int64_t n, int per, int threads, F launch)
+{
+    int64_t first = 0;
+    for (int64_t left = (n + per - 1) / per; left > 0;) {
+        const int64_t now = left < max_workgroups(threads) ? left : max_workgroups(threads);
+        left -= now;
+        if (left == 0 && first > 0) first = n - now * per;
+        kx_status st = launch(first, now);
+        if (st != KX_OK) return st;
+        first += now * per;
+    }
+    return ok();
+}
+
 // Launchers (defined in the kernel translation units).
 kx_status launch_rates(const kx_mech *m, int64_t n, const double *T, const double *p,
                        const double *Y, double *wdot, int precision, hipStream_t s);

@@ -609,12 +609,15 @@ kx_status launch_qss(const kx_mech *mech, int64_t n, const double *T, const doub
         const size_t wide_lds = qss_wide_lds_bytes(m, nw);
         kx_status st = set_lds(kern, wide_lds);
         if (st != KX_OK) return st;
-        void *args[] = {(void *)&m, (void *)&n,    (void *)&T, (void *)&p,
-                        (void *)&Y, (void *)&wdot, (void *)&Cq};
-        hipError_t e =
-            hipLaunchKernel(kern, dim3((unsigned)nblk), dim3(nw * kWave), args, wide_lds, s);
-        if (e != hipSuccess) return hip_fail(e, "QSS rates kernel launch");
-        return ok();
+        return launch_tiles(n, kRow, nw * kWave, [&](int64_t i, int64_t groups) {
+            const double *Ti = T + i, *pi = p + i, *Yi = Y + i;
+            double *wi = wdot ? wdot + i : nullptr, *Ci = Cq ? Cq + i : nullptr;
+            void *args[] = {(void *)&m, (void *)&n,  (void *)&Ti, (void *)&pi,
+                            (void *)&Yi, (void *)&wi, (void *)&Ci};
+            hipError_t e = hipLaunchKernel(kern, dim3((unsigned)groups), dim3(nw * kWave), args,
+                                           wide_lds, s);
+            return e != hipSuccess ? hip_fail(e, "QSS rates kernel launch") : KX_OK;
+        });
     }
     // One wave per point.  A point's work is a chain of dependent loads and
     // barriers rather than arithmetic, so more points in flight per CU beat more

@@ -840,12 +840,15 @@ __global__ __launch_bounds__(NW *kWave, wide_waves(NW)) void rates_wide_kernel(
     rates_wide_tile<MIXED, NW>(m, n, i0, (int)min((int64_t)kRow, n - i0), T, P, Y, wdot);
 }
 
-// Batched requests, one tile per workgroup.
-template <bool MIXED, int NW>
+// Batched requests, one tile per workgroup.  YX: more tiles than one grid dimension
+// takes, kYX in each row of a two-dimensional grid (an instance of its own, see
+// launch_tiles).
+constexpr int kYX = 1 << 21;
+template <bool MIXED, int NW, bool YX>
 __global__ __launch_bounds__(NW *kWave, wide_waves(NW)) void rates_wide_items_kernel(
     MechDev m, const WorkList *__restrict__ wl)
 {
-    const int t = (int)blockIdx.x;
+    const int t = (int)(YX ? blockIdx.y * kYX + blockIdx.x : blockIdx.x);
     if (t >= wl->ntiles[0]) return;
     const int r = work_item_ballot(wl, 0, t);
     const WorkItem it = wl->items[r];
@@ -890,11 +893,12 @@ size_t wide_lds_bytes(const MechDev &m, int precision, int nw)
 int wide_launch_waves(const MechDev &m, int64_t tiles) { return tiles <= 256 ? 16 : m.wnw; }
 
 // The instance of a wide kernel for a precision and number of waves.  FORM 0:
-// direct launch, 1: work-stealing batch, 2: one tile per workgroup.
+// direct launch, 1: work-stealing batch, 2: one tile per workgroup, 3: the same over
+// two grid dimensions.
 template <int FORM, bool MIXED, int NW> const void *wide_instance()
 {
     if (FORM == 1) return (const void *)rates_wide_batch_kernel<MIXED, NW>;
-    if (FORM == 2) return (const void *)rates_wide_items_kernel<MIXED, NW>;
+    if (FORM >= 2) return (const void *)rates_wide_items_kernel<MIXED, NW, FORM == 3>;
     return (const void *)rates_wide_kernel<MIXED, NW>;
 }
 
@@ -918,7 +922,8 @@ kx_status launch_wide(const MechDev &m, int precision, int nw, int64_t grid, voi
     const size_t lds = wide_lds_bytes(m, precision, nw);
     hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute (rates)");
-    e = hipLaunchKernel(kern, dim3((unsigned)grid), dim3(nw * kWave), args, lds, s);
+    const dim3 g = FORM == 3 ? dim3(kYX, (unsigned)((grid + kYX - 1) / kYX)) : dim3((unsigned)grid);
+    e = hipLaunchKernel(kern, g, dim3(nw * kWave), args, lds, s);
     if (e != hipSuccess) return hip_fail(e, what);
     return ok();
 }
@@ -1082,9 +1087,13 @@ kx_status launch_rates(const kx_mech *mech, int64_t n, const double *T, const do
         const int64_t nblk = (body + kRow - 1) / kRow;
         if (nblk > 0x7fffffff) return fail(KX_EINVAL, "production rates: n too large");
         if (body) {  // whole tiles if there is a tail
-            void *args[] = {(void *)&m, (void *)&n, (void *)&T, (void *)&p, (void *)&Y, (void *)&wdot};
-            kx_status st = launch_wide<0>(m, precision, wide_launch_waves(m, nblk), nblk, args, s,
-                                          "rates kernel launch");
+            const int nw = wide_launch_waves(m, nblk);
+            kx_status st = launch_tiles(body, kRow, nw * kWave, [&](int64_t i, int64_t groups) {
+                const double *Ti = T + i, *pi = p + i, *Yi = Y + i;
+                double *wi = wdot + i;
+                void *args[] = {(void *)&m, (void *)&n, (void *)&Ti, (void *)&pi, (void *)&Yi, (void *)&wi};
+                return launch_wide<0>(m, precision, nw, groups, args, s, "rates kernel launch");
+            });
             if (st != KX_OK || !tail) return st;
         }
         T += body, p += body, Y += body, wdot += body;
@@ -1104,11 +1113,12 @@ kx_status launch_rates(const kx_mech *mech, int64_t n, const double *T, const do
     auto kern = precision == KX_MIXED ? pick(std::true_type{}) : pick(std::false_type{});
     kx_status st = set_lds(kern, lds);
     if (st != KX_OK) return st;
-    hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(kWave), lds, s, m, n, T, p, Y, wdot,
-                       tp);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e, "rates kernel launch");
-    return ok();
+    return launch_tiles(n, tp, kWave, [&](int64_t i, int64_t groups) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(kWave), lds, s, m, n, T + i, p + i,
+                           Y + i, wdot + i, tp);
+        hipError_t e = hipGetLastError();
+        return e != hipSuccess ? hip_fail(e, "rates kernel launch") : KX_OK;
+    });
 }
 
 namespace {
@@ -1144,9 +1154,13 @@ kx_status launch_rates_items(const MechDev &m, const FewDev *few, const WorkList
     }
     if (m.wnw) {
         void *args[] = {(void *)&m, (void *)&wl};
-        return launch_wide<2>(m, precision, wide_launch_waves(m, ntiles), ntiles, args, s,
-                              "rates items kernel launch");
+        const int nw = wide_launch_waves(m, ntiles);
+        return ntiles <= max_workgroups(nw * kWave)
+                   ? launch_wide<2>(m, precision, nw, ntiles, args, s, "rates items kernel launch")
+                   : launch_wide<3>(m, precision, nw, ntiles, args, s, "rates items kernel launch");
     }
+    if (ntiles > max_workgroups(kWave))
+        return fail(KX_EINVAL, "production rates: too many tiles");
     const int tp = rates_tile_points(m);
     const size_t lds = rates_lds_bytes(m, tp);
     if (lds > 160 * 1024)

@@ -1216,6 +1216,12 @@ kx_status prepare_transport_batch(const MechDev &m, int precision)
 }
 
 namespace {
+// The arrays of one launch (kernel arguments).
+struct TransportPtrs {
+    const double *T, *p, *Y;
+    double *mu, *lam, *Dmix;
+};
+
 template <class F>
 kx_status go_transport(const MechDev &m, int64_t n, const double *T, const double *p,
                        const double *Y, double *mu, double *lam, double *Dmix, bool sym,
@@ -1246,20 +1252,23 @@ kx_status go_transport(const MechDev &m, int64_t n, const double *T, const doubl
         const int np = mfma_np<F>(m);
         const int64_t nblk = (n + np - 1) / np;
         if (nblk > 0x7fffffff) return fail(KX_EINVAL, "transport: n too large");
-        void *args[] = {(void *)&m, (void *)&n, (void *)&T, (void *)&p, (void *)&Y,
-                        (void *)&mu, (void *)&lam, (void *)&Dmix};
-        hipError_t e = hipLaunchKernel(mfma_kernel<F, 0>(m), dim3((unsigned)nblk),
-                                       dim3(mfma_nt<F>(m)), args, lds, s);
-        if (e != hipSuccess) return hip_fail(e, "transport kernel launch");
-        return ok();
+        return launch_tiles(n, np, mfma_nt<F>(m), [&](int64_t i, int64_t groups) {
+            TransportPtrs a{T + i, p + i, Y + i, mu + i, lam + i, Dmix + i};
+            void *args[] = {(void *)&m, (void *)&n, &a.T, &a.p, &a.Y, &a.mu, &a.lam, &a.Dmix};
+            hipError_t e = hipLaunchKernel(mfma_kernel<F, 0>(m), dim3((unsigned)groups),
+                                           dim3(mfma_nt<F>(m)), args, lds, s);
+            return e != hipSuccess ? hip_fail(e, "transport kernel launch") : KX_OK;
+        });
     }
     const int64_t nblk = (n + kWave - 1) / kWave;
     if (nblk > 0x7fffffff) return fail(KX_EINVAL, "transport: n too large");
     kx_status st = rows_prepare<F, 0>(m);
     if (st != KX_OK) return st;
-    void *args[] = {(void *)&m, (void *)&n,  (void *)&T,   (void *)&p,
-                    (void *)&Y, (void *)&mu, (void *)&lam, (void *)&Dmix};
-    return rows_launch<F, 0>(m, nblk, args, s, "transport kernel launch");
+    return launch_tiles(n, kWave, rows_waves(m) * kWave, [&](int64_t i, int64_t groups) {
+        TransportPtrs a{T + i, p + i, Y + i, mu + i, lam + i, Dmix + i};
+        void *args[] = {(void *)&m, (void *)&n, &a.T, &a.p, &a.Y, &a.mu, &a.lam, &a.Dmix};
+        return rows_launch<F, 0>(m, groups, args, s, "transport kernel launch");
+    });
 }
 
 template <class F>
@@ -1281,7 +1290,8 @@ template <class F>
 kx_status go_transport_items(const MechDev &m, const WorkList *wl, int64_t ntiles, hipStream_t s)
 {
     if (ntiles <= 0) return ok();
-    if (ntiles > 0x7fffffff) return fail(KX_EINVAL, "transport: too many tiles");
+    if (ntiles > max_workgroups(use_mfma(m) ? mfma_nt<F>(m) : rows_waves(m) * kWave))
+        return fail(KX_EINVAL, "transport: too many tiles");
     if (use_mfma(m)) {
         size_t lds = 0;
         kx_status st = mfma_prepare<F, 2>(m, &lds);
@@ -1336,11 +1346,13 @@ kx_status launch_thermo(const kx_mech *mech, int64_t n, const double *T, const d
 {
     const int64_t nblk = (n + kWave - 1) / kWave;
     if (nblk > 0x7fffffff) return fail(KX_EINVAL, "thermo: n too large");
-    hipLaunchKernelGGL(thermo_kernel, dim3((unsigned)nblk), dim3(kBlock), 0, s, mech->dev, n, T, Y,
-                       cpk, hk, cpmix);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e, "thermo kernel launch");
-    return ok();
+    return launch_tiles(n, kWave, kBlock, [&](int64_t i, int64_t groups) {
+        hipLaunchKernelGGL(thermo_kernel, dim3((unsigned)groups), dim3(kBlock), 0, s, mech->dev, n,
+                           T + i, Y + i, cpk ? cpk + i : cpk, hk ? hk + i : hk,
+                           cpmix ? cpmix + i : cpmix);
+        hipError_t e = hipGetLastError();
+        return e != hipSuccess ? hip_fail(e, "thermo kernel launch") : KX_OK;
+    });
 }
 
 }  // namespace kx
