@@ -440,7 +440,8 @@ void jac_tables(const kx_mech_desc *d, const std::vector<int> &perm, const std::
                 const std::vector<DevAux> &aux, const std::vector<DevEff> &eff, JacTables &t)
 {
     const int ns = d->n_species, nr = d->n_reactions;
-    if (ns > kJacBlockSpecies || nr == 0 || d->qss) return;
+    if (ns > kJacBlockSpecies || nr == 0) return;
+    if (d->qss && std::any_of(d->qss, d->qss + ns, [](int32_t q) { return q != 0; })) return;
     const int dense = ns;  // pseudo column
     // contributions to (row, column), |nu| times: slot derivative and sign
     struct Item {
