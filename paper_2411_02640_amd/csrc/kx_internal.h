@@ -24,6 +24,9 @@ constexpr int kMaxQss = 64;          // QSS species per mechanism (one wave of r
 constexpr int kWideMaxSpecies = 128; // one-lane-per-point kernels (species rows in LDS)
 constexpr int kWideQss = 7;           // QSS species of the one-lane-per-point kernel
 constexpr int kJacBlockSpecies = 128;   // Jacobian in row blocks
+constexpr int kMfmaMinSpecies = 24;     // matrix-core transport (1/D_kj fits): below, the padded
+                                        // 16 x 4 tiles are mostly empty and the vector-ALU
+                                        // kernel is faster
 constexpr int kChunkMax = 192;       // reactions per chunk of the gather lists, at most
 
 // Reaction flags.

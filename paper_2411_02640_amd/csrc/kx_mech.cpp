@@ -725,63 +725,13 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
     if (aux.empty()) aux.resize(1);
     if (plog.empty()) plog.resize(1);
 
-    // ---- species-major gather lists per reaction chunk.  Each species lists
-    // the chunk slots of the reactions that produce it (+q, once per unit of
-    // net nu) and of those that consume it (-q); both lists are padded to a
-    // whole number of eight-entry groups common to all lanes, and a group is
-    // eight 32-bit LDS offsets (32 bytes per lane, so lane k reads it with a
-    // pair of coalesced 16-byte loads).  The rates of progress of two points sit
-    // side by side in LDS, so one offset addresses both.
+    // ---- chunks of the species-major gather lists (below)
     const int chunk = std::max(kWave, std::min(kChunkMax, (nr + kWave - 1) / kWave * kWave));
     const int nchunks = std::max(1, (nr + chunk - 1) / chunk);
-    // species per lane of the species phases: 1, 2 or 4 (the kernels are
-    // instantiated for these), so lists are laid out for 64 * gpass lanes
+    // species per lane of the species phases: 1, 2 or 4, so lists are laid out for
+    // 64 * gpass lanes
     const int gpass = ns <= kWave ? 1 : (ns <= 2 * kWave ? 2 : 4);
     const int gw = kWave * gpass;
-    std::vector<int32_t> gpos(nchunks), gneg(nchunks), goff(nchunks);
-    std::vector<uint32_t> gent;  // 8 per (group, lane)
-    size_t ngroups = 0;
-    for (int c = 0; c < nchunks; ++c) {
-        std::vector<std::vector<uint32_t>> pos(gw), neg(gw);
-        for (int s = c * chunk; s < std::min(nr, (c + 1) * chunk); ++s) {
-            const int i = perm[s];
-            std::vector<std::pair<int, int>> net;  // (species, nu'' - nu')
-            auto addnu = [&](int k, int v) {
-                for (auto &pr : net)
-                    if (pr.first == k) { pr.second += v; return; }
-                net.push_back({k, v});
-            };
-            for (int e = d->reac_ptr[i]; e < d->reac_ptr[i + 1]; ++e)
-                addnu(d->reac_sp[e], -d->reac_nu[e]);
-            for (int e = d->prod_ptr[i]; e < d->prod_ptr[i + 1]; ++e)
-                addnu(d->prod_sp[e], d->prod_nu[e]);
-            const uint32_t slot = (uint32_t)(16 * (s - c * chunk));
-            for (auto &pr : net)
-                for (int u = 0; u < std::abs(pr.second); ++u)
-                    (pr.second > 0 ? pos : neg)[pr.first].push_back(slot);
-        }
-        size_t lp = 0, ln = 0;
-        for (int k = 0; k < gw; ++k) {
-            lp = std::max(lp, pos[k].size());
-            ln = std::max(ln, neg[k].size());
-        }
-        gpos[c] = (int32_t)((lp + 7) / 8);
-        gneg[c] = (int32_t)((ln + 7) / 8);
-        goff[c] = (int32_t)ngroups;
-        const uint32_t pad = (uint32_t)(16 * chunk);  // the zero slot
-        for (int side = 0; side < 2; ++side) {
-            const auto &lists = side ? neg : pos;
-            const int groups = side ? gneg[c] : gpos[c];
-            for (int g = 0; g < groups; ++g)
-                for (int k = 0; k < gw; ++k)
-                    for (int u = 0; u < 8; ++u) {
-                        const size_t e = (size_t)g * 8 + u;
-                        gent.push_back(e < lists[k].size() ? lists[k][e] : pad);
-                    }
-            ngroups += groups;
-        }
-    }
-    if (gent.empty()) gent.resize(8, 0);
 
     // ---- QSS species: index per species, per reaction (kernel order) the QSS
     // species of either side, and per QSS species the reactions of its balance
@@ -899,8 +849,9 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
         s.inv_W = 1.0 / W[k];
         spv[k] = s;
     }
-    std::vector<double> gsoa((size_t)((ns + kWave - 1) / kWave) * 16 * kWave, 0.0);
-    for (int k = 0; k < ns; ++k) {
+    std::vector<double> gsoa(ns > kWideMaxSpecies ? (size_t)((ns + kWave - 1) / kWave) * 16 * kWave
+                                                  : 0);
+    for (int k = 0; k < ns && !gsoa.empty(); ++k) {
         double *g = gsoa.data() + (size_t)(k / kWave) * 16 * kWave + k % kWave;
         for (int e = 0; e < 7; ++e) {
             g[e * kWave] = spv[k].g_lo[e];
@@ -920,6 +871,7 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
     WideShape wsh[3];
     std::vector<int32_t> wmap[3];
     std::vector<uint32_t> wstart[3], wgat[3];
+    int wsame[3] = {0, 1, 2};
     std::vector<int32_t> fptr;
     std::vector<uint32_t> fent;
     int nplog = 0;
@@ -995,7 +947,11 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
         wsh[1].nw = 16;
         wsh[2] = wide_shape_alone(ns, nr);
         const SpeciesRows rows = species_rows(d, perm);
-        for (int v = 0; v < 3; ++v) wide_gather(rows, wsh[v], wmap[v], wstart[v], wgat[v]);
+        for (int v = 0; v < 3; ++v) {
+            for (wsame[v] = 0; wsame[v] < v; ++wsame[v])  // an equal shape's tables serve both
+                if (wsh[wsame[v]].nw == wsh[v].nw && wsh[wsame[v]].chunk == wsh[v].chunk) break;
+            if (wsame[v] == v) wide_gather(rows, wsh[v], wmap[v], wstart[v], wgat[v]);
+        }
         few_lists(rows, nr, ws.chunk, fptr, fent);
     }
     if (wrx.empty()) wrx.resize(1), wrx32.resize(1);
@@ -1006,16 +962,74 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
     JacTables jt;
     jac_tables(d, perm, rx, aux, eff, jt);
 
+    // ---- species-major gather lists per reaction chunk, where a kernel reads them:
+    // rates above kWideMaxSpecies, QSS rates by one wave per point, the Jacobian by one
+    // row per thread.  Each species lists
+    // the chunk slots of the reactions that produce it (+q, once per unit of
+    // net nu) and of those that consume it (-q); both lists are padded to a
+    // whole number of eight-entry groups common to all lanes, and a group is
+    // eight 32-bit LDS offsets (32 bytes per lane, so lane k reads it with a
+    // pair of coalesced 16-byte loads).  The rates of progress of two points sit
+    // side by side in LDS, so one offset addresses both.
+    std::vector<int32_t> gpos(nchunks), gneg(nchunks), goff(nchunks);
+    std::vector<uint32_t> gent;  // 8 per (group, lane)
+    size_t ngroups = 0;
+    const bool lists = ns > kWideMaxSpecies || (nq > 0 ? qlist.empty() : jt.rows == 0);
+    for (int c = 0; c < nchunks && lists; ++c) {
+        std::vector<std::vector<uint32_t>> pos(gw), neg(gw);
+        for (int s = c * chunk; s < std::min(nr, (c + 1) * chunk); ++s) {
+            const int i = perm[s];
+            std::vector<std::pair<int, int>> net;  // (species, nu'' - nu')
+            auto addnu = [&](int k, int v) {
+                for (auto &pr : net)
+                    if (pr.first == k) { pr.second += v; return; }
+                net.push_back({k, v});
+            };
+            for (int e = d->reac_ptr[i]; e < d->reac_ptr[i + 1]; ++e)
+                addnu(d->reac_sp[e], -d->reac_nu[e]);
+            for (int e = d->prod_ptr[i]; e < d->prod_ptr[i + 1]; ++e)
+                addnu(d->prod_sp[e], d->prod_nu[e]);
+            const uint32_t slot = (uint32_t)(16 * (s - c * chunk));
+            for (auto &pr : net)
+                for (int u = 0; u < std::abs(pr.second); ++u)
+                    (pr.second > 0 ? pos : neg)[pr.first].push_back(slot);
+        }
+        size_t lp = 0, ln = 0;
+        for (int k = 0; k < gw; ++k) {
+            lp = std::max(lp, pos[k].size());
+            ln = std::max(ln, neg[k].size());
+        }
+        gpos[c] = (int32_t)((lp + 7) / 8);
+        gneg[c] = (int32_t)((ln + 7) / 8);
+        goff[c] = (int32_t)ngroups;
+        const uint32_t pad = (uint32_t)(16 * chunk);  // the zero slot
+        for (int side = 0; side < 2; ++side) {
+            const auto &lists = side ? neg : pos;
+            const int groups = side ? gneg[c] : gpos[c];
+            for (int g = 0; g < groups; ++g)
+                for (int k = 0; k < gw; ++k)
+                    for (int u = 0; u < 8; ++u) {
+                        const size_t e = (size_t)g * 8 + u;
+                        gent.push_back(e < lists[k].size() ? lists[k][e] : pad);
+                    }
+            ngroups += groups;
+        }
+    }
+    if (gent.empty()) gent.resize(8, 0);
+
     // ---- transport tables
     const int nkb = (ns + kKB - 1) / kKB;
     std::vector<double> visc((size_t)ns * order), cond((size_t)ns * order);
     std::memcpy(visc.data(), d->visc_fit, visc.size() * sizeof(double));
     std::memcpy(cond.data(), d->cond_fit, cond.size() * sizeof(double));
-    std::vector<double> wilke((size_t)nkb * ns * kKB, 0.0), wq(ns);
+    // the matrix-core kernel reads fragments of the pair tables (below), the others
+    // the pair tables themselves
+    const bool mfma = d->diff_fit_kind == 1 && ns >= kMfmaMinSpecies;
+    std::vector<double> wilke(mfma ? 1 : (size_t)nkb * ns * kKB, 0.0), wq(ns);
     for (int k = 0; k < ns; ++k) wq[k] = std::pow(W[k], 0.25);
-    std::vector<double> dfit((size_t)nkb * ns * kKB * order, 0.0);
+    std::vector<double> dfit(mfma ? 1 : (size_t)nkb * ns * kKB * order, 0.0);
     std::vector<double> ddiag((size_t)ns * order);
-    for (int kb = 0; kb < nkb; ++kb)
+    for (int kb = 0; kb < nkb && !mfma; ++kb)
         for (int j = 0; j < ns; ++j)
             for (int kk = 0; kk < kKB; ++kk) {
                 const int k = kb * kKB + kk;
@@ -1040,7 +1054,6 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
 
     // ---- MFMA fragments of the quadratic sums (fits of 1/D_kj only)
     const int mblk = (ns + 15) / 16, kstep = (ns + 3) / 4;
-    const bool mfma = d->diff_fit_kind == 1;
     std::vector<double> gfrag, c1frag;
     if (mfma) {
         gfrag.assign((size_t)order * mblk * kstep * 64, 0.0);
@@ -1081,6 +1094,7 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
         o_wmap[v] = add_vec(b, wmap[v]);
         o_wstart[v] = add_vec(b, wstart[v]);
         o_wgat[v] = add_vec(b, wgat[v]);
+        o_wmap[v] = o_wmap[wsame[v]], o_wstart[v] = o_wstart[wsame[v]], o_wgat[v] = o_wgat[wsame[v]];
     }
     const size_t o_W = add_vec(b, W), o_visc = add_vec(b, visc), o_cond = add_vec(b, cond);
     const size_t o_wil = add_vec(b, wilke), o_df = add_vec(b, dfit), o_dd = add_vec(b, ddiag);

@@ -1159,9 +1159,6 @@ template <class F> size_t mfma_lds(const MechDev &m)
     });
 }
 
-// Below about two dozen species the padded 16 x 4 MFMA tiles are mostly empty
-// and the vector-ALU kernel is faster.
-constexpr int kMfmaMinSpecies = 24;
 bool use_mfma(const MechDev &m)
 {
     return m.diff_kind == 1 && m.gfrag != nullptr && m.ns >= kMfmaMinSpecies;

@@ -19,3 +19,13 @@ def test_all_zero_qss_flags(spec):
     mech = I.make_mechanism(spec)
     flagged = dict(mech, qss=np.zeros(mech["n_species"], np.int32))
     assert _bytes(flagged) == _bytes(dict(mech, qss=None))
+
+
+@pytest.mark.parametrize("spec,most", [(I.MECH_9, 55312), (I.MECH_53, 570640),
+                                       (I.MECH_100, 1786128), (I.MECH_200, 6442000)],
+                         ids=lambda v: getattr(v, "name", str(v)))
+def test_no_tables_that_no_kernel_reads(spec, most):
+    """The tables of the one-lane-per-point kernels and the row-block Jacobian replace
+    those of the kernels they replaced: a mechanism (and a server's copy of it) takes
+    no more memory than with the former ones."""
+    assert _bytes(I.make_mechanism(spec)) <= most
