@@ -99,7 +99,7 @@ extern "C" kx_status kx_batch_noalloc(const kx_mech *mech, int32_t ops, int32_t 
     int64_t points = 0;
     for (int r = 0; r < nitems; ++r) points += std::max<int64_t>(items[r].n, 0);
     const int rtp = rates_items_tile_points(mech->dev, points);
-    const int ttp = transport_tile_points(mech->dev, precision);
+    const int ttp = transport_items_tile_points(mech->dev, precision, points);
     BatchArgs a;
     std::memset(&a, 0, sizeof a);
     int64_t tiles_r = 0, tiles_t = 0;
@@ -155,7 +155,7 @@ extern "C" kx_status kx_batch_noalloc(const kx_mech *mech, int32_t ops, int32_t 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "kx_batch_noalloc: setup kernel launch");
     st = launch_rates_items(mech->dev, rtp == 1 ? &mech->few : nullptr, wl, tiles_r, precision, stream);
-    if (st == KX_OK && tr) st = launch_transport_items(mech->dev, wl, tiles_t, precision, stream);
+    if (st == KX_OK && tr) st = launch_transport_items(mech->dev, wl, tiles_t, points, precision, stream);
     if (st != KX_OK) return st;
     return ok();
 }

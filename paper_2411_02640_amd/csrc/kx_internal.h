@@ -377,6 +377,7 @@ int rates_tile_points(const MechDev &m);
 // The same for launch_rates_items with `points` points in all (one-point tiles for
 // few points).
 int rates_items_tile_points(const MechDev &m, int64_t points);
+int transport_items_tile_points(const MechDev &m, int precision, int64_t points);
 int transport_tile_points(const MechDev &m, int precision);
 // Batched (work-list) launches; `counter` must be zero at launch.
 // prepare_rates_batch sets the kernel's dynamic-LDS limit (call it before
@@ -384,11 +385,12 @@ int transport_tile_points(const MechDev &m, int precision);
 kx_status prepare_rates_batch(const MechDev &m, int precision);
 // One workgroup per tile of the work list (`ntiles` = wl->ntiles[0] for rates,
 // wl->ntiles[1] for transport, known to the host that wrote the list); no
-// counters.  few: the list is cut in tiles of one point (null: rates_tile_points).
+// counters.  points: the items' points together (transport_items_tile_points).  few:
+// the list is cut in tiles of one point (null: rates_tile_points).
 kx_status launch_rates_items(const MechDev &m, const FewDev *few, const WorkList *wl,
                              int64_t ntiles, int precision, hipStream_t s);
 kx_status launch_transport_items(const MechDev &m, const WorkList *wl, int64_t ntiles,
-                                 int precision, hipStream_t s);
+                                 int64_t points, int precision, hipStream_t s);
 kx_status launch_rates_batch(const MechDev &m, const WorkList *wl, int *counter, int precision,
                              int grid, hipStream_t s);
 kx_status launch_transport_batch(const MechDev &m, const WorkList *wl, int *counter,

@@ -256,7 +256,11 @@ bool enqueue_batch(kx_server *s, Slot &sl, const ServedMech &sm, hipGraphExec_t 
     std::memset(&w, 0, sizeof w);
     w.nitems = (int)batch.size();
     const int tpr = rates_tile_points(sm.dev);
-    const int tpt = transport_tile_points(sm.dev, prec);
+    int64_t points = 0;  // of the requests with transport
+    for (const Req *q : batch)
+        if (q->r.ops & KX_OP_TRANSPORT) points += q->r.n;
+    const int tpt = sl.big ? transport_items_tile_points(sm.dev, prec, points)
+                           : transport_tile_points(sm.dev, prec);
     int tr = 0, tt = 0;
     for (size_t r = 0; r < batch.size(); ++r) {
         const Req *q = batch[r];
@@ -290,7 +294,7 @@ bool enqueue_batch(kx_server *s, Slot &sl, const ServedMech &sm, hipGraphExec_t 
         // one workgroup per tile, rates then transport
         ok_launch = launch_rates_items(sm.dev, nullptr, sl.d_wl, tr, prec, sl.stream) == KX_OK &&
                     (!(ops & KX_OP_TRANSPORT) ||
-                     launch_transport_items(sm.dev, sl.d_wl, tt, prec, sl.stream) == KX_OK);
+                     launch_transport_items(sm.dev, sl.d_wl, tt, points, prec, sl.stream) == KX_OK);
     } else if (ok_launch) {
         if (!graph) {
             // captured when the mechanism was added; built here only if that

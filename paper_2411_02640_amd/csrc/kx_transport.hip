@@ -622,14 +622,27 @@ struct MfmaPoint {
     double u, xf, wbar, pr;
 };
 
-template <class F, int NP, int NT>
-__host__ __device__ constexpr size_t mfma_lds_bytes_np(int kstep)
+// A tile's shape: points, threads, and how its sums over species are cut into
+// partial sums -- the prologue's by j mod PG, mu's by row block mod MC -- which with
+// their order fix the bits.  A thread of a shape with fewer groups (or row blocks in
+// flight) keeps several partial sums, so that two shapes of a mechanism give the same.
+template <int NP_, int NT_, int PG_ = NT_ / NP_, int MC_ = 0> struct MfmaShape {
+    static constexpr int NP = NP_, NT = NT_, PG = PG_;
+    // a wave takes NB of the 16-point column blocks, WC waves share a row block, WR
+    // row blocks are in flight
+    static constexpr int WC = NT == 512 && NP == 64 ? 2 : 1, NB = NP / 16 / WC;
+    static constexpr int WR = NT / kWave / WC, MC = MC_ ? MC_ : WR;
+    static constexpr int NG = NT / NP;  // species groups of the prologue
+    static_assert((PG == NG || PG == 2 * NG) && MC % WR == 0 && MC <= PG, "partial sums");
+};
+
+template <class F, class S> constexpr size_t mfma_lds_bytes(int kstep)
 {
-    // X and rho tiles, point table, partial sums (per (group, point) in the
-    // prologue: 3 sums, and the normalisation sum in a slot of its own; 16 per
+    // X and rho tiles, point table, partial sums (per (class, point) in the
+    // prologue: 3 sums, and the normalisation sum in a slot of its own; 4 MC per
     // point for mu)
-    return 2 * (size_t)(4 * kstep) * (NP + kMfmaPad) * sizeof(F) + NP * sizeof(MfmaPoint) +
-           (size_t)4 * NT * sizeof(double);
+    return 2 * (size_t)(4 * kstep) * (S::NP + kMfmaPad) * sizeof(F) + S::NP * sizeof(MfmaPoint) +
+           (size_t)4 * S::PG * S::NP * sizeof(double);
 }
 
 // `tid` is threadIdx.x; the batch kernel passes it through an opaque move in
@@ -637,7 +650,7 @@ __host__ __device__ constexpr size_t mfma_lds_bytes_np(int kstep)
 // not hoisted out of the loop (kept live across tiles they cost the kernel
 // its occupancy).  LOOP: the workgroup takes another tile after this one (its
 // LDS is then reused).
-template <class F, int NP, int NT, int ORDER, bool LOOP>
+template <class F, class Sh, int ORDER, bool LOOP>
 __device__ __forceinline__ void transport_mfma_tile(int tid, const MechDev &m, int64_t n,
                                                     int64_t base,
                                                     const double *__restrict__ T,
@@ -650,11 +663,8 @@ __device__ __forceinline__ void transport_mfma_tile(int tid, const MechDev &m, i
     using Tb = Tabs<F>;
     using MF = Mfma<F>;
     using V = typename MF::V;
-    constexpr int NW = NT / kWave;       // waves
-    constexpr int NBT = NP / 16;         // 16-point column blocks of the tile
-    // a wave takes NB of them, WC waves side by side share a row block
-    constexpr int WC = NT == 512 && NP == 64 ? 2 : 1, NB = NBT / WC, WR = NW / WC;
-    constexpr int NG = NT / NP;          // species groups of the prologue
+    constexpr int NP = Sh::NP, NT = Sh::NT, NG = Sh::NG, NB = Sh::NB, WC = Sh::WC, WR = Sh::WR;
+    constexpr int PH = Sh::PG / NG, MH = Sh::MC / WR;  // partial sums per thread
     constexpr int LD = NP + kMfmaPad;    // LDS row stride of the tiles
     const int ns = m.ns, order = ORDER > 0 ? ORDER : m.fit_order;
     const int KS = m.kstep, MB = m.mblk, Kp = 4 * KS;
@@ -664,8 +674,8 @@ __device__ __forceinline__ void transport_mfma_tile(int tid, const MechDev &m, i
     F *Xs = reinterpret_cast<F *>(smem_d);
     F *Rs = Xs + (size_t)Kp * LD;
     MfmaPoint *pt = reinterpret_cast<MfmaPoint *>(Rs + (size_t)Kp * LD);
-    double *part = reinterpret_cast<double *>(pt + NP);  // [NG][3][NP], then mu's [16][NP]
-    double *part1 = part + 3 * NT;                   // [NG][NP]: sum of Y_j / W_j
+    double *part = reinterpret_cast<double *>(pt + NP);  // [PG][3][NP], then mu's [4 MC][NP]
+    double *part1 = part + 3 * Sh::PG * NP;              // [PG][NP]: sum of Y_j / W_j
 
     // ---- prologue: thread = (point p, species group g)
     const int p = t % NP;
@@ -684,20 +694,26 @@ __device__ __forceinline__ void transport_mfma_tile(int tid, const MechDev &m, i
         const int j = g + NG * q;
         yw[q] = j < ns ? Y[(int64_t)j * n + ip] : 0.0;
     }
-    double s = 0.0;
+    // the partial sums in scalars: as arrays they change the code of the prologue
+    // also where there is one (200 species FP64 1.3 % slower)
+    double s = 0.0, sB = 0.0;
 #pragma unroll
     for (int q = 0; q < kJmax; ++q) {
         const int j = g + NG * q;
         if (j < ns) {
             yw[q] *= m.sp[j].inv_W;  // Y_j / W_j
-            s += yw[q];
+            if (PH > 1 && q % 2)
+                sB += yw[q];
+            else
+                s += yw[q];
         }
     }
     part1[g * NP + p] = s;
+    if (PH > 1) part1[(g + NG) * NP + p] = sB;
     __syncthreads();
     double sYW = 0.0;
 #pragma unroll
-    for (int q = 0; q < NG; ++q) sYW += part1[q * NP + p];
+    for (int q = 0; q < Sh::PG; ++q) sYW += part1[q * NP + p];
     const double xf = krcp(sYW);
     if (t < NP) {
         MfmaPoint P;
@@ -707,18 +723,26 @@ __device__ __forceinline__ void transport_mfma_tile(int tid, const MechDev &m, i
         P.pr = Pp[ip] * (1.0 / kPatm);
         pt[p] = P;
     }
-    double wb = 0.0, s1 = 0.0, s2 = 0.0;
+    double wb = 0.0, s1 = 0.0, s2 = 0.0, wbB = 0.0, s1B = 0.0, s2B = 0.0;
 #pragma unroll
     for (int q = 0; q < kJmax; ++q) {
         const int j = g + NG * q;
         if (j >= Kp) break;
         if (j < ns) {
             const double X = yw[q] * xf;  // FP64 X_j for W-bar and the Mathur sums
-            wb = fma(X, m.W[j], wb);
+            if (PH > 1 && q % 2)
+                wbB = fma(X, m.W[j], wbB);
+            else
+                wb = fma(X, m.W[j], wb);
             const F lj = NP == 64 ? horner<ORDER>(Tb::cond(m) + j * order, (F)up, order)
                                   : horner_v<ORDER>(Tb::cond(m) + j * order, (F)up, order);
-            s1 = fma(X, (double)lj, s1);
-            s2 = fma(X, (double)rcp_mfma(lj), s2);
+            if (PH > 1 && q % 2) {
+                s1B = fma(X, (double)lj, s1B);
+                s2B = fma(X, (double)rcp_mfma(lj), s2B);
+            } else {
+                s1 = fma(X, (double)lj, s1);
+                s2 = fma(X, (double)rcp_mfma(lj), s2);
+            }
             const F ej = NP == 64 ? horner<ORDER>(Tb::visc(m) + j * order, (F)up, order)
                                   : horner_v<ORDER>(Tb::visc(m) + j * order, (F)up, order);
             Xs[(size_t)j * LD + p] = (F)X;
@@ -731,11 +755,17 @@ __device__ __forceinline__ void transport_mfma_tile(int tid, const MechDev &m, i
     part[(g * 3 + 0) * NP + p] = wb;
     part[(g * 3 + 1) * NP + p] = s1;
     part[(g * 3 + 2) * NP + p] = s2;
+    if (PH > 1) {
+        double *pg = part + (g + NG) * 3 * NP + p;
+        pg[0] = wbB;
+        pg[NP] = s1B;
+        pg[2 * NP] = s2B;
+    }
     __syncthreads();
     if (t < NP && base + p < n) {
         double a1 = 0.0, a2 = 0.0;
 #pragma unroll
-        for (int q = 0; q < NG; ++q) {
+        for (int q = 0; q < Sh::PG; ++q) {
             a1 += part[(q * 3 + 1) * NP + p];
             a2 += part[(q * 3 + 2) * NP + p];
         }
@@ -749,9 +779,7 @@ __device__ __forceinline__ void transport_mfma_tile(int tid, const MechDev &m, i
     F uc[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) uc[nb] = (F)pt[16 * nb + col].u;
-    double mup[NB];
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) mup[nb] = 0.0;
+    double mup[MH][NB] = {};
     const F *gf = MF::gfrag(m), *cf = MF::c1frag(m);
     constexpr int MO = ORDER > 0 ? ORDER : kMaxFitOrder;  // A fragments per K-step
     const size_t ostride = (size_t)MB * KS * 64;           // between fit orders
@@ -833,7 +861,14 @@ __device__ __forceinline__ void transport_mfma_tile(int tid, const MechDev &m, i
             const MfmaPoint P = pt[pp];
             double wbar = 0.0;
 #pragma unroll
-            for (int q = 0; q < NG; ++q) wbar += part[(q * 3 + 0) * NP + pp];
+            for (int q = 0; q < Sh::PG; ++q) wbar += part[(q * 3 + 0) * NP + pp];
+            double own = 0.0;  // this row block's class of mu (several per thread)
+            if constexpr (MH > 1) {
+#pragma unroll
+                for (int h = 0; h < MH; ++h)
+                    if (mb / WR % MH == h) own = mup[h][nb];
+            }
+            double &mue = MH > 1 ? own : mup[0][nb];
             double yk[4];
             if (!F64) {
                 const int64_t ic = min(i, n - 1);
@@ -847,7 +882,7 @@ __device__ __forceinline__ void transport_mfma_tile(int tid, const MechDev &m, i
                 const F rho = Rs[(size_t)k * LD + pp];
                 const F den = fma(fma(A[nb][e], rho, (F)2 * B[nb][e]), rho, C[nb][e]);
                 const double Zk = F64 ? (double)Xs[(size_t)k * LD + pp] : yk[e] * P.xf;
-                mup[nb] = fma(Zk, (double)(rf[e] * rcp_mfma(den)), mup[nb]);
+                mue = fma(Zk, (double)(rf[e] * rcp_mfma(den)), mue);
                 double D;
                 if (S[nb][e] == (F)0) {
                     // no other species present: D_km -> D_kk
@@ -858,17 +893,25 @@ __device__ __forceinline__ void transport_mfma_tile(int tid, const MechDev &m, i
                 }
                 if (i < n) Dmix[(int64_t)k * n + i] = D;
             }
+            if constexpr (MH > 1) {
+#pragma unroll
+                for (int h = 0; h < MH; ++h)
+                    if (mb / WR % MH == h) mup[h][nb] = own;
+            }
         }
     }
-    // mu: 4 WR partial sums per point (waves x 4 row groups), fixed order
+    // mu: 4 MC partial sums per point (row block classes x 4 row groups), fixed order
     __syncthreads();
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) part[(wr * 4 + jr) * NP + 16 * nb + col] = mup[nb];
+    for (int h = 0; h < MH; ++h)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+            part[((wr + WR * h) * 4 + jr) * NP + 16 * nb + col] = mup[h][nb];
     __syncthreads();
     if (t < NP && base + t < n) {
         double v = 0.0;
 #pragma unroll
-        for (int q = 0; q < 4 * WR; ++q) v += part[q * NP + t];
+        for (int q = 0; q < 4 * Sh::MC; ++q) v += part[q * NP + t];
         mu[base + t] = v;
     }
     if (LOOP) __syncthreads();  // LDS reused by the next tile
@@ -880,8 +923,8 @@ template <class F> constexpr int mfma_waves(int nt, int np)
     return nt == 512 && (np == 64 || sizeof(F) == 4) ? 4 : 2;
 }
 
-template <class F, int NP, int NT, int ORDER>
-__global__ __launch_bounds__(NT, mfma_waves<F>(NT, NP)) void transport_mfma_kernel(MechDev m, int64_t n,
+template <class F, class S, int ORDER>
+__global__ __launch_bounds__(S::NT, mfma_waves<F>(S::NT, S::NP)) void transport_mfma_kernel(MechDev m, int64_t n,
                                                                 const double *__restrict__ T,
                                                                 const double *__restrict__ Pp,
                                                                 const double *__restrict__ Y,
@@ -889,14 +932,14 @@ __global__ __launch_bounds__(NT, mfma_waves<F>(NT, NP)) void transport_mfma_kern
                                                                 double *__restrict__ lam,
                                                                 double *__restrict__ Dmix)
 {
-    transport_mfma_tile<F, NP, NT, ORDER, false>(threadIdx.x, m, n, (int64_t)blockIdx.x * NP, T, Pp,
-                                                 Y, mu, lam, Dmix);
+    transport_mfma_tile<F, S, ORDER, false>(threadIdx.x, m, n, (int64_t)blockIdx.x * S::NP, T, Pp, Y,
+                                             mu, lam, Dmix);
 }
 
 // At most 256 VGPRs (two waves per SIMD): the FP64 form for fits of any order
 // would otherwise take 258 and run one wave per SIMD.
-template <class F, int NP, int NT, int ORDER>
-__global__ __launch_bounds__(NT, mfma_waves<F>(NT, NP)) void transport_mfma_batch_kernel(
+template <class F, class S, int ORDER>
+__global__ __launch_bounds__(S::NT, mfma_waves<F>(S::NT, S::NP)) void transport_mfma_batch_kernel(
     MechDev m, const WorkList *__restrict__ wl, int *__restrict__ counter)
 {
     __shared__ int tile;
@@ -914,7 +957,7 @@ __global__ __launch_bounds__(NT, mfma_waves<F>(NT, NP)) void transport_mfma_batc
         const WorkItem it = wl->items[r];
         int tid;
         asm volatile("v_mov_b32 %0, %1" : "=v"(tid) : "v"((int)threadIdx.x));
-        transport_mfma_tile<F, NP, NT, ORDER, true>(tid, m, it.n, (int64_t)(t - wl->start[1][r]) * NP, it.T,
+        transport_mfma_tile<F, S, ORDER, true>(tid, m, it.n, (int64_t)(t - wl->start[1][r]) * S::NP, it.T,
                                           it.p, it.Y, it.mu, it.lam, it.Dmix);
     }
 }
@@ -922,15 +965,15 @@ __global__ __launch_bounds__(NT, mfma_waves<F>(NT, NP)) void transport_mfma_batc
 // Batched requests, one tile per workgroup (grid = the batch's transport
 // tiles).  Uniform per workgroup, so a workgroup past the last tile returns
 // before any barrier.
-template <class F, int NP, int NT, int ORDER>
-__global__ __launch_bounds__(NT, mfma_waves<F>(NT, NP)) void transport_mfma_items_kernel(
+template <class F, class S, int ORDER>
+__global__ __launch_bounds__(S::NT, mfma_waves<F>(S::NT, S::NP)) void transport_mfma_items_kernel(
     MechDev m, const WorkList *__restrict__ wl)
 {
     const int t = (int)blockIdx.x;
     if (t >= wl->ntiles[1]) return;
     const int r = work_item_ballot(wl, 1, t);
     const WorkItem it = wl->items[r];
-    transport_mfma_tile<F, NP, NT, ORDER, false>(threadIdx.x, m, it.n, (int64_t)(t - wl->start[1][r]) * NP,
+    transport_mfma_tile<F, S, ORDER, false>(threadIdx.x, m, it.n, (int64_t)(t - wl->start[1][r]) * S::NP,
                                       it.T, it.p, it.Y, it.mu, it.lam, it.Dmix);
 }
 
@@ -1118,44 +1161,67 @@ kx_status rows_launch(const MechDev &m, int64_t grid, void **args, hipStream_t s
 //    share (53 species, 2^20 points: 1.22 ms with 256 threads, 1.24 with 512, mixed
 //    0.71 and 0.74);
 //  * up to 128: 32 points, 256 threads, two workgroups per CU;
-//  * above, mixed: 32 points, 512 threads, two workgroups per CU (200 species,
-//    100003 points 0.80 -> 0.75 ms against 16 points and 256 threads);
 //  * above, FP64: 16 points, 256 threads (32 points leave one workgroup per CU:
-//    1.68 against 1.58 ms).
-struct MfmaShape {
-    int np, nt;
-};
-template <class F> MfmaShape mfma_shape(const MechDev &m)
+//    1.68 against 1.58 ms);
+//  * above, mixed: 32 points, 512 threads, two workgroups per CU, or 16 points and
+//    256 threads.  us by 32 / 16 points: 200 species, 1000 points 73 / 62 and 4096
+//    points 74 / 63 (a tile is a shorter chain, and each has a CU of its own), 8192
+//    points 79 / 88, 10000 points 122 / 111 (the first CU with two 32-point tiles),
+//    16384 points 125 / 142, 100003 points 746 / 794; with nine row blocks, which eight
+//    waves take in two turns (144 species), 32768 points 140 / 145, 100003 points 441 /
+//    410; where two 32-point groups do not share a CU's LDS (256 species) 100003 points
+//    1289 / 1212, 16384 points 199 / 224.
+// Three row blocks, mixed: from 160000 points on the 256-thread groups are the faster
+// ones after all (48 species, 131072 points 88 us by 512 threads, 91 by 256; 200000
+// points 134 and 134, 524288 points 326 and 312).
+// A shape's bits are its partial sums (MfmaShape), so what a mechanism and precision
+// use has the same ones throughout; where two shapes do, the number of points decides.
+enum MfmaId { k64x512, k64x256, k64x256of8, k32x256, k32x512, k16x256, k16x256of8 };
+template <class F> MfmaId mfma_shape(const MechDev &m, int64_t points)
 {
     const int kp = 4 * m.kstep;
-    if (kp <= 64) return {64, m.mblk < 4 ? 512 : 256};
-    if (kp <= 128) return {32, 256};
-    if (sizeof(F) == 4) return {32, 512};
-    return {16, 256};
+    constexpr bool F64 = sizeof(F) == 8;
+    if (kp <= 64) {
+        if (m.mblk >= 4) return k64x256;
+        return !F64 && m.mblk == 3 && points >= 160000 ? k64x256of8 : k64x512;
+    }
+    if (kp <= 128) return k32x256;
+    if (F64) return k16x256;
+    const bool alone = mfma_lds_bytes<F, MfmaShape<32, 512>>(m.kstep) > 80 * 1024;
+    const bool small = points >= 0 && (points <= 4096 || (points > 8192 && points <= 10240));
+    const bool large = (m.mblk == 9 && points > 49152) || (alone && points > 16384);
+    return small || large ? k16x256of8 : k32x512;
 }
-template <class F> int mfma_np(const MechDev &m) { return mfma_shape<F>(m).np; }
-template <class F> int mfma_nt(const MechDev &m) { return mfma_shape<F>(m).nt; }
+constexpr int64_t kAnyPoints = -1;  // the shape of the batch kernels
 
-// f(NP, NT) of the shape, as compile-time values.
-template <class F, class Fn> auto with_mfma_shape(const MechDev &m, Fn f)
+// f(MfmaShape) of the shape.  The batch kernels' shapes do not depend on the points.
+template <class F, int FORM, class Fn> auto with_mfma_shape(MfmaId id, Fn f)
 {
-    const MfmaShape s = mfma_shape<F>(m);
-    using std::integral_constant;
-    if (s.np == 64)
-        return s.nt == 512 ? f(integral_constant<int, 64>{}, integral_constant<int, 512>{})
-                           : f(integral_constant<int, 64>{}, integral_constant<int, 256>{});
-    if (s.np == 32 && s.nt == 256)
-        return f(integral_constant<int, 32>{}, integral_constant<int, 256>{});
-    if constexpr (sizeof(F) == 4)
-        return f(integral_constant<int, 32>{}, integral_constant<int, 512>{});
-    else
-        return f(integral_constant<int, 16>{}, integral_constant<int, 256>{});
+    if (id == k64x512) return f(MfmaShape<64, 512>{});
+    if constexpr (sizeof(F) == 4) {
+        if constexpr (FORM != 1) {
+            if (id == k64x256of8) return f(MfmaShape<64, 256, 8>{});
+            if (id == k16x256of8) return f(MfmaShape<16, 256, 16, 8>{});
+        }
+        if (id == k32x512) return f(MfmaShape<32, 512>{});
+    } else {
+        if (id == k16x256) return f(MfmaShape<16, 256>{});
+    }
+    if (id == k32x256) return f(MfmaShape<32, 256>{});
+    return f(MfmaShape<64, 256>{});
 }
-
-template <class F> size_t mfma_lds(const MechDev &m)
+template <class F> int mfma_np(const MechDev &m, int64_t points)
 {
-    return with_mfma_shape<F>(m, [&](auto np, auto nt) {
-        return mfma_lds_bytes_np<F, decltype(np)::value, decltype(nt)::value>(m.kstep);
+    return with_mfma_shape<F, 0>(mfma_shape<F>(m, points), [](auto s) { return decltype(s)::NP; });
+}
+template <class F> int mfma_nt(const MechDev &m, int64_t points)
+{
+    return with_mfma_shape<F, 0>(mfma_shape<F>(m, points), [](auto s) { return decltype(s)::NT; });
+}
+template <class F> size_t mfma_lds(const MechDev &m, int64_t points)
+{
+    return with_mfma_shape<F, 0>(mfma_shape<F>(m, points), [&](auto s) {
+        return mfma_lds_bytes<F, decltype(s)>(m.kstep);
     });
 }
 
@@ -1165,31 +1231,31 @@ bool use_mfma(const MechDev &m)
 }
 
 // FORM 0: direct launch, 1: work-stealing batch, 2: one tile per workgroup
-template <class F, int FORM, int NP, int NT> const void *mfma_instance(bool o5)
+template <class F, int FORM, class S> const void *mfma_instance(bool o5)
 {
     if (FORM == 1)
-        return o5 ? (const void *)transport_mfma_batch_kernel<F, NP, NT, 5>
-                  : (const void *)transport_mfma_batch_kernel<F, NP, NT, 0>;
+        return o5 ? (const void *)transport_mfma_batch_kernel<F, S, 5>
+                  : (const void *)transport_mfma_batch_kernel<F, S, 0>;
     if (FORM == 2)
-        return o5 ? (const void *)transport_mfma_items_kernel<F, NP, NT, 5>
-                  : (const void *)transport_mfma_items_kernel<F, NP, NT, 0>;
-    return o5 ? (const void *)transport_mfma_kernel<F, NP, NT, 5>
-              : (const void *)transport_mfma_kernel<F, NP, NT, 0>;
+        return o5 ? (const void *)transport_mfma_items_kernel<F, S, 5>
+                  : (const void *)transport_mfma_items_kernel<F, S, 0>;
+    return o5 ? (const void *)transport_mfma_kernel<F, S, 5>
+              : (const void *)transport_mfma_kernel<F, S, 0>;
 }
-template <class F, int FORM> const void *mfma_kernel(const MechDev &m)
+template <class F, int FORM> const void *mfma_kernel(const MechDev &m, int64_t points)
 {
     const bool o5 = m.fit_order == 5;
-    return with_mfma_shape<F>(m, [&](auto np, auto nt) {
-        return mfma_instance<F, FORM, decltype(np)::value, decltype(nt)::value>(o5);
+    return with_mfma_shape<F, FORM>(mfma_shape<F>(m, points), [&](auto s) {
+        return mfma_instance<F, FORM, decltype(s)>(o5);
     });
 }
 
-template <class F, int FORM> kx_status mfma_prepare(const MechDev &m, size_t *lds)
+template <class F, int FORM> kx_status mfma_prepare(const MechDev &m, int64_t points, size_t *lds)
 {
-    *lds = mfma_lds<F>(m);
+    *lds = mfma_lds<F>(m, points);
     if (*lds > 160 * 1024)
         return fail(KX_EUNSUPPORTED, "transport: mechanism too large for the LDS tiles");
-    hipError_t e = hipFuncSetAttribute(mfma_kernel<F, FORM>(m),
+    hipError_t e = hipFuncSetAttribute(mfma_kernel<F, FORM>(m, points),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)*lds);
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute (transport)");
     return KX_OK;
@@ -1197,10 +1263,16 @@ template <class F, int FORM> kx_status mfma_prepare(const MechDev &m, size_t *ld
 
 }  // namespace
 
+int transport_items_tile_points(const MechDev &m, int precision, int64_t points)
+{
+    if (use_mfma(m))
+        return precision == KX_MIXED ? mfma_np<float>(m, points) : mfma_np<double>(m, points);
+    return kWave;
+}
+
 int transport_tile_points(const MechDev &m, int precision)
 {
-    if (use_mfma(m)) return precision == KX_MIXED ? mfma_np<float>(m) : mfma_np<double>(m);
-    return kWave;
+    return transport_items_tile_points(m, precision, kAnyPoints);
 }
 
 kx_status prepare_transport_batch(const MechDev &m, int precision)
@@ -1208,8 +1280,8 @@ kx_status prepare_transport_batch(const MechDev &m, int precision)
     if (!use_mfma(m))
         return precision == KX_MIXED ? rows_prepare<float, 1>(m) : rows_prepare<double, 1>(m);
     size_t lds = 0;
-    return precision == KX_MIXED ? mfma_prepare<float, 1>(m, &lds)
-                                 : mfma_prepare<double, 1>(m, &lds);
+    return precision == KX_MIXED ? mfma_prepare<float, 1>(m, kAnyPoints, &lds)
+                                 : mfma_prepare<double, 1>(m, kAnyPoints, &lds);
 }
 
 namespace {
@@ -1244,16 +1316,16 @@ kx_status go_transport(const MechDev &m, int64_t n, const double *T, const doubl
     }
     if (use_mfma(m)) {
         size_t lds = 0;
-        kx_status st = mfma_prepare<F, 0>(m, &lds);
+        kx_status st = mfma_prepare<F, 0>(m, n, &lds);
         if (st != KX_OK) return st;
-        const int np = mfma_np<F>(m);
+        const int np = mfma_np<F>(m, n);
         const int64_t nblk = (n + np - 1) / np;
         if (nblk > 0x7fffffff) return fail(KX_EINVAL, "transport: n too large");
-        return launch_tiles(n, np, mfma_nt<F>(m), [&](int64_t i, int64_t groups) {
+        return launch_tiles(n, np, mfma_nt<F>(m, n), [&](int64_t i, int64_t groups) {
             TransportPtrs a{T + i, p + i, Y + i, mu + i, lam + i, Dmix + i};
             void *args[] = {(void *)&m, (void *)&n, &a.T, &a.p, &a.Y, &a.mu, &a.lam, &a.Dmix};
-            hipError_t e = hipLaunchKernel(mfma_kernel<F, 0>(m), dim3((unsigned)groups),
-                                           dim3(mfma_nt<F>(m)), args, lds, s);
+            hipError_t e = hipLaunchKernel(mfma_kernel<F, 0>(m, n), dim3((unsigned)groups),
+                                           dim3(mfma_nt<F>(m, n)), args, lds, s);
             return e != hipSuccess ? hip_fail(e, "transport kernel launch") : KX_OK;
         });
     }
@@ -1273,10 +1345,10 @@ kx_status go_transport_batch(const MechDev &m, const WorkList *wl, int *counter,
                              hipStream_t s)
 {
     if (use_mfma(m)) {
-        const size_t lds = mfma_lds<F>(m);
+        const size_t lds = mfma_lds<F>(m, kAnyPoints);
         void *args[] = {(void *)&m, (void *)&wl, (void *)&counter};
-        hipError_t e = hipLaunchKernel(mfma_kernel<F, 1>(m), dim3(grid), dim3(mfma_nt<F>(m)),
-                                       args, lds, s);
+        hipError_t e = hipLaunchKernel(mfma_kernel<F, 1>(m, kAnyPoints), dim3(grid),
+                                       dim3(mfma_nt<F>(m, kAnyPoints)), args, lds, s);
         if (e != hipSuccess) return hip_fail(e, "transport batch kernel launch");
         return ok();
     }
@@ -1284,18 +1356,19 @@ kx_status go_transport_batch(const MechDev &m, const WorkList *wl, int *counter,
     return rows_launch<F, 1>(m, grid, args, s, "transport batch kernel launch");
 }
 template <class F>
-kx_status go_transport_items(const MechDev &m, const WorkList *wl, int64_t ntiles, hipStream_t s)
+kx_status go_transport_items(const MechDev &m, const WorkList *wl, int64_t ntiles, int64_t points,
+                             hipStream_t s)
 {
     if (ntiles <= 0) return ok();
-    if (ntiles > max_workgroups(use_mfma(m) ? mfma_nt<F>(m) : rows_waves(m) * kWave))
+    if (ntiles > max_workgroups(use_mfma(m) ? mfma_nt<F>(m, points) : rows_waves(m) * kWave))
         return fail(KX_EINVAL, "transport: too many tiles");
     if (use_mfma(m)) {
         size_t lds = 0;
-        kx_status st = mfma_prepare<F, 2>(m, &lds);
+        kx_status st = mfma_prepare<F, 2>(m, points, &lds);
         if (st != KX_OK) return st;
         void *args[] = {(void *)&m, (void *)&wl};
-        hipError_t e = hipLaunchKernel(mfma_kernel<F, 2>(m), dim3((unsigned)ntiles),
-                                       dim3(mfma_nt<F>(m)), args, lds, s);
+        hipError_t e = hipLaunchKernel(mfma_kernel<F, 2>(m, points), dim3((unsigned)ntiles),
+                                       dim3(mfma_nt<F>(m, points)), args, lds, s);
         if (e != hipSuccess) return hip_fail(e, "transport items kernel launch");
         return ok();
     }
@@ -1307,10 +1380,10 @@ kx_status go_transport_items(const MechDev &m, const WorkList *wl, int64_t ntile
 }  // namespace
 
 kx_status launch_transport_items(const MechDev &m, const WorkList *wl, int64_t ntiles,
-                                 int precision, hipStream_t s)
+                                 int64_t points, int precision, hipStream_t s)
 {
-    if (precision == KX_MIXED) return go_transport_items<float>(m, wl, ntiles, s);
-    return go_transport_items<double>(m, wl, ntiles, s);
+    if (precision == KX_MIXED) return go_transport_items<float>(m, wl, ntiles, points, s);
+    return go_transport_items<double>(m, wl, ntiles, points, s);
 }
 
 kx_status launch_transport(const kx_mech *mech, int64_t n, const double *T, const double *p,

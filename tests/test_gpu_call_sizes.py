@@ -138,3 +138,34 @@ def test_small_calls_against_the_oracle(name):
     w = kx.production_rates(dm, *d, precision="mixed")[:, :70].cpu().numpy()
     assert np.all(np.abs(w - ref) <= 1e-5 * s + 1e-300)
     dm.close()
+
+
+TRANSPORT = {"48sp": dict(ns=48),   # three row blocks: 512 or 256 threads (mixed)
+             "144sp": dict(ns=144), "200sp": dict(ns=200), "256sp": dict(ns=256)}
+
+
+@pytest.mark.parametrize("name", list(TRANSPORT))
+def test_transport(name):
+    """The matrix-core tile shapes that a call's size selects (mixed path), and the
+    batched call of the same sizes."""
+    from paper_2411_02640_amd import kx
+    kw = dict(TRANSPORT[name])
+    ns = kw.pop("ns")
+    dm = kx.Mechanism(I.make_mechanism(I.MechSpec(ns, 5 * ns, ns // 2, 0, 2, seed=9000 + ns, **kw)), 0)
+    n = 160001 if ns <= 64 else 50001
+    base = _states(ns, 1024)
+    d = [t.repeat(*([1] * (t.dim() - 1)), n // 1024 + 1)[..., :n].contiguous() for t in base]
+    d[2][:, 3] = 0.0
+    d[2][ns - 1, 3] = 1.0
+    for prec in ("fp64", "mixed"):
+        print("[gpu-case] transport call sizes", name, prec, flush=True)
+        out = kx.transport(dm, *d, precision=prec)
+        for m in (1, 65, 4096, 4097, 8193, 10241, 16385, n - 1):
+            for a, b in zip(kx.transport(dm, *_first(d, m), precision=prec), out):
+                assert torch.equal(a, b[..., :m]), m
+        for sizes in ((1, 65), (4097,), (5000, 5000), (16384, 30000)):
+            sets = [_first(d, m) for m in sizes]
+            for got, m in zip(kx.batch_noalloc(dm, sets, transport=True, precision=prec), sizes):
+                for a, b in zip(got[1:], out):
+                    assert torch.equal(a, b[..., :m]), (sizes, m)
+    dm.close()
