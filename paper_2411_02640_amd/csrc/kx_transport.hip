@@ -61,12 +61,8 @@ __device__ __forceinline__ F horner_v(const F *__restrict__ c, F u, int order)
     return r;
 }
 
-// Mixture-averaged transport for P points per lane.  F is the arithmetic
-// type of the fits and mixing sums (double: FP64 path; float: mixed path);
-// KIND is the diffusion fit kind (0: D_kj, 1: 1/D_kj); KB species k are held
-// in registers per step of the j loop, which serves the Wilke and the D_km
-// sums together.  Every uniform coefficient fetched by a scalar load feeds
-// P lanes' worth of arithmetic.
+// Reciprocals and square roots by arithmetic type: double on the FP64 path, float
+// on the mixed path.
 template <class F> __device__ __forceinline__ F rcp_fast(F x);
 template <> __device__ __forceinline__ double rcp_fast<double>(double x) { return krcp1(x); }
 template <> __device__ __forceinline__ float rcp_fast<float>(float x)
@@ -147,10 +143,8 @@ constexpr int kRowsChunk = 32;
 // bytes (24 mixed) were a load the wave waited for: 200 species, 2^20 points 56 -> 39
 // ms, mixed 39 -> 22; 53 species mixed 2.16 -> 1.89.  FP64 with four species per wave
 // keeps the scalar loads: there the stages' LDS leaves one workgroup per CU (53
-// species, 2^20 points: 2.41 ms scalar, 3.16 staged).  The form of one thread per
-// four points took 35, 21 and 1.58 ms at that size, but 13.0, 5.5 and 0.46 ms for
-// 1000 points, where this one takes 0.56, 0.33 and 0.03 (262144: 16.6 -> 9.9, 9.6 ->
-// 5.6, 0.65 -> 0.46).
+// species, 2^20 points: 2.41 ms scalar, 3.16 staged).  Calls of very many points take
+// transport_lanes_tile where it is the faster form (lanes_form).
 constexpr int kStage = 8;
 static_assert(kRowsChunk % kStage == 0 && kStage % 2 == 0, "whole stages of pairs");
 
@@ -421,7 +415,7 @@ __device__ __forceinline__ void transport_rows_tile(const MechDev &m, int64_t n,
             } else {
                 // sum_{j!=k} X_j / D_kj = (p/p_atm) acc for either fit kind; the
                 // numerator (W-bar - X_k W_k)/W-bar is formed in FP64
-                D = (wbar - Xk * Wt[k]) * krcp(wbar * (double)acc[r] * pr);
+                D = fma(-Xk, Wt[k], wbar) * krcp(wbar * (double)acc[r] * pr);
             }
             if (act) Dmix[(int64_t)k * n + i] = D;
         }
@@ -446,6 +440,247 @@ __device__ __forceinline__ void transport_rows_tile(const MechDev &m, int64_t n,
             mu[i] = (double)v;
         }
     }
+}
+
+// The same results by one thread per P points (a wave per 64 P), for calls of very
+// many points: species k in blocks of KB, j streaming over all species with X_j and
+// rho_j formed again per block, so that a coefficient serves 64 P points and nothing
+// waits at a barrier.  Every sum runs over the same terms in the same order as in
+// transport_rows_tile (the shares of its waves of rw species one after another), so a
+// point's bits are the same.
+template <class F, int ORDER, int KIND, int P, int KB>
+__device__ __forceinline__ void transport_lanes_tile(const MechDev &m, int rw, int64_t n,
+                                                     int64_t base, const double *__restrict__ T,
+                                                     const double *__restrict__ Pp,
+                                                     const double *__restrict__ Y,
+                                                     double *__restrict__ mu,
+                                                     double *__restrict__ lam,
+                                                     double *__restrict__ Dmix)
+{
+    using Tb = Tabs<F>;
+    constexpr bool F64 = std::is_same<F, double>::value;
+    static_assert(kKB % KB == 0 && KB % 2 == 0, "blocks of the tables");
+    const int ns = m.ns, order = ORDER > 0 ? ORDER : m.fit_order, nw = (ns + rw - 1) / rw;
+    KX_CONST DevSpecies *sp = const_table(m.sp);
+    KX_CONST double *Wt = const_table(m.W);
+    KX_CONST F *visc_t = const_table(Tb::visc(m)), *cond_t = const_table(Tb::cond(m));
+    KX_CONST F *wq_t = const_table(Tb::wq(m));
+
+    int64_t idx[P];
+    bool act[P];
+    F u[P];
+    double pr[P], xf[P], wbar[P];
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+        const int64_t i = base + threadIdx.x + kWave * q;
+        act[q] = i < n;
+        idx[q] = act[q] ? i : n - 1;
+        u[q] = (F)((kln(T[idx[q]]) - m.fit_L0) * m.inv_fit_h);
+        pr[q] = Pp[idx[q]] * (1.0 / kPatm);
+    }
+    auto Yat = [&](int k, int q) { return Y[(int64_t)k * n + idx[q]]; };
+    {
+        double sYW[P];
+#pragma unroll
+        for (int q = 0; q < P; ++q) sYW[q] = 0.0;
+        for (int w = 0; w < nw; ++w) {
+            double s[P];
+#pragma unroll
+            for (int q = 0; q < P; ++q) s[q] = 0.0;
+            for (int k = w; k < ns; k += nw) {
+                const double iw = sp[k].inv_W;
+#pragma unroll
+                for (int q = 0; q < P; ++q) s[q] = fma(Yat(k, q), iw, s[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < P; ++q) sYW[q] += s[q];
+        }
+#pragma unroll
+        for (int q = 0; q < P; ++q) xf[q] = krcp(sYW[q]);
+    }
+    // W-bar and Mathur's sums: FP64 by the waves' shares, mixed Mathur's in species
+    // order
+    {
+        double a1[P], a2[P];
+        F s1[P], s2[P];
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+            wbar[q] = a1[q] = a2[q] = 0.0;
+            s1[q] = s2[q] = (F)0;
+        }
+        for (int w = 0; w < nw; ++w) {
+            double wb[P];
+#pragma unroll
+            for (int q = 0; q < P; ++q) {
+                wb[q] = 0.0;
+                if (F64) s1[q] = s2[q] = (F)0;
+            }
+            for (int j0 = 0; j0 < ns; j0 += kRowsChunk)
+                for (int j = j0 + w; j < min(j0 + kRowsChunk, ns); j += nw) {
+                    const double iw = sp[j].inv_W, W = Wt[j];
+#pragma unroll
+                    for (int q = 0; q < P; ++q) {
+                        const double X = Yat(j, q) * iw * xf[q];
+                        if constexpr (F64) {
+                            const F lk = horner_c<ORDER>(cond_t + j * order, u[q], order);
+                            s1[q] = fma(X, lk, s1[q]);
+                            s2[q] = fma(X, rcp_acc(lk), s2[q]);
+                        }
+                        wb[q] = fma(X, W, wb[q]);
+                    }
+                }
+#pragma unroll
+            for (int q = 0; q < P; ++q) {
+                wbar[q] += wb[q];
+                if constexpr (F64) {
+                    a1[q] += s1[q];
+                    a2[q] += s2[q];
+                }
+            }
+        }
+        if constexpr (!F64) {
+            for (int j = 0; j < ns; ++j) {
+                const double iw = sp[j].inv_W;
+#pragma unroll
+                for (int q = 0; q < P; ++q) {
+                    const double X = Yat(j, q) * iw * xf[q];
+                    const F lk = horner_c<ORDER>(cond_t + j * order, u[q], order);
+                    s1[q] = fma((F)X, lk, s1[q]);
+                    s2[q] = fma((F)X, rcp_acc(lk), s2[q]);
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < P; ++q)
+            if (act[q]) {
+                if constexpr (F64)
+                    lam[idx[q]] = 0.5 * (a1[q] + rcp_acc(a2[q]));
+                else
+                    lam[idx[q]] = (double)((F)0.5 * (s1[q] + rcp_acc(s2[q])));
+            }
+    }
+
+    double v[P], vp[P];  // FP64: mu and the current share's part of it
+    F v32[P];
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+        v[q] = vp[q] = 0.0;
+        v32[q] = (F)0;
+    }
+    for (int k0 = 0; k0 < ns; k0 += KB) {
+        if (F64 && k0 > 0 && k0 % rw == 0) {
+#pragma unroll
+            for (int q = 0; q < P; ++q) {
+                v[q] += vp[q];
+                vp[q] = 0.0;
+            }
+        }
+        F sig[P][KB], den[P][KB], acc[P][KB];
+#pragma unroll
+        for (int r = 0; r < KB; ++r) {
+            const int k = k0 + r, kc = min(k, ns - 1);
+#pragma unroll
+            for (int q = 0; q < P; ++q) {
+                const F ek = horner_c<ORDER>(visc_t + kc * order, u[q], order);
+                sig[q][r] = k < ns ? ek * rsqrt_acc(ek) * rcp_acc((F)wq_t[kc]) : (F)0;
+                den[q][r] = acc[q][r] = (F)0;
+            }
+        }
+        KX_CONST F *c1b = const_table(Tb::wilke(m)) + (size_t)(k0 / kKB) * ns * kKB + k0 % kKB;
+        KX_CONST F *dfb = const_table(Tb::dfit(m)) +
+                          ((size_t)(k0 / kKB) * ns * kKB + k0 % kKB) * order;
+        auto point = [&](int j, F (&X)[P], F (&rho)[P]) {
+            const double iw = sp[j].inv_W;
+            const F wj = (F)wq_t[j];
+#pragma unroll
+            for (int q = 0; q < P; ++q) {
+                X[q] = (F)(Yat(j, q) * iw * xf[q]);
+                rho[q] = wj * rsqrt_acc(horner_c<ORDER>(visc_t + j * order, u[q], order));
+            }
+        };
+        auto wilke = [&](F c1, int q, int r, F X, F rho) {
+            const F t = fma(sig[q][r], rho, (F)1);
+            const F xt = X * t;
+            den[q][r] = fma(c1, xt * t, den[q][r]);
+        };
+        constexpr bool PAIRS = F64 && KIND == 0;
+        // species j0 .. j1 - 1; diag: they hold species of the block
+        auto steps = [&](int j0, int j1, bool diag) {
+            int j = j0;
+            if constexpr (PAIRS) {
+#pragma clang loop unroll(disable)
+                for (; j + 1 < j1; j += 2) {
+                    F Xa[P], ra[P], Xb[P], rb[P];
+                    point(j, Xa, ra);
+                    point(j + 1, Xb, rb);
+                    KX_CONST F *ca = c1b + (size_t)j * kKB, *da = dfb + (size_t)j * kKB * order;
+#pragma unroll
+                    for (int r = 0; r < KB; ++r) {
+                        const bool sa = diag && k0 + r == j, sb = diag && k0 + r == j + 1;
+#pragma unroll
+                        for (int q = 0; q < P; ++q) {
+                            wilke(ca[r], q, r, Xa[q], ra[q]);
+                            wilke(ca[kKB + r], q, r, Xb[q], rb[q]);
+                            const F fa = horner_c<ORDER>(da + r * order, u[q], order);
+                            const F fb = horner_c<ORDER>(da + (kKB + r) * order, u[q], order);
+                            const F xa = sa ? (F)0 : Xa[q], xb = sb ? (F)0 : Xb[q];
+                            acc[q][r] = fma(fma(xa, fb, xb * fa), rcp_fast(fa * fb), acc[q][r]);
+                        }
+                        // two species' coefficients in scalar registers at a time (all
+                        // four spill: 200 species, 2^20 points 38.6 against 33.9 ms)
+                        if (r % 2) __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            }
+#pragma clang loop unroll(disable)
+            for (; j < j1; ++j) {
+                F X[P], rho[P];
+                point(j, X, rho);
+                KX_CONST F *c1 = c1b + (size_t)j * kKB, *df = dfb + (size_t)j * kKB * order;
+#pragma unroll
+                for (int r = 0; r < KB; ++r) {
+                    const bool self = diag && k0 + r == j;
+#pragma unroll
+                    for (int q = 0; q < P; ++q) {
+                        wilke(c1[r], q, r, X[q], rho[q]);
+                        const F f = horner_c<ORDER>(df + r * order, u[q], order);
+                        acc[q][r] = fma(self ? (F)0 : X[q], KIND == 0 ? rcp_fast(f) : f, acc[q][r]);
+                    }
+                }
+            }
+        };
+        const int k1 = min(k0 + KB, ns);
+        steps(0, k0, false);
+        steps(k0, k1, true);
+        steps(k1, ns, false);
+#pragma unroll
+        for (int r = 0; r < KB; ++r) {
+            const int k = k0 + r;
+            if (k < ns) {
+                const double iw = sp[k].inv_W, Wk = Wt[k];
+#pragma unroll
+                for (int q = 0; q < P; ++q) {
+                    const double Xk = Yat(k, q) * iw * xf[q];
+                    const F ek = horner_c<ORDER>(visc_t + k * order, u[q], order);
+                    if constexpr (F64)
+                        vp[q] = fma(Xk * ek, rcp_acc(den[q][r]), vp[q]);
+                    else
+                        v32[q] = fma((F)Xk * ek, rcp_acc(den[q][r]), v32[q]);
+                    double D;
+                    if (acc[q][r] == (F)0) {
+                        const F f = horner_c<ORDER>(const_table(Tb::ddiag(m)) + k * order, u[q], order);
+                        D = (KIND == 0) ? (double)f / pr[q] : 1.0 / ((double)f * pr[q]);
+                    } else {
+                        D = fma(-Xk, Wk, wbar[q]) * krcp(wbar[q] * (double)acc[q][r] * pr[q]);
+                    }
+                    if (act[q]) Dmix[(int64_t)k * n + idx[q]] = D;
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < P; ++q)
+        if (act[q]) mu[idx[q]] = F64 ? v[q] + vp[q] : (double)v32[q];
 }
 
 // ---------------------------------------------------------------------------
@@ -990,6 +1225,38 @@ __global__ __launch_bounds__(1024, rows_min_waves<F>(KIND, RW)) void transport_r
                                             Dmix);
 }
 
+// Points of a thread and species of a block of transport_lanes_tile.  Four points by
+// four species in FP64 (219 registers, two waves per SIMD) took 3.45 ms for 53
+// species and 2^20 points, three by four (169) 3.03, two by eight 2.73, two by four
+// (119, four waves) 2.57; mixed four by four 2.40 ms, four by eight 2.27, two by four
+// 1.63, two by eight (96 registers) 1.50.
+constexpr int kLanePoints = 2, kLaneTile = kLanePoints * kWave;
+template <class F> constexpr int lane_species() { return sizeof(F) == 8 ? 4 : 8; }
+
+template <class F, int KIND>
+__global__ __launch_bounds__(kWave, 2) void transport_lanes_kernel(
+    MechDev m, int rw, int64_t n, const double *__restrict__ T, const double *__restrict__ Pp,
+    const double *__restrict__ Y, double *__restrict__ mu, double *__restrict__ lam,
+    double *__restrict__ Dmix)
+{
+    transport_lanes_tile<F, 5, KIND, kLanePoints, lane_species<F>()>(
+        m, rw, n, (int64_t)blockIdx.x * kLaneTile, T, Pp, Y, mu, lam, Dmix);
+}
+
+// Batched requests of very many points together.
+template <class F, int KIND>
+__global__ __launch_bounds__(kWave, 2) void transport_lanes_items_kernel(
+    MechDev m, int rw, const WorkList *__restrict__ wl)
+{
+    const int t = (int)blockIdx.x;
+    if (t >= wl->ntiles[1]) return;
+    const int r = work_item_ballot(wl, 1, t);
+    const WorkItem it = wl->items[r];
+    transport_lanes_tile<F, 5, KIND, kLanePoints, lane_species<F>()>(
+        m, rw, it.n, (int64_t)(t - wl->start[1][r]) * kLaneTile, it.T, it.p, it.Y, it.mu, it.lam,
+        it.Dmix);
+}
+
 // Batched requests: persistent workgroups taking tiles from a counter.
 template <class F, int ORDER, int KIND, int RW>
 __global__ __launch_bounds__(1024, rows_min_waves<F>(KIND, RW)) void transport_rows_batch_kernel(MechDev m,
@@ -1134,6 +1401,54 @@ template <class F, int FORM> const void *rows_kernel(const MechDev &m)
                      : rows_instance<F, FORM, 0, 16>(o5);
 }
 
+// Whether a call of `points` points takes one thread per two points.  That form has
+// no barriers and reads a coefficient once per 128 points, but a wave is a chain of
+// ns^2 pairs, and of waves it has rounds of 4 per SIMD, 524288 points (mixed 5, 655360),
+// so it is for calls of much of one whose last round is not nearly empty.  There it
+// gains where the waves of transport_rows_tile leave much of a CU unused (FP64: 9 to 12
+// waves, of which one workgroup fits) and, mixed, where its chains are short.  us, rows
+// / lanes, D_kj fits.  FP64: 33 species (9 waves), 350000 points 466 / 388, 2^20 1425 /
+// 950; 129 species, 2^20 20956 / 14430; 40 species (10), 300000 points 458 / 502, 450000
+// 701 / 660; 48 species (12), 700000 points 1251 / 1339, 2^20 faster; 17 species, 450000
+// points 165 / 147, 24 species 400000 points 218 / 240; 53 species (14), 600000 points
+// 1392 / 1679, 2^20 2400 / 2329; 200 species (13), 450000 points 16999 / 17392, 524288
+// 20009 / 18298, 2^20 40095 / 33910; not with 128 species (13838 / 15787).  Mixed: 33 species, 450000 points
+// 359 / 347, 2^20 849 / 679; 53 species, 2^20 1883 / 1497; 129 species 13488 / 8792; 200
+// species, 450000 points 9706 / 10167, 2^20 22215 / 20231; 44 species, 786432 points 833
+// / 933, 900000 points equal; 24 species, 700000 points 258 / 281, 2^20 387 / 349; not
+// with 48 (1127 / 1188) or 100 species.  Fits of 1/D_kj (below 24 species), 2^20 points:
+// 17 species FP64 322 / 302, mixed 278 / 228.
+template <class F> bool lanes_form(const MechDev &m, int64_t points)
+{
+    constexpr bool F64 = sizeof(F) == 8;
+    constexpr int64_t round = (F64 ? 4096 : 5120) * (int64_t)kLaneTile;
+    const int nw = rows_waves(m), ns = m.ns;
+    const int64_t rest = points > round && points % round ? points % round : round;
+    if (m.fit_order != 5 || ns < 17 || points < 250000) return false;
+    if (F64) {
+        if (m.diff_kind == 1) return points > round && rest > round * 9 / 10;
+        if (nw == 9) return points >= 300000;
+        if (nw <= 11 && nw != 7 && nw != 8) return points >= 420000 && rest >= round / 5;
+        if (nw == 12 && points >= 750000) return true;
+        return (ns > 64 && (nw == 12 || nw == 13) && points >= 500000 && points <= round) ||
+               ((nw == 13 || nw == 14) && points >= 900000 && rest >= round * 9 / 20);
+    }
+    if (ns > 128 && nw == 9) return true;
+    if (rest < round / 4) return false;
+    if (m.diff_kind == 1 || (ns > 32 && ns <= 40) || (ns > 48 && ns <= 56) ||
+        (ns > 64 && (nw == 9 || nw == 10)))
+        return points >= 450000;
+    return (ns <= 44 || (ns > 48 && ns <= 64) || ns > 160) && points >= 900000;
+}
+template <class F> const void *lanes_kernel(const MechDev &m, bool items)
+{
+    if (items)
+        return m.diff_kind == 0 ? (const void *)transport_lanes_items_kernel<F, 0>
+                                : (const void *)transport_lanes_items_kernel<F, 1>;
+    return m.diff_kind == 0 ? (const void *)transport_lanes_kernel<F, 0>
+                            : (const void *)transport_lanes_kernel<F, 1>;
+}
+
 template <class F, int FORM> kx_status rows_prepare(const MechDev &m)
 {
     hipError_t e = hipFuncSetAttribute(rows_kernel<F, FORM>(m),
@@ -1267,6 +1582,8 @@ int transport_items_tile_points(const MechDev &m, int precision, int64_t points)
 {
     if (use_mfma(m))
         return precision == KX_MIXED ? mfma_np<float>(m, points) : mfma_np<double>(m, points);
+    if (precision == KX_MIXED ? lanes_form<float>(m, points) : lanes_form<double>(m, points))
+        return kLaneTile;
     return kWave;
 }
 
@@ -1331,6 +1648,16 @@ kx_status go_transport(const MechDev &m, int64_t n, const double *T, const doubl
     }
     const int64_t nblk = (n + kWave - 1) / kWave;
     if (nblk > 0x7fffffff) return fail(KX_EINVAL, "transport: n too large");
+    if (lanes_form<F>(m, n)) {
+        int rw = rows_per_wave(m);
+        return launch_tiles(n, kLaneTile, kWave, [&](int64_t i, int64_t groups) {
+            TransportPtrs a{T + i, p + i, Y + i, mu + i, lam + i, Dmix + i};
+            void *args[] = {(void *)&m, &rw, (void *)&n, &a.T, &a.p, &a.Y, &a.mu, &a.lam, &a.Dmix};
+            hipError_t e = hipLaunchKernel(lanes_kernel<F>(m, false), dim3((unsigned)groups),
+                                           dim3(kWave), args, 0, s);
+            return e != hipSuccess ? hip_fail(e, "transport kernel launch") : KX_OK;
+        });
+    }
     kx_status st = rows_prepare<F, 0>(m);
     if (st != KX_OK) return st;
     return launch_tiles(n, kWave, rows_waves(m) * kWave, [&](int64_t i, int64_t groups) {
@@ -1369,6 +1696,14 @@ kx_status go_transport_items(const MechDev &m, const WorkList *wl, int64_t ntile
         void *args[] = {(void *)&m, (void *)&wl};
         hipError_t e = hipLaunchKernel(mfma_kernel<F, 2>(m, points), dim3((unsigned)ntiles),
                                        dim3(mfma_nt<F>(m, points)), args, lds, s);
+        if (e != hipSuccess) return hip_fail(e, "transport items kernel launch");
+        return ok();
+    }
+    if (lanes_form<F>(m, points)) {
+        int rw = rows_per_wave(m);
+        void *args[] = {(void *)&m, &rw, (void *)&wl};
+        hipError_t e = hipLaunchKernel(lanes_kernel<F>(m, true), dim3((unsigned)ntiles), dim3(kWave),
+                                       args, 0, s);
         if (e != hipSuccess) return hip_fail(e, "transport items kernel launch");
         return ok();
     }

@@ -141,18 +141,24 @@ def test_small_calls_against_the_oracle(name):
 
 
 TRANSPORT = {"48sp": dict(ns=48),   # three row blocks: 512 or 256 threads (mixed)
-             "144sp": dict(ns=144), "200sp": dict(ns=200), "256sp": dict(ns=256)}
+             "144sp": dict(ns=144), "200sp": dict(ns=200), "256sp": dict(ns=256),
+             # the vector-ALU forms: 5, 9, 14, 9 and 9 waves, an odd last species
+             "17sp-Dkj": dict(ns=17, diff_fit_kind=0), "23sp": dict(ns=23),
+             "33sp-Dkj": dict(ns=33, diff_fit_kind=0), "53sp-Dkj": dict(ns=53, diff_fit_kind=0),
+             "65sp-Dkj": dict(ns=65, diff_fit_kind=0), "129sp-Dkj": dict(ns=129, diff_fit_kind=0)}
 
 
 @pytest.mark.parametrize("name", list(TRANSPORT))
 def test_transport(name):
-    """The matrix-core tile shapes that a call's size selects (mixed path), and the
-    batched call of the same sizes."""
+    """The matrix-core tile shapes that a call's size selects (mixed path), the
+    vector-ALU kernel's form for very many points, and the batched calls of the same
+    sizes."""
     from paper_2411_02640_amd import kx
     kw = dict(TRANSPORT[name])
     ns = kw.pop("ns")
     dm = kx.Mechanism(I.make_mechanism(I.MechSpec(ns, 5 * ns, ns // 2, 0, 2, seed=9000 + ns, **kw)), 0)
-    n = 160001 if ns <= 64 else 50001
+    vector = "diff_fit_kind" in kw or ns < 24
+    n = 900001 if vector and ns <= 53 else 450001 if vector else 160001 if ns <= 64 else 50001
     base = _states(ns, 1024)
     d = [t.repeat(*([1] * (t.dim() - 1)), n // 1024 + 1)[..., :n].contiguous() for t in base]
     d[2][:, 3] = 0.0
@@ -160,10 +166,10 @@ def test_transport(name):
     for prec in ("fp64", "mixed"):
         print("[gpu-case] transport call sizes", name, prec, flush=True)
         out = kx.transport(dm, *d, precision=prec)
-        for m in (1, 65, 4096, 4097, 8193, 10241, 16385, n - 1):
+        for m in (1, 65, 4096, 4097, 8193, 10241, 16385, n // 2, n - 1):
             for a, b in zip(kx.transport(dm, *_first(d, m), precision=prec), out):
                 assert torch.equal(a, b[..., :m]), m
-        for sizes in ((1, 65), (4097,), (5000, 5000), (16384, 30000)):
+        for sizes in ((1, 65), (4097,), (5000, 5000), (16384, 30000), (63, n - 1)):
             sets = [_first(d, m) for m in sizes]
             for got, m in zip(kx.batch_noalloc(dm, sets, transport=True, precision=prec), sizes):
                 for a, b in zip(got[1:], out):
