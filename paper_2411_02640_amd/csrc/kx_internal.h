@@ -398,9 +398,9 @@ kx_status launch_transport_batch(const MechDev &m, const WorkList *wl, int *coun
 // Sets the transport batch kernel's dynamic-LDS limit (before graph capture).
 kx_status prepare_transport_batch(const MechDev &m, int precision);
 kx_status launch_zero(int *p, int count, hipStream_t s);
-// Persistent grids of the batch kernels: waves of the rates batch kernel (16 per CU,
-// in workgroups of MechDev::wnw waves, or of one) and workgroups of the transport
-// batch kernel.
+// Persistent grids of the batch kernels: workgroups of the rates batch kernel above
+// kWideMaxSpecies (one wave, 16 per CU; the one-lane-per-point kernel fills the CUs by
+// its own shape) and of the transport batch kernel.
 constexpr int kRatesBatchGrid = 4096;
 constexpr int kTransportBatchGrid = 1024;
 // Counters a batch uses: one per XCD for the rates tiles, one for transport.

@@ -1194,7 +1194,13 @@ kx_status launch_rates_batch(const MechDev &m, const WorkList *wl, int *counter,
 {
     if (m.wnw) {
         void *args[] = {(void *)&m, (void *)&wl, (void *)&counter};
-        hipError_t e = hipLaunchKernel(wide_kernel<1>(precision, m.wnw), dim3(grid / m.wnw),
+        // as many workgroups as the CUs hold: one of 16 waves, or 24 waves (53 species,
+        // 65536 points 121 -> 103 us against 16 waves a CU, 100000 points 176 -> 147; 24
+        // species 60000 points 51 -> 47); of the smallest mechanisms' groups of four
+        // waves, whose tiles are over soonest, 16 (9 species, 100000 points 37 us, with
+        // 24 waves 40)
+        const int groups = 256 * (m.wnw == 16 ? 1 : (m.wnw == 4 ? 4 : 24 / m.wnw));
+        hipError_t e = hipLaunchKernel(wide_kernel<1>(precision, m.wnw), dim3(groups),
                                        dim3(m.wnw * kWave), args, wide_lds_bytes(m, precision, m.wnw), s);
         if (e != hipSuccess) return hip_fail(e, "rates batch kernel launch");
         return ok();
