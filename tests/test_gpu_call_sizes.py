@@ -175,3 +175,46 @@ def test_transport(name):
                 for a, b in zip(got[1:], out):
                     assert torch.equal(a, b[..., :m]), (sizes, m)
     dm.close()
+
+
+@pytest.mark.parametrize("name", list(QSS))
+def test_qss_forms_against_the_oracle(name):
+    """C_Q and wdot at sampled points of a call with several tiles to a CU, of one with a
+    CU to each tile and of one with a point per workgroup; the QSS rows of Y hold NaN."""
+    from paper_2411_02640_amd import kx
+
+    from . import test_gpu_qss as Q
+    mech = QSS[name]()
+    ns, n = mech["n_species"], 16384 + 70
+    T, p, Y = I.make_states(ns, I.StateSpec(n, seed=94, p_atm_range=(0.2, 40.0), dirichlet_alpha=0.3))
+    hidden = Y.copy()
+    hidden[np.flatnonzero(mech["qss"])] = np.nan
+    dm = kx.Mechanism(mech, 0)
+    for m in (n, 5000, 700):
+        print("[gpu-case] qss forms", name, m, flush=True)
+        w, C = Q.run_qss(kx, dm, T[:m], p[:m], np.ascontiguousarray(hidden[:, :m]))
+        i = np.unique(np.concatenate([np.arange(0, m, max(1, m // 90)), [63, 64, m - 1]]))
+        Q.compare(mech, w[:, i], C[:, i], T[i], p[i], np.ascontiguousarray(Y[:, i]), name)
+    dm.close()
+
+
+@pytest.mark.parametrize("ns", [24, 57])
+def test_served_rates(ns):
+    """The work-stealing and the one-tile-per-workgroup batches with 8 and 16 waves a
+    tile against direct calls."""
+    from paper_2411_02640_amd import kx
+    dm = kx.Mechanism(_mech(ns), 0)
+    d = _states(ns, 140000)
+    srv = kx.Server(0, hbm_budget=1 << 30, max_slots=16)
+    for sizes in ((1, 65, 700, 3000), (140000,)):
+        for prec in ("fp64", "mixed"):
+            print("[gpu-case] served rates", ns, sizes, prec, flush=True)
+            sets = [_first(d, m) for m in sizes]
+            torch.cuda.synchronize()
+            tickets = [srv.submit(dm, *s, precision=prec) for s in sets]
+            for t, s in zip(tickets, sets):
+                assert srv.wait(t)["state"] == "done"
+                assert torch.equal(srv.outputs(t)[0], kx.production_rates(dm, *s, precision=prec))
+                srv.release(t)
+    srv.close()
+    dm.close()
