@@ -3,10 +3,10 @@
 // Three kernels.  Mechanisms of up to kWideMaxSpecies species: one lane per point,
 // every species and reaction wave-uniform (kx_wide.h, rates_wide_tile below), or for
 // calls of few points one point per workgroup with the same arithmetic (kx_few.h,
-// rates_few_point).  Larger ones, whose species rows for 64 points exceed the LDS: lanes over
-// species and (reaction, point) pairs (rates_tile).
+// rates_few_point).  Larger ones, whose species rows for 64 points exceed the LDS:
+// lanes over species and (reaction, point) pairs (rates_tile).
 //
-// Both evaluate, per point,
+// All evaluate, per point,
 //  1. species: C_k, the Gibbs energy g_k = G_k/RT of eq:Ck (range by T_mid),
 //     a_k = (p_atm/RT) exp(-g_k) and b_k = C_k / a_k into LDS.  With these,
 //     prod_k C_k^nu' = A' B' and prod_k C_k^nu'' / K_c = A' B''
@@ -27,9 +27,9 @@
 // What bounds the one-lane-per-point kernel (53 species, FP64, 2^20 points;
 // measured 1.02 ms, 1.57 ms by the lanes-over-reactions form it replaced; 9
 // species 0.083 against 0.64 ms, 100 species at 2^18 points 0.77 against 0.94):
-// it issues about 400 vector and as many scalar instructions per point (657
-// vector ones before: the record decoding, the padded gather lists and the idle
-// lanes are gone), 65 % of the time the vector units could take at best; the rest
+// it issues about 400 vector and 310 scalar instructions per point (657 vector
+// ones before: the record decoding, the padded gather lists and the idle lanes
+// are gone), 65 % of the time the vector units could take at best; the rest
 // is the latency of the scalar loads that miss the 16 KB scalar cache (the
 // tables stream through it once per tile: their size and the number of waves
 // decide, see DevWide and wide_shape) and the chunk barriers.
@@ -216,14 +216,11 @@ struct PtVals {
     double T, lnT, invT, M, lnp;
 };
 
-// Rates of progress R_i = c_i k_f A' (B' - B'') of one reaction at the NPT
-// points of this lane (lane-private).  The record is decoded once; the LDS
-// reads of every point are issued before the first exponential, and the
-// points' exponentials are independent, so their chains interleave.
-template <bool MIXED, int NPT>
-__device__ __forceinline__ void rates_of_progress(const MechDev &m, const RxnWords &w,
-                                                  const char *const (&pb)[NPT],
-                                                  const PtVals (&q)[NPT], double (&R)[NPT])
+// Rate of progress R_i = c_i k_f A' (B' - B'') of one reaction at the point of
+// this lane.  The LDS reads are issued before the first exponential.
+template <bool MIXED>
+__device__ __forceinline__ double rate_of_progress(const MechDev &m, const RxnWords &w,
+                                                   const char *pb, const PtVals &q)
 {
     const double lnA = as_double(w.w0.x, w.w0.y);
     const double beta = as_double(w.w0.z, w.w0.w);
@@ -245,120 +242,80 @@ __device__ __forceinline__ void rates_of_progress(const MechDev &m, const RxnWor
     // (such reactions are sorted together, so the branch is mostly wave-uniform),
     // or interpolated in ln p for a pressure-table reaction
     const bool kconst = (flags & kFlagKfConst) != 0;
-    double xf[NPT];
-#pragma unroll
-    for (int j = 0; j < NPT; ++j)
-        xf[j] = kconst ? lnA : fma(beta, q[j].lnT, fma(-ER, q[j].invT, lnA));
+    double xf = kconst ? lnA : fma(beta, q.lnT, fma(-ER, q.invT, lnA));
     if (type == KX_RXN_PLOG) {
         const DevAux &ax = m.aux[aux];
-#pragma unroll
-        for (int j = 0; j < NPT; ++j)
-            xf[j] = plog_exponent(m.plog + ax.plog_off, ax.plog_cnt, q[j].lnT, q[j].invT,
-                                  q[j].lnp);
+        xf = plog_exponent(m.plog + ax.plog_off, ax.plog_cnt, q.lnT, q.invT, q.lnp);
     }
     // the LDS reads go before the exponentials so that their latency hides behind them
-    Pair r0[NPT], r1[NPT];
-    double bp0[NPT], bp1[NPT];
-#pragma unroll
-    for (int j = 0; j < NPT; ++j) {
-        r0[j] = load_pair(pb[j], o0);
-        r1[j] = load_pair(pb[j], o1);
-        bp0[j] = load_b(pb[j], o3);
-        bp1[j] = load_b(pb[j], o4);
-    }
-    double kf[NPT], Ap[NPT], Bp[NPT], Bpp[NPT];
-#pragma unroll
-    for (int j = 0; j < NPT; ++j) {
-        kf[j] = A;
-        if (!kconst) kf[j] = MIXED ? exp_mixed(xf[j]) : kexp(xf[j]);
-    }
-#pragma unroll
-    for (int j = 0; j < NPT; ++j) {
-        Ap[j] = r0[j].a * r1[j].a;
-        Bp[j] = r0[j].b * r1[j].b;
-        Bpp[j] = bp0[j] * bp1[j];
-    }
+    const Pair r0 = load_pair(pb, o0), r1 = load_pair(pb, o1);
+    const double bp0 = load_b(pb, o3), bp1 = load_b(pb, o4);
+    double kf = A;
+    if (!kconst) kf = MIXED ? exp_mixed(xf) : kexp(xf);
+    double Ap = r0.a * r1.a, Bp = r0.b * r1.b, Bpp = bp0 * bp1;
     // third molecule slots: skipped by the whole wave when none of its
     // reactions has three molecules on a side (the dummy species gives 1)
     const unsigned o2 = w.w2.y & 0xFFFFu, o5 = w.w2.z >> 16;
     const unsigned dummy = 16u * (unsigned)m.ns;
     if (__builtin_amdgcn_ballot_w64(o2 != dummy || o5 != dummy) != 0) {
-#pragma unroll
-        for (int j = 0; j < NPT; ++j) {
-            const Pair r2 = load_pair(pb[j], o2);
-            Ap[j] *= r2.a;
-            Bp[j] *= r2.b;
-            Bpp[j] *= load_b(pb[j], o5);
-        }
+        const Pair r2 = load_pair(pb, o2);
+        Ap *= r2.a;
+        Bp *= r2.b;
+        Bpp *= load_b(pb, o5);
     }
     if (flags & kFlagOrders) {
         // explicit forward orders (irreversible): prod_k C_k^o_k, C_k = a_k b_k
         const DevAux &ax = m.aux[aux];
+        double s = 0.0;
+        bool zero = false;
 #pragma unroll
-        for (int j = 0; j < NPT; ++j) {
-            double s = 0.0;
-            bool zero = false;
-#pragma unroll
-            for (int e = 0; e < kMaxOrd; ++e) {
-                const double o = ax.oval[e];
-                if (o != 0.0) {
-                    const Pair qq = load_pair(pb[j], ax.ooff[e]);
-                    const double C = qq.a * qq.b;
-                    zero = zero || !(C > 0.0);
-                    s = fma(o, kln(fmax(C, DBL_MIN)), s);
-                }
+        for (int e = 0; e < kMaxOrd; ++e) {
+            const double o = ax.oval[e];
+            if (o != 0.0) {
+                const Pair qq = load_pair(pb, ax.ooff[e]);
+                const double C = qq.a * qq.b;
+                zero = zero || !(C > 0.0);
+                s = fma(o, kln(fmax(C, DBL_MIN)), s);
             }
-            Ap[j] = zero ? 0.0 : kexp(s);
-            Bp[j] = 1.0;
-            Bpp[j] = 0.0;
         }
+        Ap = zero ? 0.0 : kexp(s);
+        Bp = 1.0;
+        Bpp = 0.0;
     }
-    double c[NPT];
-#pragma unroll
-    for (int j = 0; j < NPT; ++j) c[j] = 1.0;
+    double c = 1.0;
     if (has_tb) {
         // FP64: the falloff data is read before the third-body sums, whose LDS
         // reads and products then cover its memory latency (the mixed path
         // reads it where it is used: the earlier read measured slower there)
         if (!MIXED && has_fo) fo = load_falloff(m.aux[aux]);
-        double X[NPT];
-#pragma unroll
-        for (int j = 0; j < NPT; ++j) {
-            X[j] = third_body(m, tb, pb[j], q[j].M);
-            c[j] = X[j];
-        }
+        const double X = third_body(m, tb, pb, q.M);
+        c = X;
         if (has_fo) {
             if (MIXED) fo = load_falloff(m.aux[aux]);
-#pragma unroll
-            for (int j = 0; j < NPT; ++j) {
-                // P_r = k_0 [X] / k_inf = e0 [X] with e0 = exp(x_0 - x_inf) (no division)
-                const double d0 =
-                    fma(fo.beta0, q[j].lnT, fma(-fo.ER0, q[j].invT, fo.lnA0)) - xf[j];
-                const double e0 = MIXED ? exp_mixed(d0) : kexp(d0);
-                const double Pr = e0 * X[j];
-                double F = 1.0;
-                if (type == KX_RXN_TROE || type == KX_RXN_SRI) {
-                    const bool sri = type == KX_RXN_SRI;
-                    if (MIXED) {
-                        F = (double)blend_F32(fo, sri, (float)q[j].T, (float)q[j].lnT,
-                                              (float)q[j].invT, log10_wide(Pr));
-                    } else {
-                        // ln max(P_r, DBL_MIN) without forming the logarithm of P_r
-                        const double lnPr =
-                            fmax(d0 + kln(fmax(X[j], DBL_MIN)), -708.39641853226410622);
-                        F = blend_F64(fo, sri, q[j].T, q[j].lnT, q[j].invT, lnPr);
-                    }
+            // P_r = k_0 [X] / k_inf = e0 [X] with e0 = exp(x_0 - x_inf) (no division)
+            const double d0 = fma(fo.beta0, q.lnT, fma(-fo.ER0, q.invT, fo.lnA0)) - xf;
+            const double e0 = MIXED ? exp_mixed(d0) : kexp(d0);
+            const double Pr = e0 * X;
+            double F = 1.0;
+            if (type == KX_RXN_TROE || type == KX_RXN_SRI) {
+                const bool sri = type == KX_RXN_SRI;
+                if (MIXED) {
+                    F = (double)blend_F32(fo, sri, (float)q.T, (float)q.lnT, (float)q.invT,
+                                          log10_wide(Pr));
+                } else {
+                    // ln max(P_r, DBL_MIN) without forming the logarithm of P_r
+                    const double lnPr = fmax(d0 + kln(fmax(X, DBL_MIN)), -708.39641853226410622);
+                    F = blend_F64(fo, sri, q.T, q.lnT, q.invT, lnPr);
                 }
-                // eq:c_i: P_r/(1+P_r) F; chemically activated: F/(1+P_r) with k_0 =
-                // e0 k_inf in r_i, i.e. c k_inf = e0 F/(1+P_r) k_inf
-                const double g = krcp(1.0 + Pr) * F;
-                c[j] = (flags & kFlagChemAct) ? e0 * g : Pr * g;
             }
+            // eq:c_i: P_r/(1+P_r) F; chemically activated: F/(1+P_r) with k_0 =
+            // e0 k_inf in r_i, i.e. c k_inf = e0 F/(1+P_r) k_inf
+            const double g = krcp(1.0 + Pr) * F;
+            c = (flags & kFlagChemAct) ? e0 * g : Pr * g;
         }
     }
     const double rev = (flags & kFlagReversible) ? 1.0 : 0.0;
-#pragma unroll
-    for (int j = 0; j < NPT; ++j) R[j] = c[j] * kf[j] * Ap[j] * fma(-rev, Bpp[j], Bp[j]);
+    return c * kf * Ap * fma(-rev, Bpp, Bp);
 }
 
 // Gibbs energy g = G/RT of one species at one temperature (eq:Ck with the
@@ -369,35 +326,36 @@ __device__ __forceinline__ double gibbs(const double (&g)[7], double T, double l
     return fma(g[0], 1.0 - lnT, poly) + fma(g[5], invT, g[6]);
 }
 
+// The lanes-over-reactions kernel: points per tile, and species per lane in the
+// species phases (mechanisms above 128 species).
+constexpr int kPts = 2;
+constexpr int kSpl = 4;
+
 // Two groups' partial sums ga, gb per trip of a gather loop: FP64 adds each to
 // the running sum as it is formed (first_of_pair, then second_of_pair); the
 // mixed path adds their sum with one compensated step (the two groups' plain
 // sum carries FP64 rounding, far below the mixed path's error).
-template <bool MIXED, int PS>
-__device__ __forceinline__ void first_of_pair(double (&acc)[PS], const double (&ga)[PS])
+template <bool MIXED>
+__device__ __forceinline__ void first_of_pair(double (&acc)[kPts], const double (&ga)[kPts])
 {
     if (!MIXED) {
 #pragma unroll
-        for (int j = 0; j < PS; ++j) acc[j] += ga[j];
+        for (int j = 0; j < kPts; ++j) acc[j] += ga[j];
     }
 }
 
-template <bool MIXED, int PS>
-__device__ __forceinline__ void second_of_pair(double (&acc)[PS], double (&cmp)[PS],
-                                               const double (&ga)[PS], const double (&gb)[PS])
+template <bool MIXED>
+__device__ __forceinline__ void second_of_pair(double (&acc)[kPts], double (&cmp)[kPts],
+                                               const double (&ga)[kPts], const double (&gb)[kPts])
 {
 #pragma unroll
-    for (int j = 0; j < PS; ++j) {
+    for (int j = 0; j < kPts; ++j) {
         if (MIXED)
             accumulate<true>(acc[j], cmp[j], ga[j] + gb[j]);
         else
             acc[j] += gb[j];
     }
 }
-
-// Points per tile and per step of the lanes-over-reactions kernel.
-__host__ __device__ constexpr int rates_tile_points_for(int) { return 2; }
-__host__ __device__ constexpr int rates_step_points_for(int) { return 2; }
 
 // Per-point constants of a tile, computed once per point (lane = point).
 struct PointConst {
@@ -406,20 +364,18 @@ struct PointConst {
     double lnp, pad;         // ln p (pressure-table reactions)
 };
 
-// LDS layout of one workgroup (one wave), PS = points per step:
-//   sq    rates of progress of the current chunk for the points of a step:
-//         [chunk + 1][2], the two points side by side;
-//         slot `chunk` is zero and absorbs the gather padding; at byte 0 so that
-//         the gather offsets are LDS addresses
-//   pairs [PS][ns + 1] {a, b} per point (entry ns is the dummy species, {1, 1})
-//   pc    [tp]              PointConst of the tile's points
-//   Yt    [ns][tp + 1]      Y tile in, wdot tile out (coalesced row loads/stores)
-// One tile of `npts` (<= tp) points starting at point i0 of arrays whose
-// species rows have stride ld, PS points per step:
-//   phase 1 -- lane = species, every point of the step;
-//   phase 2 -- lane = (reaction, point): lanes 2r and 2r+1 take reaction r, lane
-//              2r + j for point j of the step, so a group of 32 falloff
-//              reactions fills a whole 64-lane iteration;
+// LDS layout of one workgroup (one wave):
+//   sq    [chunk + 1][2]    rates of progress of the current chunk, the two points
+//         side by side; slot `chunk` is zero and absorbs the gather padding; at byte
+//         0 so that the gather offsets are LDS addresses
+//   pairs [2][ns + 1]       {a, b} per point (entry ns is the dummy species, {1, 1})
+//   pc    [2]               PointConst of the tile's points
+//   Yt    [ns][3]           Y tile in, wdot tile out (coalesced row loads/stores)
+// One tile of `npts` (<= 2) points starting at point i0 of arrays whose species
+// rows have stride ld:
+//   phase 1 -- lane = species, both points;
+//   phase 2 -- lane = (reaction, point): lane 2r + j takes reaction r at point j, so
+//              a group of 32 falloff reactions fills a whole 64-lane iteration;
 //   phase 3 -- lane = species: one 16-byte LDS read per list entry returns the
 //              rate of progress of the reaction at both points.
 // Two other forms were measured against this one for 200 species (1500 reactions,
@@ -443,26 +399,26 @@ __device__ __forceinline__ unsigned lds_base()
     return (unsigned)(size_t)(__attribute__((address_space(3))) double *)lds;
 }
 
-// ---- phase 3: wdot_k = sum_i nu_ki R_i for the PS points of a step, one
-// chunk of reactions.  Lane = species (SPL per lane); a group is eight list
-// entries, summed plainly per point (the mixed path compensates the running
-// sum once per two groups).  All reads of a group are issued before the first sum (left to itself the scheduler waits
-// for each read in turn), and two groups are handled per trip with
-// alternating offset registers (the next group's offsets in flight).
+// ---- phase 3: wdot_k = sum_i nu_ki R_i for both points, one chunk of reactions.
+// Lane = species (kSpl per lane); a group is eight list entries, summed plainly per
+// point (the mixed path compensates the running sum once per two groups).  All reads
+// of a group are issued before the first sum (left to itself the scheduler waits for
+// each read in turn), and two groups are handled per trip with alternating offset
+// registers (the next group's offsets in flight).
 //
 // gather_split: a +q list and a -q list per species, each padded to whole
-// groups (the group's sum is negated for the -q groups); two points per step.
-template <bool MIXED, int SPL, bool DIRECT, int PS>
+// groups (the group's sum is negated for the -q groups).
+template <bool MIXED, bool DIRECT>
 __device__ __forceinline__ void gather_split(const MechDev &m, int c, int gw, int lane,
-                                             const char *qb, double (&acc)[SPL][PS],
-                                             double (&cmp)[SPL][PS])
+                                             const char *qb, double (&acc)[kSpl][kPts],
+                                             double (&cmp)[kSpl][kPts])
 {
     const int npos = m.gpos[c], ngrp = npos + m.gneg[c];
     const uint4 *ge = m.gent + ((size_t)m.goff[c] * gw + lane) * 2;
 #pragma unroll
-    for (int s = 0; s < SPL; ++s) {
+    for (int s = 0; s < kSpl; ++s) {
         const uint4 *g = ge + 2 * kWave * s;
-        auto group = [&](const uint4 &v0, const uint4 &v1, int it, double (&gs)[PS]) {
+        auto group = [&](const uint4 &v0, const uint4 &v1, int it, double (&gs)[kPts]) {
             const unsigned off[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
             double2 q2[8];
 #pragma unroll
@@ -493,21 +449,21 @@ __device__ __forceinline__ void gather_split(const MechDev &m, int c, int gw, in
         for (; it + 1 < ngrp; it += 2) {
             b0 = g[(size_t)(it + 1) * 2 * gw];
             b1 = g[(size_t)(it + 1) * 2 * gw + 1];
-            double ga[PS], gb[PS];
+            double ga[kPts], gb[kPts];
             group(a0, a1, it, ga);
-            first_of_pair<MIXED, PS>(acc[s], ga);
+            first_of_pair<MIXED>(acc[s], ga);
             if (it + 2 < ngrp) {
                 a0 = g[(size_t)(it + 2) * 2 * gw];
                 a1 = g[(size_t)(it + 2) * 2 * gw + 1];
             }
             group(b0, b1, it + 1, gb);
-            second_of_pair<MIXED, PS>(acc[s], cmp[s], ga, gb);
+            second_of_pair<MIXED>(acc[s], cmp[s], ga, gb);
         }
         if (it < ngrp) {
-            double ga[PS];
+            double ga[kPts];
             group(a0, a1, it, ga);
 #pragma unroll
-            for (int j = 0; j < PS; ++j) accumulate<MIXED>(acc[s][j], cmp[s][j], ga[j]);
+            for (int j = 0; j < kPts; ++j) accumulate<MIXED>(acc[s][j], cmp[s][j], ga[j]);
         }
     }
 }
@@ -515,32 +471,27 @@ __device__ __forceinline__ void gather_split(const MechDev &m, int c, int gw, in
 // `lane` is threadIdx.x; the batch kernel passes it through an opaque move in
 // each trip of its tile loop, so that the tile's lane-dependent addresses are
 // not hoisted out of the loop (kept live across tiles they cost registers).
-template <bool MIXED, int SPL, bool DIRECT>
+template <bool MIXED, bool DIRECT>
 __device__ __forceinline__ void rates_tile(int lane, const MechDev &m, int64_t ld, int64_t i0,
-                                           int npts,
-                                           int tp, const double *__restrict__ T,
+                                           int npts, const double *__restrict__ T,
                                            const double *__restrict__ P,
                                            const double *__restrict__ Y,
                                            double *__restrict__ wdot)
 {
     extern __shared__ double lds[];
-    constexpr int TP = rates_tile_points_for(SPL);  // == tp
-    constexpr int PS = rates_step_points_for(SPL);  // points per step
-    constexpr int NPT = PS / 2;                     // points per lane in phase 2
-    constexpr int NGW = kWave / TP;                 // species groups of the W-bar pass
+    constexpr int NGW = kWave / kPts;  // species groups of the W-bar pass
     const int ns = m.ns;
-    const int ys = TP + 1;
+    const int ys = kPts + 1;
     double *sq = lds;
     double *pairs = sq + (2 * (m.chunk + 1));
-    PointConst *pc = reinterpret_cast<PointConst *>(pairs + 2 * PS * (ns + 1));
-    double *Yt = reinterpret_cast<double *>(pc + TP);
+    PointConst *pc = reinterpret_cast<PointConst *>(pairs + 2 * kPts * (ns + 1));
+    double *Yt = reinterpret_cast<double *>(pc + kPts);
     const char *qb = reinterpret_cast<const char *>(sq);
-    (void)tp;
 
     // the temperature and pressure of the tile's points are read first, so
     // that their memory latency overlaps the Y tile's
     double Tl = 0.0, Pl = 0.0;
-    if (lane < TP) {
+    if (lane < kPts) {
         const int64_t i = i0 + min(lane, npts - 1);
         Tl = T[i];
         Pl = P[i];
@@ -548,17 +499,17 @@ __device__ __forceinline__ void rates_tile(int lane, const MechDev &m, int64_t l
     // the tile's Y, eight row loads per lane in flight before the first LDS
     // store (a loop of load-wait-store would pay one memory latency per row)
     constexpr int kLd = 8;
-    for (int e0 = lane; e0 < ns * TP; e0 += kLd * kWave) {
+    for (int e0 = lane; e0 < ns * kPts; e0 += kLd * kWave) {
         double v[kLd];
 #pragma unroll
         for (int u = 0; u < kLd; ++u) {
-            const int e = e0 + u * kWave, k = e / TP, c = e % TP;
-            v[u] = (e < ns * TP && c < npts) ? Y[(int64_t)k * ld + i0 + c] : 0.0;
+            const int e = e0 + u * kWave, k = e / kPts, c = e % kPts;
+            v[u] = (e < ns * kPts && c < npts) ? Y[(int64_t)k * ld + i0 + c] : 0.0;
         }
 #pragma unroll
         for (int u = 0; u < kLd; ++u) {
             const int e = e0 + u * kWave;
-            if (e < ns * TP) Yt[(e / TP) * ys + e % TP] = v[u];
+            if (e < ns * kPts) Yt[(e / kPts) * ys + e % kPts] = v[u];
         }
     }
     __syncthreads();
@@ -566,7 +517,7 @@ __device__ __forceinline__ void rates_tile(int lane, const MechDev &m, int64_t l
         // sum_k Y_k / W_k = 1 / W-bar: lane = (point, species group); the
         // group partials meet in the (still unused) rate-of-progress array.
         // The 1/W_k of eight species are loaded before they are used.
-        const int c = lane % TP, g = lane / TP;
+        const int c = lane % kPts, g = lane / kPts;
         const int cc = min(c, npts - 1);  // padding points repeat the last one
         double part = 0.0;
         for (int k0 = g; k0 < ns; k0 += kLd * NGW) {
@@ -582,13 +533,13 @@ __device__ __forceinline__ void rates_tile(int lane, const MechDev &m, int64_t l
                 if (k < ns) part = fma(Yt[k * ys + cc], iw[u], part);
             }
         }
-        sq[g * TP + c] = part;
+        sq[g * kPts + c] = part;
     }
     __syncthreads();
-    if (lane < TP) {
+    if (lane < kPts) {
         double wsum = 0.0;
 #pragma unroll
-        for (int g = 0; g < NGW; ++g) wsum += sq[g * TP + lane];
+        for (int g = 0; g < NGW; ++g) wsum += sq[g * kPts + lane];
         PointConst q;
         q.T = Tl;
         q.lnT = kln(q.T);
@@ -602,7 +553,7 @@ __device__ __forceinline__ void rates_tile(int lane, const MechDev &m, int64_t l
         pc[lane] = q;
     }
     __syncthreads();
-    if (lane < PS) {
+    if (lane < kPts) {
         pairs[2 * ns + 2 * (ns + 1) * lane] = 1.0;
         pairs[2 * ns + 2 * (ns + 1) * lane + 1] = 1.0;
     }
@@ -610,111 +561,98 @@ __device__ __forceinline__ void rates_tile(int lane, const MechDev &m, int64_t l
         sq[2 * m.chunk + lane] = 0.0;
     }
 
-    const int jl = lane & 1;   // point of this lane in phase 2 (and jl + 2)
+    const int jl = lane & 1;   // point of this lane in phase 2
     const int rl = lane >> 1;  // reaction slot of this lane in phase 2
-    const char *pbl[NPT];
-#pragma unroll
-    for (int j = 0; j < NPT; ++j)
-        pbl[j] = reinterpret_cast<const char *>(pairs + 2 * (ns + 1) * (jl + 2 * j));
+    const char *pbl = reinterpret_cast<const char *>(pairs + 2 * (ns + 1) * jl);
     const int gw = kWave * m.gpass;
-    for (int pl = 0; pl < npts; pl += PS) {
-        // ---- phase 1: species (every point of the step per lane)
-        PointConst ps[PS];
+    // ---- phase 1: species (both points per lane)
+    PointConst ps[kPts];
 #pragma unroll
-        for (int j = 0; j < PS; ++j) ps[j] = pc[pl + j];
+    for (int j = 0; j < kPts; ++j) ps[j] = pc[j];
 #pragma unroll
-        for (int s = 0; s < SPL; ++s) {
-            const int k = lane + kWave * s;
-            if (k < ns) {
-                // both temperature ranges' coefficients are read once per step
-                // and selected per point (one read per point would cost the
-                // vector-memory unit four times as many loads), from the
-                // by-field table (a wave's read is one contiguous row)
-                const double *gs = m.gsoa + (size_t)s * 16 * kWave + lane;
-                // the same rows every step: read them per step (kept in
-                // registers across the steps they would cost spills)
-                asm volatile("" : "+v"(gs));
-                double glo[7], ghi[7];
+    for (int s = 0; s < kSpl; ++s) {
+        const int k = lane + kWave * s;
+        if (k < ns) {
+            // both temperature ranges' coefficients are read once per tile
+            // and selected per point (one read per point would cost the
+            // vector-memory unit four times as many loads), from the
+            // by-field table (a wave's read is one contiguous row)
+            const double *gs = m.gsoa + (size_t)s * 16 * kWave + lane;
+            // the same rows every step: read them per step (kept in
+            // registers across the steps they would cost spills)
+            asm volatile("" : "+v"(gs));
+            double glo[7], ghi[7];
 #pragma unroll
-                for (int e = 0; e < 7; ++e) {
-                    glo[e] = gs[e * kWave];
-                    ghi[e] = gs[(7 + e) * kWave];
-                }
-                const double tmid = gs[14 * kWave], iw = gs[15 * kWave];
-#pragma unroll
-                for (int j = 0; j < PS; ++j) {
-                    const PointConst &q = ps[j];
-                    double g[7];
-                    const bool lo = q.T < tmid;
-#pragma unroll
-                    for (int e = 0; e < 7; ++e) g[e] = lo ? glo[e] : ghi[e];
-                    const double ak = q.P0 * kexp(-gibbs(g, q.T, q.lnT, q.invT));
-                    const double Ck = Yt[k * ys + pl + j] * iw * q.cf;
-                    double *pr = pairs + 2 * (ns + 1) * j + 2 * k;
-                    pr[0] = ak;
-                    pr[1] = Ck * krcp(ak);
-                }
+            for (int e = 0; e < 7; ++e) {
+                glo[e] = gs[e * kWave];
+                ghi[e] = gs[(7 + e) * kWave];
             }
-        }
-        wave_sync();
-        // the points of this lane in phase 2
-        PtVals qv[NPT];
+            const double tmid = gs[14 * kWave], iw = gs[15 * kWave];
 #pragma unroll
-        for (int j = 0; j < NPT; ++j) {
-            const PointConst &q = pc[pl + jl + 2 * j];  // LDS (a lane-dependent index)
-            qv[j] = PtVals{q.T, q.lnT, q.invT, q.M, q.lnp};
-        }
-
-        // ---- phases 2 and 3, one chunk of reactions at a time
-        double acc[SPL][PS], cmp[SPL][PS];
+            for (int j = 0; j < kPts; ++j) {
+                const PointConst &q = ps[j];
+                double g[7];
+                const bool lo = q.T < tmid;
 #pragma unroll
-        for (int s = 0; s < SPL; ++s)
-#pragma unroll
-            for (int j = 0; j < PS; ++j) acc[s][j] = cmp[s][j] = 0.0;
-        for (int c = 0; c < m.nchunks; ++c) {
-            const int base = c * m.chunk;
-            const int cnt = min(m.chunk, m.nr - base);
-            // 48-byte reaction records as three 16-byte loads, the next
-            // iteration's record in flight while this one is evaluated
-            const uint4 *rsrc = reinterpret_cast<const uint4 *>(m.rxn + base);
-            RxnWords w;
-            w.w0 = w.w1 = w.w2 = make_uint4(0, 0, 0, 0);
-            if (rl < cnt) {
-                w.w0 = rsrc[3 * rl];
-                w.w1 = rsrc[3 * rl + 1];
-                w.w2 = rsrc[3 * rl + 2];
-            }
-            for (int r = rl; r < cnt; r += kWave / 2) {
-                const RxnWords cur = w;
-                const int rn = r + kWave / 2;
-                if (rn < cnt) {
-                    w.w0 = rsrc[3 * rn];
-                    w.w1 = rsrc[3 * rn + 1];
-                    w.w2 = rsrc[3 * rn + 2];
-                }
-                double R[NPT];
-                rates_of_progress<MIXED, NPT>(m, cur, pbl, qv, R);
-                sq[2 * r + jl] = R[0];
-            }
-            wave_sync();
-            gather_split<MIXED, SPL, DIRECT, PS>(m, c, gw, lane, qb, acc, cmp);
-            wave_sync();
-        }
-        // the rates of progress were stored as points (0, 1) and (2, 3); the
-        // accumulators follow the same order
-#pragma unroll
-        for (int s = 0; s < SPL; ++s) {
-            const int k = lane + kWave * s;
-            if (k < ns) {
-#pragma unroll
-                for (int j = 0; j < PS; ++j)
-                    Yt[k * ys + pl + j] = MIXED ? acc[s][j] + cmp[s][j] : acc[s][j];
+                for (int e = 0; e < 7; ++e) g[e] = lo ? glo[e] : ghi[e];
+                const double ak = q.P0 * kexp(-gibbs(g, q.T, q.lnT, q.invT));
+                const double Ck = Yt[k * ys + j] * iw * q.cf;
+                double *pr = pairs + 2 * (ns + 1) * j + 2 * k;
+                pr[0] = ak;
+                pr[1] = Ck * krcp(ak);
             }
         }
     }
+    wave_sync();
+    // the point of this lane in phase 2
+    const PointConst &ql = pc[jl];  // LDS (a lane-dependent index)
+    const PtVals qv{ql.T, ql.lnT, ql.invT, ql.M, ql.lnp};
+
+    // ---- phases 2 and 3, one chunk of reactions at a time
+    double acc[kSpl][kPts], cmp[kSpl][kPts];
+#pragma unroll
+    for (int s = 0; s < kSpl; ++s)
+#pragma unroll
+        for (int j = 0; j < kPts; ++j) acc[s][j] = cmp[s][j] = 0.0;
+    for (int c = 0; c < m.nchunks; ++c) {
+        const int base = c * m.chunk;
+        const int cnt = min(m.chunk, m.nr - base);
+        // 48-byte reaction records as three 16-byte loads, the next
+        // iteration's record in flight while this one is evaluated
+        const uint4 *rsrc = reinterpret_cast<const uint4 *>(m.rxn + base);
+        RxnWords w;
+        w.w0 = w.w1 = w.w2 = make_uint4(0, 0, 0, 0);
+        if (rl < cnt) {
+            w.w0 = rsrc[3 * rl];
+            w.w1 = rsrc[3 * rl + 1];
+            w.w2 = rsrc[3 * rl + 2];
+        }
+        for (int r = rl; r < cnt; r += kWave / 2) {
+            const RxnWords cur = w;
+            const int rn = r + kWave / 2;
+            if (rn < cnt) {
+                w.w0 = rsrc[3 * rn];
+                w.w1 = rsrc[3 * rn + 1];
+                w.w2 = rsrc[3 * rn + 2];
+            }
+            sq[2 * r + jl] = rate_of_progress<MIXED>(m, cur, pbl, qv);
+        }
+        wave_sync();
+        gather_split<MIXED, DIRECT>(m, c, gw, lane, qb, acc, cmp);
+        wave_sync();
+    }
+#pragma unroll
+    for (int s = 0; s < kSpl; ++s) {
+        const int k = lane + kWave * s;
+        if (k < ns) {
+#pragma unroll
+            for (int j = 0; j < kPts; ++j)
+                Yt[k * ys + j] = MIXED ? acc[s][j] + cmp[s][j] : acc[s][j];
+        }
+    }
     __syncthreads();
-    for (int e = lane; e < ns * TP; e += kWave) {
-        const int k = e / TP, c = e % TP;
+    for (int e = lane; e < ns * kPts; e += kWave) {
+        const int k = e / kPts, c = e % kPts;
         if (c < npts) wdot[(int64_t)k * ld + i0 + c] = Yt[k * ys + c];
     }
     __syncthreads();  // the LDS tile may be reused by the next tile
@@ -735,16 +673,16 @@ __device__ __forceinline__ unsigned xcd_tile(unsigned b, unsigned nblk)
 // kernel has no static LDS (its dynamic LDS then starts at address 0); the
 // host checks the kernel's static LDS size and launches the DIRECT = false
 // instance otherwise.
-template <bool MIXED, int SPL, bool DIRECT>
-__global__ __launch_bounds__(kWave, SPL == 1 ? 3 : 2) void rates_kernel(MechDev m, int64_t n,
+template <bool MIXED, bool DIRECT>
+__global__ __launch_bounds__(kWave, 2) void rates_kernel(MechDev m, int64_t n,
                                                       const double *__restrict__ T,
                                                       const double *__restrict__ P,
                                                       const double *__restrict__ Y,
-                                                      double *__restrict__ wdot, int tp)
+                                                      double *__restrict__ wdot)
 {
-    const int64_t i0 = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * tp;
-    const int np = (int)min((int64_t)tp, n - i0);
-    rates_tile<MIXED, SPL, DIRECT>(threadIdx.x, m, n, i0, np, tp, T, P, Y, wdot);
+    const int64_t i0 = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * kPts;
+    const int np = (int)min((int64_t)kPts, n - i0);
+    rates_tile<MIXED, DIRECT>(threadIdx.x, m, n, i0, np, T, P, Y, wdot);
 }
 
 // Batched requests.  The batch's tiles are split into kXcds contiguous ranges,
@@ -761,10 +699,10 @@ __global__ __launch_bounds__(kWave, SPL == 1 ? 3 : 2) void rates_kernel(MechDev 
 // atomic round trip; four tiles per ticket spread it.
 constexpr int kTicketTiles = 4;
 
-template <bool MIXED, int SPL, bool DIRECT>
-__global__ __launch_bounds__(kWave, SPL == 1 ? 3 : 2) void rates_batch_kernel(MechDev m,
+template <bool MIXED, bool DIRECT>
+__global__ __launch_bounds__(kWave, 2) void rates_batch_kernel(MechDev m,
                                                             const WorkList *__restrict__ wl,
-                                                            int *__restrict__ counter, int tp)
+                                                            int *__restrict__ counter)
 {
     const int ntiles = wl->ntiles[0];
     const int x0 = (int)(blockIdx.x % kXcds);
@@ -787,11 +725,11 @@ __global__ __launch_bounds__(kWave, SPL == 1 ? 3 : 2) void rates_batch_kernel(Me
             if (t >= hi) break;
             r = work_item_of(wl, 0, t, r);
             const WorkItem it = wl->items[r];
-            const int64_t i0 = (int64_t)(t - wl->start[0][r]) * tp;
-            const int np = (int)min((int64_t)tp, it.n - i0);
+            const int64_t i0 = (int64_t)(t - wl->start[0][r]) * kPts;
+            const int np = (int)min((int64_t)kPts, it.n - i0);
             int lane;
             asm volatile("v_mov_b32 %0, %1" : "=v"(lane) : "v"((int)threadIdx.x));
-            rates_tile<MIXED, SPL, DIRECT>(lane, m, it.n, i0, np, tp, it.T, it.p, it.Y, it.wdot);
+            rates_tile<MIXED, DIRECT>(lane, m, it.n, i0, np, it.T, it.p, it.Y, it.wdot);
         }
     }
 }
@@ -800,18 +738,18 @@ __global__ __launch_bounds__(kWave, SPL == 1 ? 3 : 2) void rates_batch_kernel(Me
 // to XCDs as in a direct launch; the item of tile t by work_item_ballot).
 // Persistent workgroups that take tickets measured about a tenth slower per
 // tile than this one-tile form.
-template <bool MIXED, int SPL, bool DIRECT>
-__global__ __launch_bounds__(kWave, SPL == 1 ? 3 : 2) void rates_items_kernel(
-    MechDev m, const WorkList *__restrict__ wl, int tp)
+template <bool MIXED, bool DIRECT>
+__global__ __launch_bounds__(kWave, 2) void rates_items_kernel(
+    MechDev m, const WorkList *__restrict__ wl)
 {
     const int ntiles = wl->ntiles[0];
     const int t = (int)xcd_tile(blockIdx.x, gridDim.x);
     if (t >= ntiles) return;
     const int r = work_item_ballot(wl, 0, t);
     const WorkItem it = wl->items[r];
-    const int64_t i0 = (int64_t)(t - wl->start[0][r]) * tp;
-    const int np = (int)min((int64_t)tp, it.n - i0);
-    rates_tile<MIXED, SPL, DIRECT>(threadIdx.x, m, it.n, i0, np, tp, it.T, it.p, it.Y, it.wdot);
+    const int64_t i0 = (int64_t)(t - wl->start[0][r]) * kPts;
+    const int np = (int)min((int64_t)kPts, it.n - i0);
+    rates_tile<MIXED, DIRECT>(threadIdx.x, m, it.n, i0, np, it.T, it.p, it.Y, it.wdot);
 }
 
 // ---------------------------------------------------------------------------
@@ -1035,19 +973,17 @@ int64_t rates_tail(const MechDev &m, int64_t n)
     return tail > 0 && tail <= most && rates_few_threads(m, tail) ? tail : 0;
 }
 
-size_t rates_lds_bytes(const MechDev &m, int tp)
+size_t rates_lds_bytes(const MechDev &m)
 {
-    const int ps = rates_step_points_for(m.gpass);
-    const size_t sq = 2 * (size_t)(m.chunk + 1);
-    return sizeof(double) * (sq + 2 * (size_t)ps * (m.ns + 1) + 8 * (size_t)tp +
-                             (size_t)m.ns * (tp + 1));
+    return sizeof(double) * (2 * (size_t)(m.chunk + 1) + 2 * (size_t)kPts * (m.ns + 1) +
+                             8 * kPts + (size_t)m.ns * (kPts + 1));
 }
 
 }  // namespace
 
 int rates_tile_points(const MechDev &m)
 {
-    return m.wnw ? kRow : rates_tile_points_for(m.gpass);
+    return m.wnw ? kRow : kPts;
 }
 
 int rates_items_tile_points(const MechDev &m, int64_t points)
@@ -1081,7 +1017,6 @@ kx_status launch_rates(const kx_mech *mech, int64_t n, const double *T, const do
                        const double *Y, double *wdot, int precision, hipStream_t s)
 {
     const MechDev &m = mech->dev;
-    const int tp = rates_tile_points(m);
     if (m.wnw) {
         const int64_t tail = rates_few_threads(m, n) ? n : rates_tail(m, n), body = n - tail;
         const int64_t nblk = (body + kRow - 1) / kRow;
@@ -1101,43 +1036,40 @@ kx_status launch_rates(const kx_mech *mech, int64_t n, const double *T, const do
                         (void *)&p, (void *)&Y,         (void *)&wdot};
         return launch_few<false>(m, precision, rates_few_threads(m, tail), tail, args, s);
     }
-    const size_t lds = rates_lds_bytes(m, tp);
+    const size_t lds = rates_lds_bytes(m);
     if (lds > 160 * 1024)
         return fail(KX_EUNSUPPORTED, "production rates: mechanism too large for LDS");
-    const int64_t nblk = (n + tp - 1) / tp;
+    const int64_t nblk = (n + kPts - 1) / kPts;
     if (nblk > 0x7fffffff) return fail(KX_EINVAL, "production rates: n too large");
     auto pick = [&](auto mixed) {
         constexpr bool M = decltype(mixed)::value;
-        return pick_direct(rates_kernel<M, 4, true>, rates_kernel<M, 4, false>);
+        return pick_direct(rates_kernel<M, true>, rates_kernel<M, false>);
     };
     auto kern = precision == KX_MIXED ? pick(std::true_type{}) : pick(std::false_type{});
     kx_status st = set_lds(kern, lds);
     if (st != KX_OK) return st;
-    return launch_tiles(n, tp, kWave, [&](int64_t i, int64_t groups) {
+    return launch_tiles(n, kPts, kWave, [&](int64_t i, int64_t groups) {
         hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(kWave), lds, s, m, n, T + i, p + i,
-                           Y + i, wdot + i, tp);
+                           Y + i, wdot + i);
         hipError_t e = hipGetLastError();
         return e != hipSuccess ? hip_fail(e, "rates kernel launch") : KX_OK;
     });
 }
 
 namespace {
-auto pick_batch(const MechDev &m, int precision)
+auto pick_batch(int precision)
 {
     auto pick = [&](auto mixed) {
         constexpr bool M = decltype(mixed)::value;
-        return pick_direct(rates_batch_kernel<M, 4, true>, rates_batch_kernel<M, 4, false>);
+        return pick_direct(rates_batch_kernel<M, true>, rates_batch_kernel<M, false>);
     };
     return precision == KX_MIXED ? pick(std::true_type{}) : pick(std::false_type{});
 }
-}  // namespace
-
-namespace {
-auto pick_items(const MechDev &m, int precision)
+auto pick_items(int precision)
 {
     auto pick = [&](auto mixed) {
         constexpr bool M = decltype(mixed)::value;
-        return pick_direct(rates_items_kernel<M, 4, true>, rates_items_kernel<M, 4, false>);
+        return pick_direct(rates_items_kernel<M, true>, rates_items_kernel<M, false>);
     };
     return precision == KX_MIXED ? pick(std::true_type{}) : pick(std::false_type{});
 }
@@ -1161,14 +1093,13 @@ kx_status launch_rates_items(const MechDev &m, const FewDev *few, const WorkList
     }
     if (ntiles > max_workgroups(kWave))
         return fail(KX_EINVAL, "production rates: too many tiles");
-    const int tp = rates_tile_points(m);
-    const size_t lds = rates_lds_bytes(m, tp);
+    const size_t lds = rates_lds_bytes(m);
     if (lds > 160 * 1024)
         return fail(KX_EUNSUPPORTED, "production rates: mechanism too large for LDS");
-    auto kern = pick_items(m, precision);
+    auto kern = pick_items(precision);
     kx_status st = set_lds(kern, lds);
     if (st != KX_OK) return st;
-    hipLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(kWave), lds, s, m, wl, tp);
+    hipLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(kWave), lds, s, m, wl);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "rates items kernel launch");
     return ok();
@@ -1183,10 +1114,10 @@ kx_status prepare_rates_batch(const MechDev &m, int precision)
         if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute (rates)");
         return KX_OK;
     }
-    const size_t lds = rates_lds_bytes(m, rates_tile_points(m));
+    const size_t lds = rates_lds_bytes(m);
     if (lds > 160 * 1024)
         return fail(KX_EUNSUPPORTED, "production rates: mechanism too large for LDS");
-    return set_lds(pick_batch(m, precision), lds);
+    return set_lds(pick_batch(precision), lds);
 }
 
 kx_status launch_rates_batch(const MechDev &m, const WorkList *wl, int *counter, int precision,
@@ -1205,10 +1136,9 @@ kx_status launch_rates_batch(const MechDev &m, const WorkList *wl, int *counter,
         if (e != hipSuccess) return hip_fail(e, "rates batch kernel launch");
         return ok();
     }
-    const int tp = rates_tile_points(m);
-    const size_t lds = rates_lds_bytes(m, tp);
-    hipLaunchKernelGGL(pick_batch(m, precision), dim3(grid), dim3(kWave), lds, s, m, wl,
-                       counter, tp);
+    const size_t lds = rates_lds_bytes(m);
+    hipLaunchKernelGGL(pick_batch(precision), dim3(grid), dim3(kWave), lds, s, m, wl,
+                       counter);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "rates batch kernel launch");
     return ok();
