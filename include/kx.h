@@ -208,7 +208,10 @@ kx_status kx_mech_info(const kx_mech *mech, int32_t *n_species, int32_t *n_react
  * solved first (see kx_qss_concentrations) and enter the rates of progress;
  * the mixture is that of the transported species (W-bar from their mass
  * fractions, third-body sums over them), the QSS entries of Y are not read and
- * the QSS rows of wdot are written as 0 (their balance). */
+ * the QSS rows of wdot are written as 0 (their balance).
+ * The kernel's form follows the number of points, a point's results do not: they
+ * are the same bits in a call of any size (also those of kx_qss_concentrations and
+ * kx_transport, in both precisions). */
 kx_status kx_production_rates(const kx_mech *mech, int64_t n, const double *T,
                               const double *p, const double *Y, double *wdot,
                               hipStream_t stream);
@@ -296,9 +299,9 @@ kx_status kx_qss_concentrations(const kx_mech *mech, int64_t n, const double *T,
  * batch over a device work list on one of several streams -- batches of
  * different groups overlap on the device.  A batch of fewer than 2^17 points
  * replays a captured HIP graph of work-stealing kernels; a bigger one is
- * launched directly with one rates workgroup per tile.  Every request is cut
- * into the same tiles as a direct call, so its outputs are bit-identical alone
- * and in a batch.
+ * launched directly with one rates workgroup per tile.  Every form adds in the same
+ * order as a direct call, so a request's outputs are bit-identical alone and in a
+ * batch.
  * ------------------------------------------------------------------------ */
 typedef struct kx_server kx_server;
 typedef int64_t kx_ticket;
@@ -413,8 +416,8 @@ kx_status kx_server_stats_get(kx_server *srv, kx_server_stats *stats);
  * Batched evaluation without allocation.  For callers that cannot allocate
  * device or pinned memory while they run: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  It runs the request
- * server's batch kernels for big batches (one workgroup per tile, the same
- * tiles, so every item's outputs are bit-identical to kx_production_rates /
+ * server's batch kernels for big batches (one workgroup per tile, the same sums
+ * in the same order, so every item's outputs are bit-identical to kx_production_rates /
  * kx_transport and to a served request on the same inputs) over up to
  * KX_BATCH_MAX_ITEMS point sets of one mechanism, without a server: the work
  * list lives in a fixed device array of the library (about 5 KB per device,

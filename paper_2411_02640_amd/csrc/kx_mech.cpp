@@ -11,8 +11,11 @@
 //  * ln A, E_R = E_a / R and the beta = E_R = 0 shortcut of eq:k_f;
 //  * third-body efficiencies as (alpha - default) lists, falloff k_0 and Troe
 //    parameters (inverse temperatures);
-//  * a species-major gather list per reaction chunk for wdot_k = sum_i nu_ki R_i,
-//    padded to one trip count and interleaved for coalesced loads;
+//  * the gather lists of wdot_k = sum_i nu_ki R_i: one stream per wave and chunk for
+//    the one-lane-per-point kernels, lists of pairs of rate rows for the calls of few
+//    points, and where neither runs one list per species and chunk, padded to one trip
+//    count and interleaved for coalesced loads (each laid out only for a mechanism
+//    whose kernels read it);
 //  * Gibbs coefficients of eq:Ck pre-scaled per range, raw NASA-7 for cp / h;
 //  * Wilke constants c1_kj = (8 (1 + W_k/W_j))^(-1/2) and W_k^(1/4) (so that
 //    (W_j/W_k)^(1/4) separates into per-species factors), and the ln T fit
@@ -964,13 +967,12 @@ kx_status build_mech(const kx_mech_desc *d, int device, bool host_only, kx_mech 
 
     // ---- species-major gather lists per reaction chunk, where a kernel reads them:
     // rates above kWideMaxSpecies, QSS rates by one wave per point, the Jacobian by one
-    // row per thread.  Each species lists
-    // the chunk slots of the reactions that produce it (+q, once per unit of
-    // net nu) and of those that consume it (-q); both lists are padded to a
-    // whole number of eight-entry groups common to all lanes, and a group is
-    // eight 32-bit LDS offsets (32 bytes per lane, so lane k reads it with a
-    // pair of coalesced 16-byte loads).  The rates of progress of two points sit
-    // side by side in LDS, so one offset addresses both.
+    // row per thread.  Each species lists the chunk slots of the reactions that
+    // produce it (+q, once per unit of net nu) and of those that consume it (-q); both
+    // lists are padded to a whole number of eight-entry groups common to all lanes,
+    // and a group is eight 32-bit LDS offsets (32 bytes per lane, so lane k reads it
+    // with a pair of coalesced 16-byte loads).  The rates of progress of two points
+    // sit side by side in LDS, so one offset addresses both.
     std::vector<int32_t> gpos(nchunks), gneg(nchunks), goff(nchunks);
     std::vector<uint32_t> gent;  // 8 per (group, lane)
     size_t ngroups = 0;

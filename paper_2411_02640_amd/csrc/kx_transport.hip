@@ -7,7 +7,9 @@
 //  * the vector-ALU kernel (tables of D_kj fits, or fewer species): lane = point,
 //    the waves of a workgroup divide the species k, whose sums they hold in
 //    registers while j streams over all species; X_j and rho_j come from LDS rows,
-//    every mechanism constant from scalar loads, as an instruction operand;
+//    every mechanism constant from scalar loads, as an instruction operand; in calls
+//    of very many points one thread takes two points and all species in turn, with
+//    the same sums (transport_lanes_tile);
 //  * the symmetric evaluation of D_kj fits (KX_DKJ_SYMMETRIC, §2.2.2 / §2.3.2),
 //    described where it is defined below.
 // Common to them:
@@ -1412,8 +1414,8 @@ template <class F, int FORM> const void *rows_kernel(const MechDev &m)
 // 701 / 660; 48 species (12), 700000 points 1251 / 1339, 2^20 faster; 17 species, 450000
 // points 165 / 147, 24 species 400000 points 218 / 240; 53 species (14), 600000 points
 // 1392 / 1679, 2^20 2400 / 2329; 200 species (13), 450000 points 16999 / 17392, 524288
-// 20009 / 18298, 2^20 40095 / 33910; not with 128 species (13838 / 15787).  Mixed: 33 species, 450000 points
-// 359 / 347, 2^20 849 / 679; 53 species, 2^20 1883 / 1497; 129 species 13488 / 8792; 200
+// 20009 / 18298, 2^20 40095 / 33910; not with 128 species (13838 / 15787).  Mixed: 33
+// species, 450000 points 359 / 347, 2^20 849 / 679; 53 species, 2^20 1883 / 1497; 129 species 13488 / 8792; 200
 // species, 450000 points 9706 / 10167, 2^20 22215 / 20231; 44 species, 786432 points 833
 // / 933, 900000 points equal; 24 species, 700000 points 258 / 281, 2^20 387 / 349; not
 // with 48 (1127 / 1188) or 100 species.  Fits of 1/D_kj (below 24 species), 2^20 points:
