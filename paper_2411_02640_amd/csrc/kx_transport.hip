@@ -1412,10 +1412,11 @@ template <class F, int FORM> const void *rows_kernel(const MechDev &m)
 // / lanes, D_kj fits.  FP64: 33 species (9 waves), 350000 points 466 / 388, 2^20 1425 /
 // 950; 129 species, 2^20 20956 / 14430; 40 species (10), 300000 points 458 / 502, 450000
 // 701 / 660; 48 species (12), 700000 points 1251 / 1339, 2^20 faster; 17 species, 450000
-// points 165 / 147, 24 species 400000 points 218 / 240; 53 species (14), 600000 points
-// 1392 / 1679, 2^20 2400 / 2329; 200 species (13), 450000 points 16999 / 17392, 524288
-// 20009 / 18298, 2^20 40095 / 33910; not with 128 species (13838 / 15787).  Mixed: 33
-// species, 450000 points 359 / 347, 2^20 849 / 679; 53 species, 2^20 1883 / 1497; 129 species 13488 / 8792; 200
+// points 165 / 147, 24 species 400000 points 218 / 240; not with 53 species (14), 600000
+// points 1392 / 1679, 2^20 2400 / 2329, but 2^21 with the rates call before it 6900 /
+// 7070; 200 species (13), 450000 points 16999 / 17392, 524288 20009 / 18298, 2^20 40095 /
+// 33910; not with 128 species (13838 / 15787).  Mixed: 33 species, 450000 points 359 /
+// 347, 2^20 849 / 679; 53 species, 2^20 1883 / 1497; 129 species 13488 / 8792; 200
 // species, 450000 points 9706 / 10167, 2^20 22215 / 20231; 44 species, 786432 points 833
 // / 933, 900000 points equal; 24 species, 700000 points 258 / 281, 2^20 387 / 349; not
 // with 48 (1127 / 1188) or 100 species.  Fits of 1/D_kj (below 24 species), 2^20 points:
@@ -1433,7 +1434,7 @@ template <class F> bool lanes_form(const MechDev &m, int64_t points)
         if (nw <= 11 && nw != 7 && nw != 8) return points >= 420000 && rest >= round / 5;
         if (nw == 12 && points >= 750000) return true;
         return (ns > 64 && (nw == 12 || nw == 13) && points >= 500000 && points <= round) ||
-               ((nw == 13 || nw == 14) && points >= 900000 && rest >= round * 9 / 20);
+               (ns > 64 && (nw == 13 || nw == 14) && points >= 900000 && rest >= round * 9 / 20);
     }
     if (ns > 128 && nw == 9) return true;
     if (rest < round / 4) return false;
