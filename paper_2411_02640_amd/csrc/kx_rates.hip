@@ -954,11 +954,21 @@ kx_status launch_few(const MechDev &m, int precision, int nt, int64_t points, vo
 // depends on it (FP64, us a call, one point per workgroup / tiles): 9 species (21
 // reactions) 7.0 / 6.6 at any size; 17 (119) 8.1 / 10.1 at 2000 points, 11.2 / 10.1
 // at 4096; 53 (371) 6.6 / 22.7 at 1 point, 9.0 / 23.1 at 1000, 18.9 / 23.2 at 4096,
-// 25.6 / 23.3 at 5000; 128 (896) 8.1 / 64.6 at 1 point, 37 / 66 at 4096.
+// 25.6 / 23.3 at 5000; 128 (896) 8.1 / 64.6 at 1 point, 37 / 66 at 4096.  Above 120
+// species a tile has so few rate rows that points past what the CUs hold at once pay:
+// 128 (896), 5000 points 53 / 66, 6000 55 / 66 (mixed 62 / 68), 7000 60 / 66 (69 / 68);
+// 128 (1231), 6144 points 73 / 87 (86 / 90); 128 (2500), 5000 points 138 / 166 (162 /
+// 172), 6144 173 / 166; not 100 (700), 6000 points 45 / 45 (52 / 45).  Nor do up to 4096
+// have to be resident at once where the reactions' LDS leaves fewer places: 128 (1231),
+// 4096 points 60 / 87 (68 / 89), 53 (2000) 74 / 101 (96 / 119).
 int rates_few_threads(const MechDev &m, int64_t points)
 {
-    const int64_t most = m.wnw == 0 || m.nr <= 64 ? 0 : (m.nr <= 160 ? 2048 : 4096);
-    return points <= most ? few_threads(points, few_lds_bytes(m)) : 0;
+    const size_t lds = few_lds_bytes(m);
+    if (m.wnw == 0 || m.nr <= 64 || lds > 160 * 1024) return 0;
+    const int64_t most = m.nr <= 160 ? 2048 : m.ns <= 120 ? 4096 : m.nr <= 1280 ? 6144 : 5120;
+    if (points > most) return 0;
+    const int nt = few_threads(points, lds);
+    return nt ? nt : kWave;
 }
 
 // Points at the end of a call of n points that go one to a workgroup, after tiles

@@ -13,8 +13,8 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-def _mech(ns, nq=0, seed=0, **kw):
-    nr = 7 * ns
+def _mech(ns, nq=0, seed=0, nr=0, **kw):
+    nr = nr or 7 * ns
     fall, three, lind = max(1, nr * 6 // 100), nr // 10, nr // 50
     return I.make_mechanism(I.MechSpec(ns, nr - fall - three - lind, three, lind, fall,
                                        seed=seed or 9000 + ns, n_qss=nq, **kw))
@@ -91,7 +91,9 @@ RATES = {"17sp": lambda: _mech(17),                    # 8 waves a tile, 119 rea
          "53X": lambda: I.make_mechanism(I.MECH_53X),  # 12 waves, every reaction form
          "53O": lambda: I.make_mechanism(I.MECH_53O),
          "57sp": lambda: _mech(57),                    # 16 waves
-         "128sp": lambda: _mech(128)}
+         "128sp": lambda: _mech(128),
+         "128sp-1231": lambda: _mech(128, nr=1231),    # one wave per point: not all resident
+         "53sp-2000": lambda: _mech(53, nr=2000)}
 
 
 @pytest.mark.parametrize("name", ["9sp", "200sp"] + list(RATES))
@@ -110,9 +112,10 @@ def test_rates(name):
         print("[gpu-case] rates call sizes", name, prec, flush=True)
         w = kx.production_rates(dm, *d, precision=prec)
         assert bool(torch.isfinite(w).all())
-        for m in (1, 512, 513, 1025, 2048, 2049, 4096, 4097, 16384, 16385, 16384 + 2048, n - 1):
+        for m in (1, 512, 513, 1025, 2048, 2049, 3500, 4096, 4097, 5121, 6144, 6145, 16384, 16385,
+                  16384 + 2048, 16384 + 4096, n - 1):
             assert torch.equal(kx.production_rates(dm, *_first(d, m), precision=prec), w[:, :m]), m
-        for sizes in ((1, 700, 0, 65), (2048, 2049)):
+        for sizes in ((1, 700, 0, 65), (2048, 2049), (6143, 1)):
             sets = [_first(d, m) for m in sizes]
             for out, m in zip(kx.batch_noalloc(dm, sets, precision=prec), sizes):
                 assert torch.equal(out[0], w[:, :m]), m
