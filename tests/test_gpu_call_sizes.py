@@ -96,12 +96,16 @@ RATES = {"17sp": lambda: _mech(17),                    # 8 waves a tile, 119 rea
          "53sp-2000": lambda: _mech(53, nr=2000)}
 
 
-@pytest.mark.parametrize("name", ["9sp", "200sp"] + list(RATES))
+# the ends of the ranges of 4, 8 and 12 waves a tile
+ENDS = {f"{ns}sp": (lambda ns=ns: _mech(ns)) for ns in (16, 32, 33, 56)}
+
+
+@pytest.mark.parametrize("name", ["9sp", "200sp"] + list(RATES) + list(ENDS))
 def test_rates(name):
     """Also the points past the first tile of every CU, and the batched call."""
     from paper_2411_02640_amd import kx
     mech = {"9sp": lambda: I.make_mechanism(I.MECH_9),
-            "200sp": lambda: I.make_mechanism(I.MECH_200), **RATES}[name]()
+            "200sp": lambda: I.make_mechanism(I.MECH_200), **RATES, **ENDS}[name]()
     ns, n = mech["n_species"], 16384 + 4097
     dm = kx.Mechanism(mech, 0)
     d = _states(ns, n)
@@ -122,14 +126,14 @@ def test_rates(name):
     dm.close()
 
 
-@pytest.mark.parametrize("name", list(RATES))
+@pytest.mark.parametrize("name", list(RATES) + list(ENDS))
 def test_small_calls_against_the_oracle(name):
     """One point per workgroup (the oracle checks the first 70 of 700 points)."""
     from oracle import oracle as O
     from paper_2411_02640_amd import kx
 
     from . import parity as PM
-    mech = RATES[name]()
+    mech = {**RATES, **ENDS}[name]()
     T, p, Y = I.make_states(mech["n_species"], I.StateSpec(700, seed=92, p_atm_range=(1.0, 40.0),
                                                            dirichlet_alpha=0.3))
     ref, s = O.OracleMech(mech).production_rates(T[:70], p[:70], np.ascontiguousarray(Y[:, :70]))
